@@ -352,6 +352,8 @@ int fmd_autotune_enable(fmd_model* m, int32_t enable);
  * fmd_tuning_set fixes the choice of one of these sites for the padded token counts in
  * [2^tokens_log2, 2^(tokens_log2 + 1)) (rows padded to a multiple of 256), e.g. to reuse a
  * table measured earlier or to compare candidates.
+ * Calls of at most 16384 padded rows whose choice is not fixed run these two kernels (and the
+ * fused MLP kernel, which has no site) in a form for few rows, with the same results.
  * Errors: FMD_E_INVALID for a null model, another site, a bucket outside [0, 40) or a
  * candidate the model's kernels do not offer. */
 enum { FMD_TUNE_ATTN_QUERY_TILE = 5, FMD_TUNE_FUSED_QKV = 6, FMD_TUNE_FUSED_OQC = 7 };

@@ -24,28 +24,16 @@
 // holds W[16 ks + 8 (l/32) + j][32 nb + l%32], j = 0..7, as 8 consecutive bf16; fragments
 // are stored [N/32][K/16][64 lanes], so one wave reads one contiguous kilobyte per fragment.
 
-#include "common.h"
-#include "kernels.h"
+#include "block_common.h"
 
 namespace fmd {
 namespace {
 
-constexpr int kD = 256;              // model width
-constexpr int kDh = 32;              // head width: wave w of a 256-wide slab = head w
 constexpr int kBM = 128;             // token rows per workgroup
-constexpr int kWaves = 8;            // wave w owns columns [32w, 32w + 32) of a 256-wide slab
-constexpr int kThreads = 64 * kWaves;
 constexpr int kRing = 8;             // weight fragments in flight per wave
-constexpr int kLdA = kD + 8;         // LDS pitch (bf16) of the 128 x 256 activation tile
 constexpr int kBH = 128;             // MLP hidden units per chunk
 constexpr int kLdH = kBH + 8;        // LDS pitch (bf16) of a hidden chunk
-constexpr int kKs = kD / 16;         // fragments along K = 256
-
-__device__ __forceinline__ int acc_row(int mi, int r, int lane) {
-  return mi * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-}
-
-__device__ __forceinline__ bf16x8 as_bf16x8(u32x4 v) { return __builtin_bit_cast(bf16x8, v); }
+constexpr int kLdH8 = kBH + 16;      // bytes per row of an FP8 hidden chunk
 
 // acc[mi] += A[row0 + 32 mi + .., k] x B over `nks` fragments along K, A in LDS (pitch ld,
 // first K column 0). B fragments stream through a ring of kRing registers: on entry the
@@ -87,32 +75,6 @@ __device__ __forceinline__ void mfma_phase(f32x16 (&acc)[TM], const bf16* __rest
   }
 }
 
-// Global row access in the accumulator layout. Element (mi, r) of a lane sits at byte
-// (32 mi + 8 (r/4) + r%4) * pitch + lane_off from the tile's first row, where
-// lane_off = (4 (lane/32) * ld + col) * sizeof(elem). The row-group part is added to a
-// wave-uniform base and r%4 becomes an immediate offset, so only one 32-bit per-lane
-// offset stays live instead of one 64-bit address per element.
-template <typename E, int LD>
-struct RowIo {
-  const char* base;     // wave-uniform: first row of the tile
-  uint32_t lane_off;
-  __device__ RowIo(const E* X, int64_t m0, int col, int lane)
-      : base((const char*)(X + m0 * LD)),
-        lane_off((uint32_t)((4 * (lane >> 5) * LD + col) * sizeof(E))) {
-    // opaque to the compiler: the addresses are formed here, where they are used, and not
-    // computed early and held live across the phases in between
-    asm volatile("" : "+v"(lane_off));
-  }
-  __device__ __forceinline__ E* at(int mi, int r) const {
-    const char* gb = base + (size_t)(mi * 32 + 8 * (r >> 2)) * LD * sizeof(E);
-    return (E*)(gb + lane_off + (r & 3) * LD * sizeof(E));
-  }
-};
-
-// Every row and tile transfer of these kernels is a non-temporal load or store: the rows
-// stream through once, and kept in L2 they would evict the weight fragments that every
-// workgroup re-reads.
-//
 // acc = rows m0.. of X (FP32, pitch kD) at the wave's columns, plus bias (may be null).
 template <int TM>
 __device__ __forceinline__ void load_rows(f32x16 (&acc)[TM], const float* __restrict__ X,
@@ -133,35 +95,6 @@ __device__ __forceinline__ void fill(f32x16 (&acc)[TM], float bv) {
 #pragma unroll
     for (int r = 0; r < 16; ++r) acc[mi][r] = bv;
 }
-
-// ROWS x 256 BF16 tile at rows m0.. of a head-major attention output [8 heads][Mp][32]
-// (plane = Mp x 32 elements) into LDS (pitch kLdA, row-major): consecutive threads read
-// consecutive 16-byte chunks of one head's rows.
-template <int ROWS, int NT = kThreads>
-__device__ __forceinline__ void tile_hm_to_lds(bf16* __restrict__ A, const bf16* __restrict__ S,
-                                               int64_t plane, int64_t m0, int tid) {
-  constexpr int kChunks = ROWS * kD / 8;                // 16-byte chunks
-  constexpr int kPer = kChunks / NT;
-  constexpr int kHeadChunks = ROWS * kDh / 8;           // chunks of one head's rows
-  u32x4 v[kPer];
-#pragma unroll
-  for (int i = 0; i < kPer; ++i) {
-    const int idx = tid + i * NT, hd = idx / kHeadChunks, rem = idx % kHeadChunks;
-    const u32x4* src = (const u32x4*)((const char*)(S + hd * plane + m0 * kDh) + (uint32_t)rem * 16);
-    v[i] = __builtin_nontemporal_load(src);
-  }
-#pragma unroll
-  for (int i = 0; i < kPer; ++i) {
-    const int idx = tid + i * NT, hd = idx / kHeadChunks, rem = idx % kHeadChunks;
-    *(u32x4*)(A + (rem / (kDh / 8)) * kLdA + hd * kDh + (rem % (kDh / 8)) * 8) = v[i];
-  }
-}
-
-// Cross-lane data movement inside 16-lane rows (DPP controls).
-constexpr int kDppXor1 = 0xB1;        // quad_perm [1,0,3,2]: lane i <- lane i ^ 1
-constexpr int kDppXor2 = 0x4E;        // quad_perm [2,3,0,1]: lane i <- lane i ^ 2
-constexpr int kDppHalfMirror = 0x141; // lane i <- lane 7 - i within each group of 8
-constexpr int kDppRor8 = 0x128;       // lane i <- lane (i + 8) mod 16, i.e. i ^ 8
 
 // One halving step of the transpose-reduction: lanes pair up across lane bit `bit` (the DPP
 // partner differs from the lane in that bit and agrees in every bit already reduced); of the
@@ -311,39 +244,10 @@ __device__ __forceinline__ void store_rows_bf16(const f32x16 (&acc)[TM], bf16* _
     for (int r = 0; r < 16; ++r) __builtin_nontemporal_store((bf16)acc[mi][r], io.at(mi, r));
 }
 
-// GELU(z) = z/2 (1 + erf(z / sqrt 2)) with erf by Abramowitz & Stegun 7.1.27:
-// erf(x) = 1 - (1 + a1 x + a2 x^2 + a3 x^3 + a4 x^4)^-4 for x >= 0, absolute error at most
-// 5e-4, far below the BF16 rounding of the result (relative step 2^-8). Branch-free (a
-// library erf branches on |x|), one hardware reciprocal and no exponential. The variable is
-// u = z / sqrt(2 ln 2) (the callers fold the bias into it as bu = bias / sqrt(2 ln 2)), so
-// x = |u| sqrt(ln 2), whose powers are folded into the coefficients b_k = a_k (ln 2)^(k/2);
-// with h = sqrt(ln 2 / 2), GELU = h (u + |u| erf(x)). 10 vector instructions per value.
-constexpr float kGeluU = 0.84932180028801904f;   // 1 / sqrt(2 ln 2)
-__device__ __forceinline__ float gelu_as(float a, float bu) {
-  constexpr float s = 0.83255461115769775f;   // sqrt(ln 2)
-  constexpr float b1 = 0.278393f * s, b2 = 0.230389f * s * s, b3 = 0.000972f * s * s * s,
-                  b4 = 0.078108f * s * s * s * s;
-  constexpr float h = 0.5f / kGeluU;
-  const float u = fmaf(a, kGeluU, bu);
-  const float x = fabsf(u);
-  float q = fmaf(b4, x, b3);
-  q = fmaf(q, x, b2);
-  q = fmaf(q, x, b1);
-  q = fmaf(q, x, 1.0f);
-  q = q * q;
-  const float r = __builtin_amdgcn_rcpf(q * q);
-  const float he = fmaf(-h, r, h);                  // h erf(|x|)
-  return fmaf(x, he, u * h);
-}
-
 // ---- helpers of the 64-row MLP kernel: four waves, wave w owning output column blocks
 // 2w and 2w + 1 (64 columns) of all rows and hidden column block w of every chunk.
 constexpr int kWaves4 = 4;
 constexpr int kThreads4 = 64 * kWaves4;
-// sched_barrier mask: instructions of these kinds may be scheduled across it (VALU 0x2,
-// SALU 0x4, LDS reads 0x100); vector-memory loads and MFMAs may not
-constexpr int kKeepLoadsAndMfma = 0x2 | 0x4 | 0x100;
-
 // Fragment t of a weight stream over NC column blocks taken together: K step t / NC of
 // column block t % NC (blocks cstride fragments-of-64-lanes apart).
 template <int NC>
@@ -555,33 +459,6 @@ __device__ __forceinline__ float head_partial(const f32x16 (&y)[2][2], float w0,
 
 // ---------------------------------------------------------------------------------------
 
-// Input embedding of block 0, formed in the QKV kernel instead of read from H, for a stage
-// whose time is the same for every row: row r is temb + sum_k xs[r][k] W_xin[k] over the 9
-// state features, in that order (the order of the embedding kernel, so the rows are the
-// same), and is stored to H. Rows at or past T (padding) are zero. (Per-event times would
-// need a time-embedding row per tile row; those calls keep the embedding kernel.)
-struct EmbedRows {
-  const float* xs;             // state rows, pitch kEmbLd floats, first 9 used
-  int64_t T;
-  const float* temb;           // [256] time embedding of the stage, b_xin included
-  const float* W;              // W_xin [9][256]
-  float* H;                    // [Mp][256] output
-};
-constexpr int kEmbLd = 16;     // pitch of the ODE state rows
-constexpr int kEmbF9 = 9;
-
-// Which row tiles a launch covers: tile b of the grid is rows [ROWS t, ROWS t + ROWS) with
-// t = tiles[b] when a map is given (the serving loop skips the tiles of gaps between
-// requests), t = b otherwise. Mp is the padded row count of the call: the head-major planes
-// hold Mp rows each, whatever tiles run.
-struct RowMap {
-  const int32_t* tiles;
-  int64_t Mp;
-  __device__ __forceinline__ int64_t first_row(int rows) const {
-    return (int64_t)(tiles ? tiles[blockIdx.x] : (int32_t)blockIdx.x) * rows;
-  }
-};
-
 template <int TM, bool EMBED>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(TM == 2 ? 4 : 2))) void k_fused_qkv(const float* __restrict__ H,
                                                         const float* __restrict__ g,
@@ -683,80 +560,10 @@ __global__ __launch_bounds__(kThreads) void k_fused_oqc(
   store_rows_bf16<kDh>(acc, qc + (int64_t)w * plane, m0, lane & 31, lane);   // head-major
 }
 
-// ---- FP8 (OCP e4m3) operands of the MLP's two projections (the FP8 precision form).
-// The LayerNorm tile and the hidden chunks are FP8 bytes in LDS; W_up and W_dn are FP8
-// fragments of the weights times a power of two per output column (so that the column's
-// largest magnitude lies in (224, 448]) for the 32 x 32 x 64 matrix instruction: fragment
-// (nb, ks) of lane l holds W[64 ks + 32 (l/32) + j][32 nb + l%32] s_col, j < 32, as 32 bytes,
-// stored [N/32][K/64][64 lanes]. A operands from LDS take the same k order (row l%32, bytes
-// 64 ks + 32 (l/32) ..), so products pair the same k on both sides. The up-projection output
-// is scaled back by 1/s per hidden column before the GELU; the down-projection accumulates
-// onto the residual rows multiplied by s per output column and divides by it afterwards,
-// exact for powers of two. Accumulation, statistics, GELU and residual stay FP32.
-typedef int i32x8 __attribute__((ext_vector_type(8)));
-
-struct Mlp8 {
-  const i32x8* up;      // W_up s_up fragments [1024/32][256/64][64]
-  const i32x8* dn;      // W_dn s_dn fragments [256/32][1024/64][64]
-  const float* up_inv;  // 1 / s_up per hidden column [1024]
-  const float* dn_scale;   // s_dn per output column [256]
-  const float* dn_inv;  // 1 / s_dn [256]
-};
-
-constexpr int kLdA8 = kD + 16;        // bytes per row of the FP8 LayerNorm tile
-constexpr int kLdH8 = kBH + 16;       // bytes per row of an FP8 hidden chunk
-constexpr int kKs8 = kD / 64;         // 64-deep K steps over d
-
-__device__ __forceinline__ f32x16 mfma_f8(i32x8 a, i32x8 b, f32x16 c) {
-  // block scales 2^(127 - 127) = 1: plain FP8 x FP8 products
-  return __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a, b, c, 0, 0, 0, 127, 0, 127);
-}
-
-// x rounded to the nearest e4m3 value (ties to even), as one byte
-__device__ __forceinline__ uint32_t to_fp8(float x) {
-  return (uint32_t)__builtin_amdgcn_cvt_pk_fp8_f32(x, x, 0, false) & 0xFFu;
-}
-
-// A operand of one 32-row block: row `row` of an FP8 tile (pitch ld bytes), K step ks
-__device__ __forceinline__ i32x8 lds_frag8(const uint8_t* __restrict__ t, int ld, int row, int ks,
-                                           int lane) {
-  const uint8_t* p = t + row * ld + ks * 64 + (lane >> 5) * 32;
-  const u32x4 lo = *(const u32x4*)p, hi = *(const u32x4*)(p + 16);
-  i32x8 r;
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    r[i] = (int)lo[i];
-    r[4 + i] = (int)hi[i];
-  }
-  return r;
-}
-
 // MLP block on 64-row tiles with four waves: two workgroups share a CU, one wave of each per
 // SIMD, so one workgroup's barriers, LDS traffic and loads overlap the other's matrix work.
 // With QKV, the kernel goes on to the next block's LN1 + [Q|K|V] projection from the final
 // rows still in registers (as k_fused_qkv does from H), writing head-major planes.
-struct NextQkv {
-  const float* g;        // LN1 gain and shift of the next block
-  const float* s;
-  const u32x4* Wf;       // its W_qkv fragments
-  const float* bias;
-  bf16* qkv;             // [3][8 heads][Mp][32]
-};
-
-// With HEAD (the last block), the kernel applies the output head to the final rows instead:
-// LN_f, the 9-wide projection (FP32, per-wave partial sums over the wave's 64 columns by the
-// transpose-reduction, then the 4 wave partials in wave order) and the ODE update of the
-// state, as the separate head kernel does; the residual rows are then not stored.
-struct NextHead {
-  const float* g;        // LN_f gain and shift
-  const float* s;
-  const float* Wt;       // W_out transposed: row c = weights of output c (c < 9), 256 wide
-  const float* b;
-  OdeArgs ode;
-};
-
-enum MlpTail { kTailStats = 0, kTailQkv = 1, kTailHead = 2 };
-
 template <int TM, int TAIL, bool F8>
 __global__ __launch_bounds__(kThreads4) __attribute__((amdgpu_waves_per_eu(2))) void k_fused_mlp(
     const bf16* __restrict__ att, const u32x4* __restrict__ Wf_oc, const float* __restrict__ b_oc,
@@ -1185,50 +992,28 @@ hipError_t launch_fused_oqc(hipStream_t st, int64_t Mp, const void* att, const v
   return hipGetLastError();
 }
 
-hipError_t launch_fused_mlp(hipStream_t st, int64_t Mp, const void* att, const void* Wf_oc,
-                            const float* b_oc, float* H, const float* g, const float* s,
-                            const void* Wf_up, const float* b_up, const void* Wf_dn,
-                            const float* b_dn, float2* stats_out, const float* g1n,
-                            const float* s1n, const void* Wf_qkv_n, const float* b_qkv_n,
-                            void* qkv, const float* gf, const float* sf, const float* Wt_out,
-                            const float* b_out, const OdeArgs* head, const Fp8Mlp* fp8,
-                            const int32_t* tiles, int64_t n_tiles) {
-  unsigned gsz = 0;
-  if (!fused_grid(Mp, 64, tiles, n_tiles, &gsz)) return hipErrorInvalidValue;
-  if (gsz == 0) return hipSuccess;
-  const RowMap rm{tiles, Mp};
-  if (qkv && head) return hipErrorInvalidValue;
-  if (fp8 && (!fp8->up || !fp8->dn || !fp8->up_inv || !fp8->dn_scale || !fp8->dn_inv))
-    return hipErrorInvalidValue;
-  const Mlp8 f8 = fp8 ? Mlp8{(const i32x8*)fp8->up, (const i32x8*)fp8->dn, fp8->up_inv,
-                             fp8->dn_scale, fp8->dn_inv}
-                      : Mlp8{};
-  const dim3 grid(gsz);
-#define FMD_MLP_GO(TAIL, NQ, NH)                                                              \
-  do {                                                                                        \
-    if (fp8)                                                                                  \
-      hipLaunchKernelGGL((k_fused_mlp<2, TAIL, true>), grid, dim3(kThreads4), 0, st,          \
-                         (const bf16*)att, (const u32x4*)Wf_oc, b_oc, H, g, s,                \
-                         (const u32x4*)Wf_up, b_up, (const u32x4*)Wf_dn, b_dn, stats_out, NQ, \
-                         NH, f8, rm);                                                         \
-    else                                                                                      \
-      hipLaunchKernelGGL((k_fused_mlp<2, TAIL, false>), grid, dim3(kThreads4), 0, st,         \
-                         (const bf16*)att, (const u32x4*)Wf_oc, b_oc, H, g, s,                \
-                         (const u32x4*)Wf_up, b_up, (const u32x4*)Wf_dn, b_dn, stats_out, NQ, \
-                         NH, f8, rm);                                                         \
-  } while (0)
-  if (qkv) {
-    if (!g1n || !s1n || !Wf_qkv_n || !b_qkv_n) return hipErrorInvalidValue;
-    const NextQkv nq{g1n, s1n, (const u32x4*)Wf_qkv_n, b_qkv_n, (bf16*)qkv};
-    FMD_MLP_GO(kTailQkv, nq, NextHead{});
-  } else if (head) {
-    if (!gf || !sf || !Wt_out || !b_out || head->nf != 9) return hipErrorInvalidValue;
-    const NextHead nh{gf, sf, Wt_out, b_out, *head};
-    FMD_MLP_GO(kTailHead, NextQkv{}, nh);
-  } else {
-    FMD_MLP_GO(kTailStats, NextQkv{}, NextHead{});
-  }
-#undef FMD_MLP_GO
+bool fused_mlp_args(const FusedMlpArgs& a) {
+  if (a.qkv && (a.head || !a.g1n || !a.s1n || !a.Wf_qkv_n || !a.b_qkv_n)) return false;
+  if (a.head && (!a.gf || !a.sf || !a.Wt_out || !a.b_out || a.head->nf != 9)) return false;
+  const Fp8Mlp* f = a.fp8;
+  return !f || (f->up && f->dn && f->up_inv && f->dn_scale && f->dn_inv);
+}
+
+hipError_t launch_fused_mlp(hipStream_t st, int64_t Mp, const FusedMlpArgs& a) {
+  unsigned grid = 0;
+  if (!fused_grid(Mp, 64, a.tiles, a.n_tiles, &grid) || !fused_mlp_args(a)) return hipErrorInvalidValue;
+  if (grid == 0) return hipSuccess;
+  const MlpTailArgs t = mlp_tail_args(a);
+  auto* k = a.fp8 ? (a.qkv    ? k_fused_mlp<2, kTailQkv, true>
+                     : a.head ? k_fused_mlp<2, kTailHead, true>
+                              : k_fused_mlp<2, kTailStats, true>)
+                  : (a.qkv    ? k_fused_mlp<2, kTailQkv, false>
+                     : a.head ? k_fused_mlp<2, kTailHead, false>
+                              : k_fused_mlp<2, kTailStats, false>);
+  hipLaunchKernelGGL(k, dim3(grid), dim3(kThreads4), 0, st, (const bf16*)a.att,
+                     (const u32x4*)a.Wf_oc, a.b_oc, a.H, a.g, a.s, (const u32x4*)a.Wf_up, a.b_up,
+                     (const u32x4*)a.Wf_dn, a.b_dn, a.stats_out, t.nq, t.nh, t.f8,
+                     RowMap{a.tiles, Mp});
   return hipGetLastError();
 }
 

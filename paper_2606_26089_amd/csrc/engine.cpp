@@ -341,7 +341,9 @@ int stage_events(fmd_model* m, const fmd_events_in* ev, Call& c, const int64_t* 
         break;
       }
       m->tune_all[TS_ATTN][b][k] = us;
-      if (best < 0 || us < best_us) best = k, best_us = us;
+      // a launch of a few microseconds is timed no better than to about a tenth: the smaller
+      // tile, which spreads the work over more CUs, stays unless a larger one is clearly faster
+      if (best < 0 || us < best_us * (best_us < 20.f ? 0.9f : 1.f)) best = k, best_us = us;
     }
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
@@ -462,6 +464,24 @@ int attn_tile_for(const fmd_model* m, int64_t Tp) {
 // call runs a map of 64-row tiles.
 int fused_rows_for(const fmd_model* m, const Call& c, int slot) {
   return !c.tiles && m->tune[slot][bucket_of(c.Tp)] == 1 ? 128 : 64;
+}
+
+// Rows per workgroup of the small-call kernels (block_small.hip), 0 for the throughput ones.
+// A throughput workgroup (64 rows, four waves) takes 33 us through its MLP segment whether or
+// not it has the chip to itself, so while every row tile can have a CU of its own the split
+// that makes the single tile shortest wins: 32-row tiles up to 256 of them (4,103 rows: 406 ->
+// 295 us per evaluation), then 64-row tiles of eight waves up to 256 (14,276 rows: 510 -> 465).
+// Past that a CU runs several tiles and the throughput kernels, which read each weight for
+// twice the rows or keep two independent workgroups per CU, are faster (20,810 rows: 720 us
+// against 734 and 757). The results are bitwise the same.
+int small_rows(const Call& c) {
+  constexpr int64_t kCus = 256;
+  const int64_t rows = c.tiles ? c.n_tiles * 64 : c.Tp;
+  return rows <= 32 * kCus ? 32 : rows <= 64 * kCus ? 64 : 0;
+}
+// The same for the tuned QKV / OQC sites: a choice fixed by fmd_tuning_set stands.
+int small_rows_for(const fmd_model* m, const Call& c, int slot) {
+  return m->tune_fixed[slot][bucket_of(c.Tp)] ? 0 : small_rows(c);
 }
 
 // Launches the GEMM of one tuning slot with a given tiling on the live workspace.
@@ -679,6 +699,8 @@ int net_forward(fmd_model* m, Call& c, const float* t_ev) {
                           m->W_xin, d, w.H, d, w.stats);
     }));
   const double dd = (double)d;
+  const int sr = small_rows(c), sr_qkv = small_rows_for(m, c, TS_FQKV),
+            sr_oqc = small_rows_for(m, c, TS_FOQC);
   bool qkv_ready = false;   // the previous block's MLP kernel formed this block's [Q|K|V]
   for (int l = 0; l < L; ++l) {
     const DevBlock& B = m->blk[l];
@@ -686,6 +708,9 @@ int net_forward(fmd_model* m, Call& c, const float* t_ev) {
       if (l == 0 && embed_in_qkv)
         FMD_TRY(timed(m, c.st, FMD_K_GEMM_QKV, 2.0 * Td * dd * 3 * dd + 2.0 * Td * 9 * dd,
                       Td * (dd * 4 + kStateLd * 4) + (Td + dd) * 3 * dd * es, [&] {
+          if (sr_qkv)
+            return launch_small_embed_qkv(c.st, c.Tp, sr_qkv, w.xs, kStateLd, 9, c.T, w.temb, m->W_xin,
+                                          w.H, B.g1, B.s1, B.Fqkv, B.bqkv, w.qkv);
           return launch_fused_embed_qkv(c.st, c.Tp, w.xs, kStateLd, 9, c.T, w.temb, m->W_xin,
                                         w.H, B.g1, B.s1, B.Fqkv, B.bqkv, w.qkv,
                                         fused_rows_for(m, c, TS_FQKV));
@@ -693,6 +718,9 @@ int net_forward(fmd_model* m, Call& c, const float* t_ev) {
       else if (!qkv_ready)
         FMD_TRY(timed(m, c.st, FMD_K_GEMM_QKV, 2.0 * Td * dd * 3 * dd,
                       Td * dd * 4 + (Td + dd) * 3 * dd * es, [&] {
+          if (sr_qkv)
+            return launch_small_qkv(c.st, c.Tp, sr_qkv, w.H, B.g1, B.s1, B.Fqkv, B.bqkv, w.qkv,
+                                    c.tiles, c.n_tiles);
           return launch_fused_qkv(c.st, c.Tp, w.H, B.g1, B.s1, B.Fqkv, B.bqkv, w.qkv,
                                   fused_rows_for(m, c, TS_FQKV), c.tiles, c.n_tiles);
         }));
@@ -710,6 +738,9 @@ int net_forward(fmd_model* m, Call& c, const float* t_ev) {
     if (fz & FMD_FUSED_OQC) {
       FMD_TRY(timed(m, c.st, FMD_K_FUSED_OQC, 2.0 * Td * dd * dd * 2,
                     Td * dd * (es + 8 + es) + 2 * dd * dd * es, [&] {
+        if (sr_oqc)
+          return launch_small_oqc(c.st, c.Tp, sr_oqc, w.att, B.Fo, B.bo, w.H, B.g2, B.s2, B.Fqc, B.bqc,
+                                  w.qc, c.tiles, c.n_tiles);
         return launch_fused_oqc(c.st, c.Tp, w.att, B.Fo, B.bo, w.H, B.g2, B.s2, B.Fqc, B.bqc, w.qc,
                                 fused_rows_for(m, c, TS_FOQC), c.tiles, c.n_tiles);
       }));
@@ -757,14 +788,14 @@ int net_forward(fmd_model* m, Call& c, const float* t_ev) {
                     Td * (dd * (es + (fold ? 4 : 8)) + (fold ? 0 : 8)) + 9 * dd * dd * es +
                         (chain ? Td * 3 * dd * es + 3 * dd * dd * es : 0.0) +
                         (fold ? Tv * 9 * 4 * 5 : 0.0), [&] {
-        return launch_fused_mlp(c.st, c.Tp, w.att, B.Foc, B.boc, w.H, B.g3, B.s3, B.Fup, B.bup,
-                                B.Fdn, B.bdn, w.stats, chain ? N->g1 : nullptr,
-                                chain ? N->s1 : nullptr, chain ? N->Fqkv : nullptr,
-                                chain ? N->bqkv : nullptr, chain ? w.qkv : nullptr,
-                                fold ? m->g_f : nullptr, fold ? m->s_f : nullptr,
-                                fold ? m->Wout_pk : nullptr, fold ? m->bout_pk : nullptr,
-                                fold ? c.head : nullptr, m->f8.empty() ? nullptr : &m->f8[l],
-                                c.tiles, c.n_tiles);
+        const FusedMlpArgs a{w.att, B.Foc, B.boc, w.H, B.g3, B.s3, B.Fup, B.bup, B.Fdn, B.bdn,
+                             w.stats, chain ? N->g1 : nullptr, chain ? N->s1 : nullptr,
+                             chain ? N->Fqkv : nullptr, chain ? N->bqkv : nullptr,
+                             chain ? w.qkv : nullptr, fold ? m->g_f : nullptr,
+                             fold ? m->s_f : nullptr, fold ? m->Wout_pk : nullptr,
+                             fold ? m->bout_pk : nullptr, fold ? c.head : nullptr,
+                             m->f8.empty() ? nullptr : &m->f8[l], c.tiles, c.n_tiles};
+        return sr ? launch_small_mlp(c.st, c.Tp, sr, a) : launch_fused_mlp(c.st, c.Tp, a);
       }));
       qkv_ready = chain;
       c.head_done = fold;
@@ -1593,6 +1624,7 @@ int fmd_tuning_set(fmd_model* m, int32_t site, int32_t tokens_log2, int32_t cand
   if (candidate < 0 || candidate >= n) return fail(FMD_E_INVALID, "candidate %d not in [0, %d)", candidate, n);
   const int sl = TS_ATTN + (site - FMD_TUNE_ATTN_QUERY_TILE);
   m->tune[sl][tokens_log2] = (int8_t)candidate;
+  m->tune_fixed[sl][tokens_log2] = true;
   m->tune_us[sl][tokens_log2] = 0.f;
   m->tune_gen++;   // captured graphs hold the previous choice
   return FMD_OK;

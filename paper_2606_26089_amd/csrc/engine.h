@@ -125,6 +125,7 @@ struct fmd_model {
   fmd::GraphKey gkey{};
   fmd_server* server = nullptr;    // attached server (the model's own calls are refused)
   int8_t tune[fmd::TS_COUNT][fmd::kTuneBuckets];   // chosen tiling, -1 = not tuned yet
+  bool tune_fixed[fmd::TS_COUNT][fmd::kTuneBuckets] = {};   // set by the caller, not timed
   float tune_us[fmd::TS_COUNT][fmd::kTuneBuckets]; // its measured time
   float tune_all[fmd::TS_COUNT][fmd::kTuneBuckets][8];   // every candidate's time (0: not run)
   bool timing = false;

@@ -240,16 +240,49 @@ struct Fp8Mlp {
 // inv[n] = 1 / scale[n] (both written, device [N]). K % 64 == 0, N % 32 == 0.
 hipError_t launch_pack_frag8(hipStream_t st, const float* W, int K, int N, void* Wf, float* scale,
                              float* inv);
-hipError_t launch_fused_mlp(hipStream_t st, int64_t Mp, const void* att, const void* Wf_oc,
-                            const float* b_oc, float* H, const float* g, const float* s,
-                            const void* Wf_up, const float* b_up, const void* Wf_dn,
-                            const float* b_dn, float2* stats_out, const float* g1n = nullptr,
-                            const float* s1n = nullptr, const void* Wf_qkv_n = nullptr,
-                            const float* b_qkv_n = nullptr, void* qkv = nullptr,
-                            const float* gf = nullptr, const float* sf = nullptr,
-                            const float* Wt_out = nullptr, const float* b_out = nullptr,
-                            const OdeArgs* head = nullptr, const Fp8Mlp* fp8 = nullptr,
+struct FusedMlpArgs {
+  const void* att;
+  const void* Wf_oc;
+  const float* b_oc;
+  float* H;
+  const float* g;
+  const float* s;
+  const void* Wf_up;
+  const float* b_up;
+  const void* Wf_dn;
+  const float* b_dn;
+  float2* stats_out;
+  const float* g1n;          // with qkv: the next block's LN1, W_qkv fragments and bias
+  const float* s1n;
+  const void* Wf_qkv_n;
+  const float* b_qkv_n;
+  void* qkv;
+  const float* gf;           // with head: LN_f and the output projection
+  const float* sf;
+  const float* Wt_out;
+  const float* b_out;
+  const OdeArgs* head;
+  const Fp8Mlp* fp8;         // FP8 form only
+  const int32_t* tiles;      // optional map of 64-row tiles
+  int64_t n_tiles;
+};
+hipError_t launch_fused_mlp(hipStream_t st, int64_t Mp, const FusedMlpArgs& a);
+
+// The same three kernels for calls whose 64-row tiles do not fill the chip (block_small.hip):
+// row tiles of 32 or 64 rows (`rows`) with eight waves, bitwise the same results. A tile map
+// lists 64-row tiles with either.
+hipError_t launch_small_qkv(hipStream_t st, int64_t Mp, int rows, const float* H, const float* g,
+                            const float* s, const void* Wf, const float* bias, void* qkv,
                             const int32_t* tiles = nullptr, int64_t n_tiles = 0);
+hipError_t launch_small_embed_qkv(hipStream_t st, int64_t Mp, int rows, const float* xs, int ldx,
+                                  int f, int64_t T, const float* temb, const float* W_xin, float* H,
+                                  const float* g, const float* s, const void* Wf,
+                                  const float* bias, void* qkv);
+hipError_t launch_small_oqc(hipStream_t st, int64_t Mp, int rows, const void* att, const void* Wf_o,
+                            const float* b_o, float* H, const float* g, const float* s,
+                            const void* Wf_qc, const float* b_qc, void* qc,
+                            const int32_t* tiles = nullptr, int64_t n_tiles = 0);
+hipError_t launch_small_mlp(hipStream_t st, int64_t Mp, int rows, const FusedMlpArgs& a);
 
 // dst[i] = T(src[i]).
 template <typename T>
