@@ -36,7 +36,8 @@ sys.path.insert(0, ROOT)
 
 import numpy as np  # noqa: E402
 
-PEAK_TFLOPS = {"bf16": 2500.0, "fp32": 157.3}    # MI355X dense matrix peaks
+# MI355X dense matrix peaks; an FP32 product of the GEMM kernels is six BF16 products
+PEAK_TFLOPS = {"bf16": 2500.0, "fp32": 2500.0 / 6}
 WORKLOAD_TEXT = {
     "base": "4096 events, N~U{20..200}, d=256, 6 blocks, 8 heads, RK4 16 steps (64 evaluations)",
     "batch": "65536 events, N~lognormal(median 60, sigma 0.8) in [1, 1000], d=256, 6 blocks, "

@@ -274,7 +274,7 @@ int bucket_of(int64_t Tp);
 int attn_tiles(const fmd_model* m, int* tiles);
 int attn_tile_for(const fmd_model* m, int64_t Tp);
 template <typename F>
-float time_best_us(hipStream_t st, hipEvent_t e0, hipEvent_t e1, F&& launch);
+float time_best_us(hipStream_t st, hipEvent_t e0, hipEvent_t e1, F&& launch, int reps = 3);
 template <typename T>
 hipError_t launch_self_attention(fmd_model* m, const Call& c, int qt, int64_t items,
                                  const AttnBins& bins, const AttnItem* work);
@@ -385,11 +385,34 @@ int stage_events(fmd_model* m, const fmd_events_in* ev, Call& c, const int64_t* 
   return FMD_OK;
 }
 
+hipError_t split_truth_cache(fmd_model* m, hipStream_t st, const float* u, int64_t nT, float* kv) {
+  const int d = m->cfg.d_model, N = 2 * d * m->cfg.n_blocks;
+  SplitArgs p{};
+  p.A = u;
+  p.lda = 9;
+  p.K = d;
+  p.N = N;
+  p.Wf = m->Skv;
+  p.bias = m->bkv;
+  p.g = m->g_t;
+  p.s = m->s_t;
+  p.C = kv;
+  p.ldc = N;
+  p.Win = m->W_tin;
+  p.base = m->b_tin;
+  p.T = p.m_store = nT;   // the rows past them may be another request's
+  return launch_split_gemm(st, SPLIT_KV, round_up(nT, kGemmBM), p);
+}
+
 template <typename T>
 int truth_cache(fmd_model* m, Call& c) {
   Workspace& w = m->ws;
   const fmd_model_config& cf = m->cfg;
   const int d = cf.d_model, L = cf.n_blocks;
+  if (m->split)
+    return timed(m, c.st, FMD_K_OTHER, 2.0 * c.Tt * d * 2 * d * L, [&] {
+      return split_truth_cache(m, c.st, c.u, c.Tt, (float*)w.kv);
+    });
   FMD_TRY(timed(m, c.st, FMD_K_OTHER, 0, [&] {
     return launch_truth_encode<T>(c.st, c.u, 9, 9, c.Tt, m->W_tin, m->b_tin, m->g_t, m->s_t, d,
                                   (T*)w.c, d);
@@ -516,16 +539,16 @@ hipError_t slot_gemm(fmd_model* m, Call& c, int slot, int tile, const DevBlock& 
 // k-slice accumulation order per element), so the choice affects speed only. Runs before
 // the first evaluation of a call, while the activation buffers hold nothing that is used
 // later (the residual stream is rebuilt by the next input embedding).
-// Times one launch sequence: 1 warm-up + 3 timed launches, best of the three, in
+// Times one launch sequence: 1 warm-up + `reps` timed launches, the best of them, in
 // microseconds (negative if a launch failed).
 template <typename F>
-float time_best_us(hipStream_t st, hipEvent_t e0, hipEvent_t e1, F&& launch) {
+float time_best_us(hipStream_t st, hipEvent_t e0, hipEvent_t e1, F&& launch, int reps) {
   if (launch() != hipSuccess) {
     (void)hipGetLastError();
     return -1.f;
   }
   float best = 1e30f;
-  for (int rep = 0; rep < 3; ++rep) {
+  for (int rep = 0; rep < reps; ++rep) {
     float ms = 0.f;
     if (hipEventRecord(e0, st) != hipSuccess || launch() != hipSuccess ||
         hipEventRecord(e1, st) != hipSuccess || hipEventSynchronize(e1) != hipSuccess ||
@@ -585,9 +608,101 @@ int autotune_fused(fmd_model* m, Call& c, int b) {
   return status;
 }
 
+// ---- FP32 path with split products -------------------------------------------------------
+
+TuneSlot split_slot(int cls) {
+  switch (cls) {
+    case SPLIT_PROJ:
+    case SPLIT_PROJ_CROSS: return TS_PROJ_RES;
+    case SPLIT_QC: return TS_PROJ_LN;
+    case SPLIT_UP: return TS_UP;
+    case SPLIT_DOWN: return TS_DOWN;
+    default: return TS_QKV;
+  }
+}
+
+// Arguments of one product of block B on rows A (the embedding form reads the state instead).
+SplitArgs split_args(fmd_model* m, const Call& c, int cls, const DevBlock& B, const void* A,
+                     const float* t_ev) {
+  Workspace& w = m->ws;
+  const int d = m->cfg.d_model;
+  SplitArgs p{};
+  p.A = (const float*)A;
+  p.K = cls == SPLIT_DOWN ? 4 * d : d;
+  p.lda = p.K;
+  p.N = d;
+  p.C = w.H;
+  switch (cls) {
+    case SPLIT_QKV_EMBED:
+      p.A = w.xs;
+      p.lda = kStateLd;
+      p.Win = m->W_xin;
+      p.base = w.temb;
+      p.tok_event = t_ev ? w.tok_event : nullptr;
+      p.H = w.H;
+      p.T = c.T;
+      p.m_store = c.Tp;
+      [[fallthrough]];
+    case SPLIT_QKV:
+      p.N = 3 * d, p.Wf = B.Sqkv, p.bias = B.bqkv, p.g = B.g1, p.s = B.s1, p.C = (float*)w.qkv;
+      break;
+    case SPLIT_PROJ: p.Wf = B.So, p.bias = B.bo; break;
+    case SPLIT_PROJ_CROSS: p.Wf = B.Soc, p.bias = B.boc; break;
+    case SPLIT_QC:
+      p.Wf = B.Sqc, p.bias = B.bqc, p.g = B.g2, p.s = B.s2, p.C = (float*)w.qc;
+      break;
+    case SPLIT_UP:
+      p.N = 4 * d, p.Wf = B.Sup, p.bias = B.bup, p.g = B.g3, p.s = B.s3, p.C = (float*)w.hid;
+      break;
+    default: p.Wf = B.Sdn, p.bias = B.bdn; break;
+  }
+  p.ldc = p.N;
+  return p;
+}
+
+// Times the candidates of every site of the split products (see autotune). Launches of a few
+// microseconds are close together and timed no better than that, so each takes the best of
+// eight, and a later candidate has to be clearly faster.
+int autotune_split(fmd_model* m, Call& c) {
+  const int b = bucket_of(c.Tp);
+  const DevBlock& B = m->blk[0];
+  const int cls[TS_GEMM] = {SPLIT_QKV, SPLIT_PROJ, SPLIT_QC, SPLIT_UP, SPLIT_DOWN};
+  hipEvent_t e0 = nullptr, e1 = nullptr;
+  int status = FMD_OK;
+  for (int sl = 0; sl < TS_GEMM && status == FMD_OK; ++sl) {
+    if (m->tune[sl][b] >= 0) continue;
+    if (!e0) {
+      HIP_TRY(hipEventCreate(&e0));
+      HIP_TRY(hipEventCreate(&e1));
+    }
+    const void* A = sl == TS_PROJ_RES ? m->ws.att : sl == TS_DOWN ? m->ws.hid : m->ws.H;
+    const SplitArgs p = split_args(m, c, cls[sl], B, A, nullptr);
+    int best = -1, rows = 0, parts = 0;
+    float best_us = 0.f;
+    for (int k = 0; k < kSplitCands; ++k) {
+      if (!split_tile(k, c.Tp, p.N, &rows, &parts)) continue;
+      const float us = time_best_us(
+          c.st, e0, e1, [&] { return launch_split_gemm(c.st, cls[sl], c.Tp, p, k); }, 8);
+      if (us < 0.f) {
+        status = fail(FMD_E_DEVICE, "autotune launch failed");
+        break;
+      }
+      m->tune_all[sl][b][k] = us;
+      if (best < 0 || us < best_us * (best_us < 20.f ? 0.95f : 1.f)) best = k, best_us = us;
+    }
+    m->tune[sl][b] = (int8_t)best;
+    m->tune_us[sl][b] = best_us;
+    m->tune_gen++;
+  }
+  if (e0) (void)hipEventDestroy(e0);
+  if (e1) (void)hipEventDestroy(e1);
+  return status;
+}
+
 template <typename T>
 int autotune(fmd_model* m, Call& c) {
   if (!m->autotune || m->kind != 0) return FMD_OK;   // fixed tiling
+  if (m->split) return autotune_split(m, c);
   const int b = bucket_of(c.Tp);
   if (std::is_same<T, bf16>::value && m->fused) FMD_TRY(autotune_fused(m, c, b));
   const int blocks_fused = FMD_FUSED_QKV | FMD_FUSED_OQC | FMD_FUSED_MLP;
@@ -666,10 +781,53 @@ hipError_t launch_self_attention(fmd_model* m, const Call& c, int qt, int64_t it
                              (T*)w.att, ldo, hso);
 }
 
+// The network of net_forward on the FP32 path with split products (d_model <= 256).
+int net_forward_split(fmd_model* m, Call& c, const float* t_ev) {
+  Workspace& w = m->ws;
+  const int d = m->cfg.d_model, L = m->cfg.n_blocks, Hh = m->cfg.n_heads, dh = d / Hh;
+  const double Td = (double)c.T;
+  float* kv = (float*)w.kv;
+  FMD_TRY(timed(m, c.st, FMD_K_OTHER, 0, [&] {
+    return launch_time_embed(c.st, t_ev, t_ev ? nullptr : w.desc, w.ctr, 0.f, t_ev ? (int)c.E : 1,
+                             m->W_time, m->b_time, m->b_xin, m->cfg.t_embed_dim, d, w.temb);
+  }));
+  auto product = [&](int timer, int cls, const DevBlock& B, const void* A) {
+    const SplitArgs p = split_args(m, c, cls, B, A, t_ev);
+    // operands read once, results written once (a residual update reads and writes its rows)
+    const bool embed = cls == SPLIT_QKV_EMBED;
+    const bool resid = cls == SPLIT_PROJ || cls == SPLIT_PROJ_CROSS || cls == SPLIT_DOWN;
+    const double bytes = 4.0 * (Td * (embed ? kStateLd + d : p.K) + Td * p.N * (resid ? 2 : 1) +
+                                (double)p.K * p.N);
+    return timed(m, c.st, timer, 2.0 * Td * p.K * p.N + (embed ? 2.0 * Td * 9 * d : 0.0), bytes, [&] {
+      return launch_split_gemm(c.st, cls, c.Tp, p, m->tune[split_slot(cls)][bucket_of(c.Tp)]);
+    });
+  };
+  for (int l = 0; l < L; ++l) {
+    const DevBlock& B = m->blk[l];
+    FMD_TRY(product(FMD_K_GEMM_QKV, l == 0 ? SPLIT_QKV_EMBED : SPLIT_QKV, B, w.H));
+    FMD_TRY(timed(m, c.st, FMD_K_ATTN_SELF, 4.0 * c.sum_n2 * d, Td * 4 * d * 4, [&] {
+      return launch_self_attention<float>(m, c, c.qt, c.items, c.bins, w.work);
+    }));
+    FMD_TRY(product(FMD_K_GEMM_PROJ, SPLIT_PROJ, B, w.att));
+    FMD_TRY(product(FMD_K_GEMM_QC, SPLIT_QC, B, w.H));
+    FMD_TRY(timed(m, c.st, FMD_K_ATTN_CROSS, 4.0 * c.sum_nx * d, (Td * 2 + c.Tt * 2.0) * d * 4, [&] {
+      const float* kb = kv + (size_t)l * 2 * d;
+      return launch_attention<float>(c.st, true, dh, Hh, c.qt, c.items_x, c.bins_x, w.work + c.work_x,
+                                     (const float*)w.qc, d, dh, kb, kb + d, 2 * d * L, dh,
+                                     (float*)w.att, d, dh);
+    }));
+    FMD_TRY(product(FMD_K_GEMM_PROJ, SPLIT_PROJ_CROSS, B, w.att));
+    FMD_TRY(product(FMD_K_GEMM_UP, SPLIT_UP, B, w.H));
+    FMD_TRY(product(FMD_K_GEMM_DOWN, SPLIT_DOWN, B, w.hid));
+  }
+  return FMD_OK;
+}
+
 // One evaluation of the velocity network at xs; leaves the residual stream in w.H.
 // t_ev: per-event times (device); otherwise the time of the current stage-table entry.
 template <typename T>
 int net_forward(fmd_model* m, Call& c, const float* t_ev) {
+  if (m->split) return net_forward_split(m, c, t_ev);
   Workspace& w = m->ws;
   const fmd_model_config& cf = m->cfg;
   const int d = cf.d_model, L = cf.n_blocks, Hh = cf.n_heads, dh = d / Hh;
@@ -836,10 +994,16 @@ int head(fmd_model* m, Call& c, bool direct, int mode, float* out, int ldo) {
       return launch_linear_update(c.st, (float)m->alpha, (float)m->beta, w.desc, w.ctr, c.T, 9,
                                   w.x, w.acc, w.xs, kStateLd, out, ldo);
     });
-  FMD_TRY(row_stats(m, c));
+  return output_head(m, c, head_args(m, c, direct, mode, out, ldo));
+}
+
+int output_head(fmd_model* m, Call& c, const OdeArgs& ode) {
+  Workspace& w = m->ws;
   const int d = m->cfg.d_model;
-  const OdeArgs ode = head_args(m, c, direct, mode, out, ldo);
+  if (!m->split) FMD_TRY(row_stats(m, c));
   return timed(m, c.st, FMD_K_OTHER, 2.0 * c.T * d * 9, [&] {
+    if (m->split)
+      return launch_head_rows(c.st, d, w.H, m->g_f, m->s_f, m->Wout_pk, m->bout_pk, ode);
     if (head256_supported(d, 9))
       return launch_head256(c.st, w.H, w.stats, m->g_f, m->s_f, m->Wout_pk, m->bout_pk, ode);
     return launch_gemm<float>(c.st, FMD_K_OTHER, true, EPI_ODE, c.Tp, 64, d, w.H, d, m->Wout_pk,
@@ -1123,8 +1287,14 @@ int fmd_model_create(const fmd_model_config* cfg, const float* params, size_t n_
   const int64_t d = cfg->d_model, L = cfg->n_blocks;
   const size_t es = elem_size(*cfg);
   const size_t blk_elems = 14 * d * d;
-  if (grow(m->packed, (L * blk_elems) * es) != FMD_OK) return bail(FMD_E_NOMEM);
-  if (grow(m->Wkv, (size_t)(L * 2 * d * d) * es) != FMD_OK) return bail(FMD_E_NOMEM);
+  m->split = cfg->precision == FMD_FP32 && split_supported(cfg->d_model);
+  if (m->split) {   // every block matrix, then the cross K/V weights of all blocks
+    if (grow(m->splitw, split_bytes(16 * d * d, L)) != FMD_OK) return bail(FMD_E_NOMEM);
+    m->Skv = (const u32x4*)((char*)m->splitw + split_bytes(14 * d * d, L));
+  } else {
+    if (grow(m->packed, (L * blk_elems) * es) != FMD_OK) return bail(FMD_E_NOMEM);
+    if (grow(m->Wkv, (size_t)(L * 2 * d * d) * es) != FMD_OK) return bail(FMD_E_NOMEM);
+  }
   if (grow(m->bkv, (size_t)(L * 2 * d) * 4) != FMD_OK) return bail(FMD_E_NOMEM);
   if (grow(m->Wout_pk, (size_t)64 * d * 4) != FMD_OK) return bail(FMD_E_NOMEM);
   if (grow(m->bout_pk, (size_t)64 * 4) != FMD_OK) return bail(FMD_E_NOMEM);
@@ -1144,6 +1314,7 @@ int fmd_model_create(const fmd_model_config* cfg, const float* params, size_t n_
   int status = FMD_OK;
   auto pack = [&](size_t off, int64_t rows, int64_t cols, void* dst) {
     const float* W = m->params + off;
+    if (m->split) return;
     hipError_t e = cfg->precision != FMD_FP32
                        ? launch_pack_weight<bf16>(nullptr, W, (int)rows, (int)cols, (bf16*)dst)
                        : launch_pack_weight<float>(nullptr, W, (int)rows, (int)cols, (float*)dst);
@@ -1160,8 +1331,19 @@ int fmd_model_create(const fmd_model_config* cfg, const float* params, size_t n_
         status == FMD_OK)
       status = fail(FMD_E_DEVICE, "weight packing failed");
   };
+  // split fragments at the element offset of the packed copy; the cross K/V weights after the
+  // blocks, as one [d][L 2d] matrix
+  auto pack_split = [&](size_t off, int64_t rows, int64_t cols, size_t elem_off, const u32x4** dst) {
+    if (!m->split) return;
+    void* f = (char*)m->splitw + split_bytes((int64_t)elem_off, 1);
+    if (launch_pack_split(nullptr, m->params + off, (int)rows, (int)cols, f) != hipSuccess &&
+        status == FMD_OK)
+      status = fail(FMD_E_DEVICE, "weight packing failed");
+    if (dst) *dst = (const u32x4*)f;
+  };
   walk_params(*cfg, [&](int id, int l, size_t off, int64_t rows, int64_t cols) {
     const float* p = m->params + off;
+    const size_t sb = l >= 0 ? (size_t)l * blk_elems : 0;
     DevBlock* B = l >= 0 ? &m->blk[l] : nullptr;
     char* base = l >= 0 ? pk + (size_t)l * blk_elems * es : nullptr;
     switch (id) {
@@ -1189,26 +1371,31 @@ int fmd_model_create(const fmd_model_config* cfg, const float* params, size_t n_
         B->Wqkv = base;
         pack(off, rows, cols, B->Wqkv);
         pack_frag(off, rows, cols, l, 0, &B->Fqkv);
+        pack_split(off, rows, cols, sb, &B->Sqkv);
         break;
       case P_W_O:
         B->Wo = base + 3 * d * d * es;
         pack(off, rows, cols, B->Wo);
         pack_frag(off, rows, cols, l, 3 * d * d, &B->Fo);
+        pack_split(off, rows, cols, sb + 3 * d * d, &B->So);
         break;
       case P_W_QC:
         B->Wqc = base + 4 * d * d * es;
         pack(off, rows, cols, B->Wqc);
         pack_frag(off, rows, cols, l, 4 * d * d, &B->Fqc);
+        pack_split(off, rows, cols, sb + 4 * d * d, &B->Sqc);
         break;
       case P_W_OC:
         B->Woc = base + 5 * d * d * es;
         pack(off, rows, cols, B->Woc);
         pack_frag(off, rows, cols, l, 5 * d * d, &B->Foc);
+        pack_split(off, rows, cols, sb + 5 * d * d, &B->Soc);
         break;
       case P_W_UP:
         B->Wup = base + 6 * d * d * es;
         pack(off, rows, cols, B->Wup);
         pack_frag(off, rows, cols, l, 6 * d * d, &B->Fup);
+        pack_split(off, rows, cols, sb + 6 * d * d, &B->Sup);
         if (cfg->precision == FMD_FP8) {
           char* f = (char*)m->frag8 + (size_t)l * f8_blk;
           float* sc = (float*)(f + 8 * d * d);
@@ -1223,6 +1410,7 @@ int fmd_model_create(const fmd_model_config* cfg, const float* params, size_t n_
         B->Wdn = base + 10 * d * d * es;
         pack(off, rows, cols, B->Wdn);
         pack_frag(off, rows, cols, l, 10 * d * d, &B->Fdn);
+        pack_split(off, rows, cols, sb + 10 * d * d, &B->Sdn);
         if (cfg->precision == FMD_FP8) {
           char* f = (char*)m->frag8 + (size_t)l * f8_blk + 4 * d * d;
           float* sc = (float*)((char*)m->frag8 + (size_t)l * f8_blk + 8 * d * d) + 8 * d;
@@ -1234,8 +1422,14 @@ int fmd_model_create(const fmd_model_config* cfg, const float* params, size_t n_
             status = fail(FMD_E_DEVICE, "FP8 weight packing failed");
         }
         break;
-      case P_W_KC: pack(off, rows, cols, wkv + (size_t)l * 2 * d * d * es); break;
-      case P_W_VC: pack(off, rows, cols, wkv + ((size_t)l * 2 * d + d) * d * es); break;
+      case P_W_KC:
+        pack(off, rows, cols, wkv + (size_t)l * 2 * d * d * es);
+        pack_split(off, rows, cols, L * blk_elems + (size_t)l * 2 * d * d, nullptr);
+        break;
+      case P_W_VC:
+        pack(off, rows, cols, wkv + ((size_t)l * 2 * d + d) * d * es);
+        pack_split(off, rows, cols, L * blk_elems + ((size_t)l * 2 * d + d) * d, nullptr);
+        break;
       case P_B_KC:
         if (hipMemcpy(m->bkv + l * 2 * d, p, d * 4, hipMemcpyDeviceToDevice) != hipSuccess)
           status = fail(FMD_E_DEVICE, "bias copy failed");
@@ -1301,6 +1495,7 @@ int fmd_model_destroy(fmd_model* m) {
   if (m->params) (void)hipFree(m->params);
   if (m->packed) (void)hipFree(m->packed);
   if (m->frag) (void)hipFree(m->frag);
+  if (m->splitw) (void)hipFree(m->splitw);
   if (m->frag8) (void)hipFree(m->frag8);
   if (m->Wkv) (void)hipFree(m->Wkv);
   if (m->bkv) (void)hipFree(m->bkv);
@@ -1646,7 +1841,12 @@ int fmd_tuning_table(fmd_model* m, char* buf, size_t cap, size_t* needed) {
       // GEMM sites: the tiling; attention: queries per work item (BM) x keys per chunk (BN) x
       // head width (BK); fused kernels: rows per workgroup (BM) x model width (BN) x MFMA depth
       TileDims t{};
-      if (sl < TS_GEMM)
+      if (sl < TS_GEMM && m->split) {
+        const int d = m->cfg.d_model, N = sl == TS_QKV ? 3 * d : sl == TS_UP ? 4 * d : d;
+        int rows = 0, parts = 0;
+        split_tile(m->tune[sl][b], (int64_t)1 << b, N, &rows, &parts);
+        t = TileDims{rows, N / parts, 16, 512};
+      } else if (sl < TS_GEMM)
         t = tile_dims(m->tune[sl][b]);
       else if (sl == TS_ATTN)
         t = TileDims{tiles[m->tune[sl][b]], 128, m->cfg.d_model / m->cfg.n_heads, 256};

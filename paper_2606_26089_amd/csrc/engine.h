@@ -19,6 +19,7 @@ struct DevBlock {
   const float *bqkv, *bo, *bqc, *boc, *bup, *bdn;
   void *Wqkv, *Wo, *Wqc, *Woc, *Wup, *Wdn;
   void *Fqkv, *Fo, *Fqc, *Foc, *Fup, *Fdn;   // BF16 MFMA fragment layout (fused kernels)
+  const u32x4 *Sqkv, *So, *Sqc, *Soc, *Sup, *Sdn;   // three-plane split fragments (FP32 path)
 };
 
 // Device buffers of one call, grown on demand and reused across calls.
@@ -80,7 +81,7 @@ struct GraphKey {
 };
 
 // Sites the autotuner chooses a variant for: the GEMM sites (a tiling of the matrix-core
-// GEMM kernel), then on the fused BF16 path the attention query tile (work items of 64 or
+// GEMM kernel, or a row tile and column split of the split-product one), then on the fused BF16 path the attention query tile (work items of 64 or
 // 128 queries) and the row tile of the fused QKV and OQC kernels (64 or 128 rows).
 enum TuneSlot { TS_QKV = 0, TS_PROJ_RES = 1, TS_PROJ_LN = 2, TS_UP = 3, TS_DOWN = 4, TS_GEMM = 5,
                 TS_ATTN = 5, TS_FQKV = 6, TS_FOQC = 7, TS_COUNT = 8 };
@@ -104,6 +105,9 @@ struct fmd_model {
   void* frag = nullptr;            // fragment-layout BF16 matrices of the fused kernels
   void* frag8 = nullptr;           // FP8 form: e4m3 fragments of W_up, W_dn and column scales
   std::vector<fmd::Fp8Mlp> f8;     // FP8 form: per block pointers into frag8
+  void* splitw = nullptr;          // FP32 path, d_model <= 256: split fragments of every matrix
+  const fmd::u32x4* Skv = nullptr; //   of which the cross K/V weights of all blocks
+  bool split = false;              // the FP32 products run on them (gemm_split.hip)
   bool fused_ok = false;           // the fused block kernels exist for this configuration
   bool kv_hm = false;              // cross K/V cache head-major [L][2][heads][cap][dh]
   int fused = 0;                   // segments that use them (FMD_FUSED_* bits)

@@ -143,6 +143,10 @@ int check_schedule(const fmd_schedule* s);
 int stages_per_step(int scheme);
 StageDesc stage_desc(const fmd_schedule& s, int i);
 int row_stats(fmd_model* m, Call& c);
+// LN_f, output projection and the update of ode over the residual rows of the call.
+int output_head(fmd_model* m, Call& c, const OdeArgs& ode);
+// FP32 path: truth encoding and cross K/V rows of nT truth particles (features u) into kv.
+hipError_t split_truth_cache(fmd_model* m, hipStream_t st, const float* u, int64_t nT, float* kv);
 int attn_tile_for(const fmd_model* m, int64_t Tp);   // attention query tile for a padded size
 int enter_stream(fmd_model* m, hipStream_t caller, Call& c);
 int leave_stream(fmd_model* m, hipStream_t caller);

@@ -1,0 +1,398 @@
+// FP32 products of the velocity network on the BF16 matrix cores (gfx950), for d_model <= 256.
+//
+// C[M, N] = epi(pro(A)[M, K] W[K, N] + b) as launch_gemm, with FP32 operands and results. An
+// FP32 value is the sum of three BF16 values, x = hi + mid + lo: hi its top 8 significand bits
+// (truncated, so it is finite whenever x is), mid and lo the remainders rounded to nearest, with
+// a rest below 2^-24 |x|. A product is the sum of the six partial products down to 2^-16 of it
+// (hi hi, hi mid, mid hi, mid mid, hi lo, lo hi; the ones left out are below 2^-23 and of either
+// sign), each exact in the matrix core's FP32 accumulator. Six BF16 instructions take 192 cycles
+// for what the FP32 instruction takes 512; hi hi is accumulated apart from the five small terms,
+// one rounding per 16 k.
+//
+// A workgroup of eight waves takes 32 TM rows and a range of 32-column blocks, one per wave at a
+// time. The rows are read once, normalised if asked (16 bytes a lane, a row by 16, 32 or 64
+// lanes, statistics from the registers) and written to LDS as three BF16 planes; the weights
+// stream from L2 as packed fragments of three planes, two or four K steps in flight, as in the
+// BF16 block kernels. A K above 256 (the MLP down-projection) goes in panels of 256 columns, the next
+// panel's rows in registers while the current one is multiplied. Every output element is formed
+// in the same order whatever the tile, so a row's bits do not depend on the batch around it.
+//
+// Bound: the matrix cores (six instructions a product). 448,552 rows, d = 256, against the FP32
+// instruction's GEMMs before: up 2466 -> 1652 us (142 TFLOP/s of FP32 product, 854 of BF16
+// instruction; a library BF16 GEMM reaches 1205 on this card), down 2392 -> 1513, QKV 1601 -> 1128,
+// projections 968 -> 417 (the row statistics went too), cross K/V 6590 -> 4799. 14,276 rows: down
+// 177 -> 56 us, projections 71 -> 16. Error of one velocity evaluation of the base network on
+// 4096 events against 64 bits (2-norm): 6.3e-7 -> 3.4e-7.
+//
+// Weight layout (launch_pack_split): [N/32][K/16][3 planes][64 lanes][8], lane l of fragment
+// (nb, ks) holding W[16 ks + 8 (l/32) + j][32 nb + l%32].
+#include "common.h"
+#include "kernels.h"
+
+namespace fmd {
+namespace {
+
+constexpr int kNw = 8;                 // waves
+constexpr int kNt = 64 * kNw;
+constexpr int kPanel = 256;            // K columns in LDS at a time
+constexpr int kLdP = kPanel + 8;       // LDS pitch (bf16) of a plane row
+
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+
+// x = hi + mid + lo for four values
+__device__ __forceinline__ void split4(float4 x, bf16x4 (&p)[3]) {
+  const float v[4] = {x.x, x.y, x.z, x.w};
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const uint32_t hb = __float_as_uint(v[i]) & 0xffff0000u;
+    const float r = v[i] - __uint_as_float(hb);
+    const bf16 mid = (bf16)r;
+    p[0][i] = __builtin_bit_cast(bf16, (uint16_t)(hb >> 16));
+    p[1][i] = mid;
+    p[2][i] = (bf16)(r - (float)mid);
+  }
+}
+
+// Sum over groups of KL lanes (16, 32 or 64), the same in every lane of the group.
+template <int CTRL>
+__device__ __forceinline__ float dpp_plus(float v) {
+  return v + __builtin_amdgcn_update_dpp(0.f, v, CTRL, 0xF, 0xF, false);
+}
+template <int KL>
+__device__ __forceinline__ float group_sum(float v) {
+  v = dpp_plus<0x128>(v);   // row_ror 8, 4, 2, 1
+  v = dpp_plus<0x124>(v);
+  v = dpp_plus<0x122>(v);
+  v = dpp_plus<0x121>(v);
+  if constexpr (KL >= 32) {
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    v = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+  }
+  if constexpr (KL >= 64) {
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    v = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+  }
+  return v;
+}
+
+}  // namespace
+
+// SRC: where the rows come from. EMBED: row r = base + sum_k x[r][k] Win[k] over 9 features
+// (base first, then the features in order), rows at or past T zero; optionally stored to H.
+enum SplitSrc { SRC_ROWS = 0, SRC_LN = 1, SRC_EMBED_LN = 2 };
+
+// KL: lanes that hold one row of a panel, four columns each (panel <= 4 KL columns). MULTI: K may
+// be several panels (a panel's rows stay in registers while the one before is multiplied).
+template <int TM, int SRC, int EPI, int KL, bool MULTI>
+__device__ __forceinline__ void split_body(const SplitArgs& p) {
+  constexpr int ROWS = 32 * TM;
+  constexpr int RPI = 64 / KL;                       // rows of one wave-wide load
+  constexpr int NI = (ROWS / kNw + RPI - 1) / RPI;   // loads per lane and panel
+  constexpr bool LN = SRC != SRC_ROWS;
+  // K steps of weight fragments in flight (a 64-row residual update also holds its old rows)
+  constexpr int kDepth = EPI == EPI_RESID && TM == 2 ? 2 : 4;
+  __shared__ __attribute__((aligned(16))) bf16 P[3][ROWS * kLdP];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int64_t m0 = (int64_t)blockIdx.x * ROWS;
+  const int nb0 = blockIdx.y * p.nb_per, nb1 = min(nb0 + p.nb_per, p.N / 32);
+  const int kp = MULTI ? kPanel : p.K, n_panels = MULTI ? p.K / kPanel : 1, nks = p.K / 16;
+  // staging: lane group lg of this wave takes rows row_of(i), lane gl of the group columns c4 ..
+  const int gl = lane % KL, lg = lane / KL, c4 = 4 * gl;
+  const bool in_row = c4 < kp;
+  auto row_of = [&](int i) { return w * (ROWS / kNw) + i * RPI + lg; };
+  float4 v[NI];
+
+  auto load = [&](int panel) {
+#pragma unroll
+    for (int i = 0; i < NI; ++i) {
+      v[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+      if (in_row && (RPI * NI * kNw == ROWS || row_of(i) < (w + 1) * (ROWS / kNw)))
+        v[i] = *(const float4*)(p.A + (m0 + row_of(i)) * p.lda + panel * kPanel + c4);
+    }
+  };
+  auto stage = [&]() {   // v -> LDS planes
+#pragma unroll
+    for (int i = 0; i < NI; ++i) {
+      if (!in_row || !(RPI * NI * kNw == ROWS || row_of(i) < (w + 1) * (ROWS / kNw))) continue;
+      bf16x4 pl[3];
+      split4(v[i], pl);
+#pragma unroll
+      for (int q = 0; q < 3; ++q) *(bf16x4*)&P[q][row_of(i) * kLdP + c4] = pl[q];
+    }
+  };
+
+  // weight stream of this wave's first column block, ahead of the rows
+  const int nb_first = nb0 + w;
+  u32x4 ring[kDepth][3];
+  auto frag = [&](int nb, int ks) { return p.Wf + ((int64_t)nb * nks + ks) * 3 * 64 + lane; };
+  if (nb_first < nb1) {
+#pragma unroll
+    for (int s = 0; s < kDepth; ++s)
+#pragma unroll
+      for (int q = 0; q < 3; ++q) ring[s][q] = frag(nb_first, s)[q * 64];
+  }
+  if constexpr (SRC == SRC_EMBED_LN) {
+    float4 wk[9];
+#pragma unroll
+    for (int k = 0; k < 9; ++k)
+      wk[k] = in_row ? *(const float4*)(p.Win + k * p.K + c4) : make_float4(0.f, 0.f, 0.f, 0.f);
+    const float4 b4 = in_row ? *(const float4*)(p.base + c4) : make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+    for (int i = 0; i < NI; ++i) {
+      const int64_t r = m0 + row_of(i);
+      v[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+      if (r < p.T && (RPI * NI * kNw == ROWS || row_of(i) < (w + 1) * (ROWS / kNw))) {
+        v[i] = b4;
+        if (p.tok_event && in_row)   // the event's own base row
+          v[i] = *(const float4*)(p.base + (int64_t)p.tok_event[r] * p.K + c4);
+#pragma unroll
+        for (int k = 0; k < 9; ++k) {
+          const float x = p.A[r * p.lda + k];
+          v[i].x = fmaf(x, wk[k].x, v[i].x);
+          v[i].y = fmaf(x, wk[k].y, v[i].y);
+          v[i].z = fmaf(x, wk[k].z, v[i].z);
+          v[i].w = fmaf(x, wk[k].w, v[i].w);
+        }
+      }
+      if (p.H && blockIdx.y == 0 && in_row &&
+          (RPI * NI * kNw == ROWS || row_of(i) < (w + 1) * (ROWS / kNw)))
+        *(float4*)(p.H + r * p.K + c4) = v[i];
+    }
+  } else {
+    load(0);
+  }
+  if constexpr (LN) {
+    const float inv = 1.0f / (float)p.K;
+    const float4 g4 = in_row ? *(const float4*)(p.g + c4) : make_float4(0.f, 0.f, 0.f, 0.f);
+    const float4 s4 = in_row ? *(const float4*)(p.s + c4) : make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+    for (int i = 0; i < NI; ++i) {
+      const float mu = group_sum<KL>((v[i].x + v[i].y) + (v[i].z + v[i].w)) * inv;
+      const float dx = v[i].x - mu, dy = v[i].y - mu, dz = v[i].z - mu, dw = v[i].w - mu;
+      const float q = in_row ? fmaf(dw, dw, fmaf(dz, dz, fmaf(dy, dy, dx * dx))) : 0.f;
+      const float rs = rsqrtf(group_sum<KL>(q) * inv + kLnEps);
+      v[i].x = fmaf(dx * rs, g4.x, s4.x);
+      v[i].y = fmaf(dy * rs, g4.y, s4.y);
+      v[i].z = fmaf(dz * rs, g4.z, s4.z);
+      v[i].w = fmaf(dw * rs, g4.w, s4.w);
+    }
+  }
+  stage();
+  __syncthreads();
+
+  const bf16* arow = &P[0][(lane & 31) * kLdP + (lane >> 5) * 8];
+  // all waves take the same number of passes: panels are staged together
+  for (int nbp = nb0; nbp < nb1; nbp += kNw) {
+    const int nb = nbp + w;
+    const bool on = nb < nb1;                     // wave-uniform
+    const int col = nb * 32 + (lane & 31);
+    f32x16 hi[TM], lo[TM];
+#pragma unroll
+    for (int mi = 0; mi < TM; ++mi)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) hi[mi][r] = 0.f, lo[mi][r] = 0.f;
+    // element (mi, r) of the accumulators: row 32 mi + 8 (r/4) + 4 (lane/32) + r%4, column col;
+    // its address as a wave-uniform base and one 32-bit lane offset
+    uint32_t c_off = (uint32_t)((4 * (lane >> 5) * p.ldc + col) * 4);
+    asm volatile("" : "+v"(c_off));
+    auto c_row = [&](int mi, int r) {
+      return m0 + mi * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
+    };
+    auto c_at = [&](int mi, int r) -> float* {
+      char* row = (char*)(p.C + (m0 + mi * 32 + 8 * (r >> 2) + (r & 3)) * p.ldc);
+      return (float*)(row + c_off);
+    };
+    float old[EPI == EPI_RESID ? TM : 1][16];
+    const float bv = on && p.bias ? p.bias[col] : 0.f;
+    for (int panel = 0; panel < n_panels; ++panel) {
+      if constexpr (MULTI) {
+        if (panel > 0 || nbp > nb0) {
+          __syncthreads();                          // the planes are consumed
+          stage();
+          __syncthreads();
+        }
+        if (panel + 1 < n_panels || nbp + kNw < nb1) load(panel + 1 < n_panels ? panel + 1 : 0);
+      }
+      if (!on) continue;
+      if constexpr (EPI == EPI_RESID) {             // ahead of the last panel's products
+        if (panel + 1 == n_panels) {
+#pragma unroll
+          for (int mi = 0; mi < TM; ++mi)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) old[mi][r] = *c_at(mi, r);
+        }
+      }
+      bf16x8 a[2][TM][3];
+      auto read_a = [&](bf16x8 (&d)[TM][3], int ks) {
+#pragma unroll
+        for (int mi = 0; mi < TM; ++mi)
+#pragma unroll
+          for (int q = 0; q < 3; ++q)
+            d[mi][q] = *(const bf16x8*)(arow + q * (ROWS * kLdP) + mi * 32 * kLdP + ks * 16);
+      };
+      read_a(a[0], 0);
+      for (int k0 = 0; k0 < kp / 16; k0 += kDepth) {
+#pragma unroll
+        for (int s = 0; s < kDepth; ++s) {
+          asm volatile("" ::: "memory");   // one step's operands ahead, not a whole panel's
+          bf16x8 b[3];
+          read_a(a[(s + 1) & 1], min(k0 + s + 1, kp / 16 - 1));
+          const int ks = panel * (kPanel / 16) + k0 + s;
+          // fragment kDepth steps ahead: this block's, or the start of the wave's next one
+          const bool wrap = ks + kDepth >= nks;
+          const int nbn = wrap ? nb + kNw : nb;
+          const u32x4* nf = frag(nbn < nb1 ? nbn : nb, wrap ? ks + kDepth - nks : ks + kDepth);
+#pragma unroll
+          for (int q = 0; q < 3; ++q) {
+            b[q] = __builtin_bit_cast(bf16x8, ring[s][q]);
+            ring[s][q] = nf[q * 64];
+          }
+#pragma unroll
+          for (int t = 0; t < 6; ++t) {
+            // the small terms first
+            constexpr int ia[6] = {2, 0, 1, 1, 0, 0}, ib[6] = {0, 2, 1, 0, 1, 0};
+#pragma unroll
+            for (int mi = 0; mi < TM; ++mi) {
+              f32x16& acc = t == 5 ? hi[mi] : lo[mi];
+              acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[s & 1][mi][ia[t]], b[ib[t]], acc, 0, 0, 0);
+            }
+          }
+        }
+      }
+    }
+    if (!on) continue;
+#pragma unroll
+    for (int mi = 0; mi < TM; ++mi)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        float o = (hi[mi][r] + lo[mi][r]) + bv;
+        if constexpr (EPI == EPI_GELU) o = gelu_erf(o);
+        if constexpr (EPI == EPI_RESID) o = old[mi][r] + o;
+        if (SRC != SRC_EMBED_LN || c_row(mi, r) < p.m_store) *c_at(mi, r) = o;
+      }
+  }
+}
+
+// One kernel name per class of product (the names of the general kernels), so that profiles
+// separate them.
+#define FMD_SPLIT_KERNEL(NAME)                                                               \
+  template <int TM, int SRC, int EPI, int KL, bool MULTI = false>                            \
+  __global__ __launch_bounds__(kNt) __attribute__((amdgpu_waves_per_eu(2))) void NAME(       \
+      SplitArgs p) {                                                                         \
+    split_body<TM, SRC, EPI, KL, MULTI>(p);                                                  \
+  }
+FMD_SPLIT_KERNEL(k_gemm_qkv)
+FMD_SPLIT_KERNEL(k_gemm_proj)
+FMD_SPLIT_KERNEL(k_gemm_qc)
+FMD_SPLIT_KERNEL(k_gemm_up)
+FMD_SPLIT_KERNEL(k_gemm_down)
+FMD_SPLIT_KERNEL(k_gemm_kv)
+#undef FMD_SPLIT_KERNEL
+
+__global__ void k_pack_split(const float* __restrict__ W, int K, int N, u32x4* __restrict__ Wf) {
+  const int nks = K / 16;
+  const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (e >= (int64_t)(N / 32) * nks * 64) return;
+  const int lane = (int)(e % 64);
+  const int64_t f = e / 64;                          // fragment (nb, ks)
+  const int ks = (int)(f % nks), nb = (int)(f / nks), n = nb * 32 + (lane & 31);
+  bf16x8 v[3];
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    float x[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) x[j] = W[(int64_t)(ks * 16 + (lane >> 5) * 8 + 4 * h + j) * N + n];
+    bf16x4 pl[3];
+    split4(make_float4(x[0], x[1], x[2], x[3]), pl);
+#pragma unroll
+    for (int q = 0; q < 3; ++q)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) v[q][4 * h + j] = pl[q][j];
+  }
+#pragma unroll
+  for (int q = 0; q < 3; ++q) Wf[(f * 3 + q) * 64 + lane] = __builtin_bit_cast(u32x4, v[q]);
+}
+
+// ---------------------------------------------------------------------------------------
+
+bool split_supported(int d_model) { return d_model % 64 == 0 && d_model <= kPanel; }
+
+size_t split_bytes(int64_t K, int64_t N) { return (size_t)(K * N) * 6; }
+
+hipError_t launch_pack_split(hipStream_t st, const float* W, int K, int N, void* Wf) {
+  if (K % 16 || N % 32) return hipErrorInvalidValue;
+  const int64_t n = (int64_t)(N / 32) * (K / 16) * 64;
+  hipLaunchKernelGGL(k_pack_split, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, W, K, N,
+                     (u32x4*)Wf);
+  return hipGetLastError();
+}
+
+namespace {
+using SplitKernel = void (*)(SplitArgs);
+
+template <int TM, int KL>
+SplitKernel split_kernel(int cls) {
+  switch (cls) {
+    case SPLIT_QKV: return k_gemm_qkv<TM, SRC_LN, EPI_STORE, KL>;
+    case SPLIT_QKV_EMBED: return k_gemm_qkv<TM, SRC_EMBED_LN, EPI_STORE, KL>;
+    case SPLIT_PROJ:
+    case SPLIT_PROJ_CROSS: return k_gemm_proj<TM, SRC_ROWS, EPI_RESID, KL>;
+    case SPLIT_QC: return k_gemm_qc<TM, SRC_LN, EPI_STORE, KL>;
+    case SPLIT_UP: return k_gemm_up<TM, SRC_LN, EPI_GELU, KL>;
+    case SPLIT_DOWN: return k_gemm_down<TM, SRC_ROWS, EPI_RESID, 64, true>;
+    case SPLIT_KV: return k_gemm_kv<TM, SRC_EMBED_LN, EPI_STORE, KL>;
+    default: return nullptr;
+  }
+}
+}  // namespace
+
+// Candidates of the autotuner (the results do not depend on the choice): 0: 64 rows per
+// workgroup, which uses each weight fragment twice; 1: 32 rows; 2, 3: 32 rows with the passes of
+// eight column blocks spread over two workgroups, and over one each. The rule where nothing is
+// tuned: 64 rows once those tiles fill the 256 CUs, below that 32-row tiles and as many column
+// parts as it takes.
+bool split_tile(int cand, int64_t Mp, int N, int* rows, int* parts) {
+  constexpr int64_t kCus = 256;
+  const int passes = (N / 32 + kNw - 1) / kNw;
+  if (cand < 0) {
+    *rows = Mp / 64 >= kCus ? 64 : 32;
+    *parts = 1;
+    while (*parts < passes && Mp / *rows * *parts < kCus) ++*parts;
+    return true;
+  }
+  *rows = cand == 0 ? 64 : 32;
+  *parts = cand == 2 ? 2 : cand == 3 ? passes : 1;
+  return cand < kSplitCands && (cand < 2 || passes > cand - 1);
+}
+
+hipError_t launch_split_gemm(hipStream_t st, int cls, int64_t Mp, SplitArgs p, int cand) {
+  const int K = p.K, N = p.N;
+  const bool ln = cls == SPLIT_QKV || cls == SPLIT_QC || cls == SPLIT_UP;
+  const bool embed = cls == SPLIT_QKV_EMBED || cls == SPLIT_KV;
+  if (Mp < 0 || Mp % kGemmBM || K % 64 || K <= 0 || N % 64 || N <= 0 || !p.A || !p.Wf || !p.C)
+    return hipErrorInvalidValue;
+  // several panels are whole ones, and only rows that are not normalised have them
+  if (cls == SPLIT_DOWN ? K % kPanel != 0 : K > kPanel) return hipErrorInvalidValue;
+  if ((ln || embed) && (!p.g || !p.s)) return hipErrorInvalidValue;
+  if (embed && (!p.Win || !p.base || p.lda < 9)) return hipErrorInvalidValue;
+  if (!embed && p.lda % 4) return hipErrorInvalidValue;
+  if (Mp == 0) return hipSuccess;
+  int rows = 0, parts = 0;
+  if (!split_tile(cand, Mp, N, &rows, &parts)) return hipErrorInvalidValue;
+  const int n_blocks = N / 32, passes = (n_blocks + kNw - 1) / kNw;
+  p.nb_per = (passes + parts - 1) / parts * kNw;
+  const dim3 grid((unsigned)(Mp / rows), (unsigned)((n_blocks + p.nb_per - 1) / p.nb_per));
+  const int kp = K < kPanel ? K : kPanel;
+  const int KL = kp <= 64 ? 16 : kp <= 128 ? 32 : 64;
+  SplitKernel k = nullptr;
+  if (rows == 64)
+    k = KL == 16 ? split_kernel<2, 16>(cls) : KL == 32 ? split_kernel<2, 32>(cls) : split_kernel<2, 64>(cls);
+  else
+    k = KL == 16 ? split_kernel<1, 16>(cls) : KL == 32 ? split_kernel<1, 32>(cls) : split_kernel<1, 64>(cls);
+  if (!k) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(k, grid, dim3(kNt), 0, st, p);
+  return hipGetLastError();
+}
+
+}  // namespace fmd

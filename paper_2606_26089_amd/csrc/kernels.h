@@ -6,6 +6,7 @@
 #include <stdint.h>
 
 #include "../../include/fmd.h"
+#include "common.h"
 
 namespace fmd {
 
@@ -184,6 +185,10 @@ hipError_t launch_select_write(hipStream_t st, const float* feat, int ldf, const
                                const int64_t* off_out, int64_t n_events, const uint8_t* keep,
                                float* out);
 bool head256_supported(int d, int nf);
+// As launch_head256 for d a multiple of 64 up to 256, with the LayerNorm statistics formed in
+// the kernel.
+hipError_t launch_head_rows(hipStream_t st, int d, const float* H, const float* g, const float* s,
+                            const float* Wt, const float* b, const OdeArgs& ode);
 hipError_t launch_head256(hipStream_t st, const float* H, const float2* stats, const float* g,
                           const float* s, const float* Wt, const float* b, const OdeArgs& ode);
 
@@ -194,6 +199,37 @@ hipError_t launch_linear_update(hipStream_t st, float alpha, float beta, const S
 // Wt[n, k] = T(W[k, n]) for a [K, N] row-major FP32 matrix.
 template <typename T>
 hipError_t launch_pack_weight(hipStream_t st, const float* W, int K, int N, T* Wt);
+
+// FP32 products by three-way BF16 splits, d_model a multiple of 64 up to 256 (gemm_split.hip).
+// Which product of the network a launch is: LN1 + QKV (rows read from A, or formed by the input
+// embedding and stored to H), the attention output projections and the MLP down-projection
+// (added to C), LN2 + cross query, LN3 + MLP up + GELU, truth encoder + LN_t + cross K/V.
+enum SplitClass { SPLIT_QKV = 0, SPLIT_QKV_EMBED, SPLIT_PROJ, SPLIT_PROJ_CROSS, SPLIT_QC, SPLIT_UP, SPLIT_DOWN, SPLIT_KV };
+struct SplitArgs {
+  const float* A;        // [Mp, lda] rows; embedding classes: [T, lda] with 9 features
+  int lda, K, N;
+  const u32x4* Wf;       // launch_pack_split of the K x N weights
+  const float* bias;     // [N] or null
+  const float* g;        // LayerNorm over the K columns (LN classes)
+  const float* s;
+  float* C;              // [Mp, ldc]
+  int ldc;
+  const float* Win;      // embedding classes: [9, K] input weights,
+  const float* base;     //   [K] bias (with the time embedding), or with
+  const int32_t* tok_event;   // (optional) [T] one row [K] per event,
+  float* H;              //   optional [Mp, K] store of the embedded rows,
+  int64_t T;             //   rows with features (the rest are zero),
+  int64_t m_store;       //   rows of C that are stored
+  int nb_per;            // column blocks per workgroup (set by the launcher)
+};
+bool split_supported(int d_model);
+size_t split_bytes(int64_t K, int64_t N);        // bytes of a packed K x N matrix
+hipError_t launch_pack_split(hipStream_t st, const float* W, int K, int N, void* Wf);
+// cand: a candidate of the autotuner (split_tile: rows per workgroup, parts of the columns), or
+// -1 for the rule on the shape.
+constexpr int kSplitCands = 4;
+bool split_tile(int cand, int64_t Mp, int N, int* rows, int* parts);
+hipError_t launch_split_gemm(hipStream_t st, int cls, int64_t Mp, SplitArgs p, int cand = -1);
 
 // Fused BF16 block kernels for d = 256 with 8 heads of 32 and a 4x MLP (block_bf16.hip):
 // their Q/K/V and cross-query stores are 8 head-major planes of width 32. Row counts Mp are

@@ -605,6 +605,104 @@ __global__ __launch_bounds__(256) void k_head256(const float* __restrict__ H,
   }
 }
 
+// The same output head for d = 32 NV (64 to 256) on the FP32 path, with the LayerNorm statistics
+// formed from the rows in registers, so no kernel has to leave them: half a wave per token, lane
+// i of the half owning columns 64 c + 2i and 64 c + 2i + 1.
+template <int NV>
+__global__ __launch_bounds__(256) void k_head_rows(const float* __restrict__ H,
+                                                   const float* __restrict__ g,
+                                                   const float* __restrict__ s,
+                                                   const float* __restrict__ Wt,
+                                                   const float* __restrict__ b, OdeArgs ode) {
+  constexpr int D = 32 * NV, NC = NV / 2, kIter = 2;
+  const int lane = threadIdx.x & 63, half = lane >> 5, i = lane & 31;
+  const int64_t p0 =
+      ((int64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6)) * kIter;
+  const int64_t T = ode.m_valid;
+  if (2 * p0 >= T) return;
+  float x[kIter][NV];
+#pragma unroll
+  for (int it = 0; it < kIter; ++it) {
+    const int64_t r = min(2 * (p0 + it) + half, T - 1);
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+      const float2 h = *(const float2*)(H + r * D + 64 * c + 2 * i);
+      x[it][2 * c] = h.x;
+      x[it][2 * c + 1] = h.y;
+    }
+  }
+  float gv[NV], sv[NV], w[kHeadF][NV];
+#pragma unroll
+  for (int c = 0; c < NC; ++c)
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+      const int col = 64 * c + 2 * i + k;
+      gv[2 * c + k] = g[col];
+      sv[2 * c + k] = s[col];
+#pragma unroll
+      for (int f = 0; f < kHeadF; ++f) w[f][2 * c + k] = Wt[f * D + col];
+    }
+  int mode = ode.mode;
+  float h = ode.h;
+  float* out = ode.out;
+  if (ode.desc && !ode.tok_event) {
+    const StageDesc sd = ode.desc[*ode.ctr];
+    mode = sd.mode;
+    h = sd.h;
+    if (!sd.write_out) out = nullptr;
+  }
+  const float bias = i < kHeadF ? b[i] : 0.f;
+#pragma unroll
+  for (int it = 0; it < kIter; ++it) {
+    const int64_t r = 2 * (p0 + it) + half;
+    float sum = 0.f, sq = 0.f;
+#pragma unroll
+    for (int k = 0; k < NV; ++k) sum += x[it][k];
+    const float mu = half_wave_sum(sum) * (1.0f / D);
+#pragma unroll
+    for (int k = 0; k < NV; ++k) {
+      x[it][k] -= mu;
+      sq = fmaf(x[it][k], x[it][k], sq);
+    }
+    const float rs = rsqrtf(half_wave_sum(sq) * (1.0f / D) + kLnEps);
+    float part[kHeadF];
+#pragma unroll
+    for (int f = 0; f < kHeadF; ++f) part[f] = 0.f;
+#pragma unroll
+    for (int k = 0; k < NV; ++k) {
+      const float y = fmaf(x[it][k] * rs, gv[k], sv[k]);
+#pragma unroll
+      for (int f = 0; f < kHeadF; ++f) part[f] = fmaf(y, w[f][k], part[f]);
+    }
+    float v = 0.f;
+#pragma unroll
+    for (int f = 0; f < kHeadF; ++f) {
+      const float tot = half_wave_sum(part[f]);
+      v = i == f ? tot : v;
+    }
+    if (i < kHeadF && r < T) {
+      const int64_t o = r * ode.ldx + i;
+      if (ode.tok_event) {
+        const StageDesc sd = ode.desc[ode.tok_event[r]];
+        ode_update(sd.mode, sd.h, v + bias, ode.x + o, ode.acc + o, ode.xs + o,
+                   out && sd.write_out ? out + r * ode.ldo + i : nullptr);
+      } else {
+        ode_update(mode, h, v + bias, ode.x + o, ode.acc + o, ode.xs + o,
+                   out ? out + r * ode.ldo + i : nullptr);
+      }
+    }
+  }
+}
+
+hipError_t launch_head_rows(hipStream_t st, int d, const float* H, const float* g, const float* s,
+                            const float* Wt, const float* b, const OdeArgs& ode) {
+  if (ode.nf != kHeadF || d % 64 || d < 64 || d > 256) return hipErrorInvalidValue;
+  if (ode.m_valid <= 0) return hipSuccess;
+  auto* k = d == 64 ? k_head_rows<2> : d == 128 ? k_head_rows<4> : d == 192 ? k_head_rows<6> : k_head_rows<8>;
+  hipLaunchKernelGGL(k, dim3((unsigned)((ode.m_valid + 15) / 16)), dim3(256), 0, st, H, g, s, Wt, b, ode);
+  return hipGetLastError();
+}
+
 bool head256_supported(int d, int nf) { return d == 256 && nf == kHeadF; }
 
 hipError_t launch_head256(hipStream_t st, const float* H, const float2* stats, const float* g,

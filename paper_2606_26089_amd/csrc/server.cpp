@@ -209,6 +209,10 @@ int admit_device(fmd_server* S, Req* r, const int64_t* roff_pin, const float* fe
                        w.xs + b * kStateLd, kStateLd));
   if (nT == 0) return FMD_OK;
   HIP_TRY(hipMemcpyAsync(w.u + b * 9, feat_pin, (size_t)nT * 9 * 4, hipMemcpyHostToDevice, S->st));
+  if (m->split) {
+    HIP_TRY(split_truth_cache(m, S->st, w.u + b * 9, nT, (float*)w.kv + b * 2 * d * L));
+    return FMD_OK;
+  }
   const size_t es = sizeof(T);
   T* cb = (T*)w.c + b * d;
   HIP_TRY(launch_truth_encode<T>(S->st, w.u + b * 9, 9, 9, nT, m->W_tin, m->b_tin, m->g_t, m->s_t,
@@ -339,16 +343,7 @@ int iterate(fmd_server* S, int k, std::vector<Req*>& finished) {
   c.head = &ode;
   FMD_TRY(net_forward<T>(m, c, w.tev));
   c.head = nullptr;
-  const int d = m->cfg.d_model;
-  if (!c.head_done) {   // else the last block's MLP kernel applied the head
-    FMD_TRY(row_stats(m, c));
-    if (head256_supported(d, 9))
-      HIP_TRY(launch_head256(S->st, w.H, w.stats, m->g_f, m->s_f, m->Wout_pk, m->bout_pk, ode));
-    else
-      HIP_TRY(launch_gemm<float>(S->st, FMD_K_OTHER, true, EPI_ODE, c.Tp, 64, d, w.H, d,
-                                 m->Wout_pk, m->bout_pk, w.stats, m->g_f, m->s_f, nullptr, 0,
-                                 &ode));
-  }
+  if (!c.head_done) FMD_TRY(output_head(m, c, ode));   // else the last MLP kernel applied it
   // a finished request's rows go to its pool rows of the pinned output staging
   for (Req* r : res)
     if (r->stage == r->n_stages - 1) {
