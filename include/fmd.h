@@ -66,9 +66,9 @@ enum { FMD_EULER = 0, FMD_RK4 = 1, FMD_MIDPOINT = 2 };
 
 /* Network shape. Supported: d_model = n_heads * dh with dh in {16, 32, 64}; d_model a
  * multiple of 64; mlp_ratio = 4; t_embed_dim = 32; f_truth = f_reco = 9; 1 <= n_max <= 4096.
- * precision FMD_FP32 computes every product to FP32 accuracy: attention (and the GEMMs of
- * d_model above 256) as FP32 MFMA, the GEMMs up to 256 with both operands split into three BF16
- * parts and the six partial products that matter on BF16 MFMA. FMD_BF16 feeds
+ * precision FMD_FP32 computes every product to FP32 accuracy: the GEMMs of d_model up to 256 and
+ * the attention of heads of 32 with both operands split into three BF16 parts and the six partial
+ * products that matter on BF16 MFMA, the others as FP32 MFMA. FMD_BF16 feeds
  * BF16 operands to the MFMA with FP32 accumulation. In both, the residual stream,
  * LayerNorm and softmax statistics, the output head and the ODE state stay FP32. */
 typedef struct {

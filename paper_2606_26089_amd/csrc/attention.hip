@@ -1,6 +1,6 @@
 // Masked multi-head attention over ragged CSR events on gfx950 matrix cores.
 //
-// Each workgroup takes one (event, 64-query tile) work item for one head. Each of its four
+// The general kernel (heads of 16 and 64; heads of 32 have their own below): each workgroup takes one (event, 64-query tile) work item for one head. Each of its four
 // waves owns 16 queries. Keys and values of the event stream through LDS in chunks of 64
 // keys, with an online (running max / running sum) softmax. Keys of other events are
 // never touched. Slots past the end of the event are excluded by a select before the
@@ -477,6 +477,236 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
 }
 
 
+// ---------------------------------------------------------------------------------------
+// FP32 with heads of 32: the split of k_attn32 (one head of one work item per workgroup, 16-query
+// tiles dealt to four waves, XCD bins) with every product on the BF16 matrix cores as in the
+// split GEMMs: Q, K, V and the probabilities as three BF16 parts each, the six partial products
+// down to 2^-16 of the product in FP32 accumulators (96 instructions of 16 cycles for 16 queries
+// and 128 keys, where the FP32 instruction takes 128 of 32). Row sums stay FP32 sums of the
+// unsplit probabilities.
+//  - Chunks of 64 keys (29 KB of LDS, five workgroups per CU), the next chunk's rows in registers
+//    while the current one is computed. K is split as it is staged, 8 dims a thread; V is staged
+//    transposed in the key order of vt_pos, four keys a store.
+//  - Only a chunk that the event ends in is masked; one of at most 32 keys is computed for 32.
+// Bound: staging, products and softmax of a chunk in turn per workgroup, as in k_attn32; 448,552
+// rows: 1050 -> 650 us a launch (2.8 TB/s), 14,276 rows: 46 -> 26 us, against the FP32 matrix
+// instruction with 64-query items.
+namespace {
+constexpr int kKcF = 64;              // keys per chunk
+constexpr int kLdKF = kH32 + 8;       // Ks pitch (bf16)
+constexpr int kLdVF = kKcF + 8;       // Vt pitch (bf16)
+
+// x = hi + mid + lo for eight values (hi truncated, mid and lo rounded to nearest)
+__device__ __forceinline__ void split8(const float (&x)[8], bf16x8 (&p)[3]) {
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    const uint32_t hb = __float_as_uint(x[i]) & 0xffff0000u;
+    const float r = x[i] - __uint_as_float(hb);
+    const bf16 mid = (bf16)r;
+    p[0][i] = __builtin_bit_cast(bf16, (uint16_t)(hb >> 16));
+    p[1][i] = mid;
+    p[2][i] = (bf16)(r - (float)mid);
+  }
+}
+
+// acc += A B over 32 k, the small partial products first
+__device__ __forceinline__ f32x4 mfma_split(const bf16x8 (&a)[3], const bf16x8 (&b)[3], f32x4 acc) {
+  constexpr int ia[6] = {2, 0, 1, 1, 0, 0}, ib[6] = {0, 2, 1, 0, 1, 0};
+#pragma unroll
+  for (int t = 0; t < 6; ++t)
+    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[ia[t]], b[ib[t]], acc, 0, 0, 0);
+  return acc;
+}
+
+struct AttnLdsF {
+  bf16 Ks[3][kKcF * kLdKF];
+  bf16 Vt[3][kH32 * kLdVF];
+};
+}  // namespace
+
+// One staged chunk of KB key blocks of 16, `rest` of its keys in the event.
+template <int TPW, int KB>
+__device__ __forceinline__ void attn32f_chunk(const AttnLdsF& L, const bf16x8 (&qf)[TPW][3],
+                                              float (&m_run)[TPW], float (&l_run)[TPW],
+                                              f32x4 (&o)[TPW][2], int nq, int rest, int wave, int g,
+                                              int j, float sl2e) {
+  asm volatile("" ::: "memory");   // the forms' LDS reads are not merged above their branches
+#pragma unroll
+  for (int t = 0; t < TPW; ++t) {
+    if ((t * 4 + wave) * 16 >= nq) continue;   // wave-uniform
+    f32x4 s[KB];
+#pragma unroll
+    for (int kb = 0; kb < KB; ++kb) {
+      bf16x8 kf[3];
+#pragma unroll
+      for (int q = 0; q < 3; ++q) kf[q] = *(const bf16x8*)&L.Ks[q][(kb * 16 + j) * kLdKF + 8 * g];
+      s[kb] = mfma_split(kf, qf[t], f32x4{0.f, 0.f, 0.f, 0.f});
+    }
+    if (rest < 16 * KB) {
+#pragma unroll
+      for (int kb = 0; kb < KB; ++kb)
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          if (kb * 16 + 4 * g + r >= rest) s[kb][r] = -INFINITY;
+    }
+    float cmax = -INFINITY;
+#pragma unroll
+    for (int kb = 0; kb < KB; ++kb)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) cmax = fmaxf(cmax, s[kb][r]);
+    {
+      const auto r16 = __builtin_amdgcn_permlane16_swap(__float_as_uint(cmax),
+                                                        __float_as_uint(cmax), false, false);
+      cmax = fmaxf(__uint_as_float(r16[0]), __uint_as_float(r16[1]));
+      const auto r32 = __builtin_amdgcn_permlane32_swap(__float_as_uint(cmax),
+                                                        __float_as_uint(cmax), false, false);
+      cmax = fmaxf(__uint_as_float(r32[0]), __uint_as_float(r32[1]));
+    }
+    const float m_new = fmaxf(m_run[t], cmax);    // finite: the chunk holds a key of the event
+    const float alpha = __builtin_amdgcn_exp2f((m_run[t] - m_new) * sl2e);
+    m_run[t] = m_new;
+    const float mb = -m_new * sl2e;
+    float l = l_run[t] * alpha;
+#pragma unroll
+    for (int kb = 0; kb < KB; ++kb)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        s[kb][r] = __builtin_amdgcn_exp2f(fmaf(s[kb][r], sl2e, mb));
+        l += s[kb][r];
+      }
+    l_run[t] = l;
+#pragma unroll
+    for (int db = 0; db < 2; ++db) o[t][db] *= alpha;
+#pragma unroll
+    for (int c = 0; c < KB / 2; ++c) {
+      float pv[8];
+#pragma unroll
+      for (int r = 0; r < 4; ++r) pv[r] = s[2 * c][r], pv[4 + r] = s[2 * c + 1][r];
+      bf16x8 pf[3];
+      split8(pv, pf);
+#pragma unroll
+      for (int db = 0; db < 2; ++db) {
+        bf16x8 vf[3];
+#pragma unroll
+        for (int q = 0; q < 3; ++q)
+          vf[q] = *(const bf16x8*)&L.Vt[q][(db * 16 + j) * kLdVF + 32 * c + 8 * g];
+        o[t][db] = mfma_split(vf, pf, o[t][db]);
+      }
+    }
+  }
+}
+
+template <int TPW>
+__device__ __forceinline__ void attention32f_body(
+    const float* __restrict__ Q, int ldq, int64_t hsq, const float* __restrict__ Kp,
+    const float* __restrict__ Vp, int ldkv, int64_t hskv, float* __restrict__ O, int ldo,
+    int64_t hso, const AttnItem* __restrict__ work, const AttnBins& bins, int n_heads, float sl2e) {
+  __shared__ __attribute__((aligned(16))) AttnLdsF L;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int g = lane >> 4, j = lane & 15;
+  const int bin = blockIdx.x % kAttnBins, k = blockIdx.x / kAttnBins;
+  const int item = k / n_heads;
+  if (item >= bins.len[bin]) return;     // the bin is shorter than the longest one
+  const AttnItem wk = work[bins.start[bin] + item];
+  const int h = k % n_heads;
+  const int nq = wk.nq, nk = wk.nk;
+  const float* kc = Kp + (int64_t)wk.k0 * ldkv + h * hskv;
+  const float* vc = Vp + (int64_t)wk.k0 * ldkv + h * hskv;
+
+  // staging: thread = (key, 8 dims) of K and (4 consecutive keys, 2 dims) of V; keys past the
+  // event end read its last key (K: masked scores) or are zero (V)
+  const int kkey = tid >> 2, kch = tid & 3, vkg = tid >> 4, vdg = tid & 15;
+  float4 rk[2];
+  float2 rv[4];
+  auto load = [&](int c0) {
+    const int lim = nk - 1 - c0;
+    const float* kr = kc + (int64_t)(c0 + min(kkey, lim)) * ldkv + 8 * kch;
+    rk[0] = *(const float4*)kr;
+    rk[1] = *(const float4*)(kr + 4);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int key = 4 * vkg + r;
+      rv[r] = *(const float2*)(vc + (int64_t)(c0 + min(key, lim)) * ldkv + 2 * vdg);
+      if (key > lim) rv[r] = make_float2(0.f, 0.f);
+    }
+  };
+  auto stage = [&]() {
+    const float kx[8] = {rk[0].x, rk[0].y, rk[0].z, rk[0].w, rk[1].x, rk[1].y, rk[1].z, rk[1].w};
+    const float vx[8] = {rv[0].x, rv[1].x, rv[2].x, rv[3].x, rv[0].y, rv[1].y, rv[2].y, rv[3].y};
+    bf16x8 kp[3], vp[3];
+    split8(kx, kp);
+    split8(vx, vp);
+    const int pos = vt_pos(4 * vkg);
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+      *(bf16x8*)&L.Ks[q][kkey * kLdKF + 8 * kch] = kp[q];
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        bf16x4 w4;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) w4[r] = vp[q][4 * i + r];
+        *(bf16x4*)&L.Vt[q][(2 * vdg + i) * kLdVF + pos] = w4;
+      }
+    }
+  };
+
+  load(0);
+  bf16x8 qf[TPW][3];
+  float m_run[TPW], l_run[TPW];
+  f32x4 o[TPW][2];
+#pragma unroll
+  for (int t = 0; t < TPW; ++t) {
+    const int qi = (t * 4 + wave) * 16 + j;
+    const float* qr = Q + (int64_t)(wk.q0 + min(qi, nq - 1)) * ldq + h * hsq + 8 * g;
+    const float4 a = *(const float4*)qr, b = *(const float4*)(qr + 4);
+    const float qx[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
+    split8(qx, qf[t]);
+    m_run[t] = -INFINITY;
+    l_run[t] = 0.f;
+#pragma unroll
+    for (int db = 0; db < 2; ++db) o[t][db] = f32x4{0.f, 0.f, 0.f, 0.f};
+  }
+  for (int c0 = 0; c0 < nk; c0 += kKcF) {
+    if (c0) __syncthreads();             // the chunk before is consumed
+    stage();
+    if (c0 + kKcF < nk) load(c0 + kKcF);
+    __syncthreads();
+    const int rest = nk - c0;
+    if (rest > 32)
+      attn32f_chunk<TPW, 4>(L, qf, m_run, l_run, o, nq, rest, wave, g, j, sl2e);
+    else
+      attn32f_chunk<TPW, 2>(L, qf, m_run, l_run, o, nq, rest, wave, g, j, sl2e);
+  }
+#pragma unroll
+  for (int t = 0; t < TPW; ++t) {
+    const int qi = (t * 4 + wave) * 16 + j;
+    if ((t * 4 + wave) * 16 >= nq) continue;
+    float l = l_run[t] + __shfl_xor(l_run[t], 16, kWave);
+    l += __shfl_xor(l, 32, kWave);
+    const float inv = 1.0f / l;
+    if (qi < nq) {
+      float* orow = O + (int64_t)(wk.q0 + qi) * ldo + h * hso + 4 * g;
+#pragma unroll
+      for (int db = 0; db < 2; ++db)
+        *(float4*)(orow + db * 16) = make_float4(o[t][db][0] * inv, o[t][db][1] * inv,
+                                                 o[t][db][2] * inv, o[t][db][3] * inv);
+    }
+  }
+}
+
+#define FMD_ATTN32F_KERNEL(NAME)                                                               \
+  template <int TPW>                                                                           \
+  __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void NAME(         \
+      const float* __restrict__ Q, int ldq, int64_t hsq, const float* __restrict__ K,          \
+      const float* __restrict__ V, int ldkv, int64_t hskv, float* __restrict__ O, int ldo,     \
+      int64_t hso, const AttnItem* __restrict__ work, AttnBins bins, int n_heads, float sl2e) { \
+    attention32f_body<TPW>(Q, ldq, hsq, K, V, ldkv, hskv, O, ldo, hso, work, bins, n_heads,    \
+                           sl2e);                                                              \
+  }
+FMD_ATTN32F_KERNEL(k_attn_self)
+FMD_ATTN32F_KERNEL(k_attn_cross)
+#undef FMD_ATTN32F_KERNEL
+
 template <typename T, int DH>
 static hipError_t go_attn(bool cross, dim3 grid, hipStream_t st, const T* Q, int ldq,
                           const T* K, const T* V, int ldkv, T* O, int ldo,
@@ -554,9 +784,12 @@ int64_t build_attention_work_kv(const int64_t* q_off, const int64_t* kv_start,
       items, bins);
 }
 
-int attention_query_tile(bool bf16, int dh, int n_heads) {
-  (void)n_heads;
-  return bf16 && dh == kH32 ? 128 : QT;
+int attention_query_tile(bool bf16, int dh, int64_t rows) {
+  if (dh != kH32) return QT;
+  // FP32: 128 queries share each staged (and split) chunk; below about 64 row tiles per XCD the
+  // work is too thin for that and 64 spread it wider (632 rows: 11.7 us a launch with 64, 15.6
+  // with 128; 14,276 rows: 30.2 and 30.5; 58,499 rows: 99 and 90; three tiles a wave spill)
+  return bf16 || rows > 16384 ? 128 : 64;
 }
 
 int attention_query_tiles(bool bf16, int dh, int* tiles) {
@@ -578,34 +811,25 @@ hipError_t launch_attention(hipStream_t st, bool cross, int dh, int n_heads, int
   if (n_items <= 0) return hipSuccess;
   if (n_items > 0x7fffffff) return hipErrorInvalidValue;
   const float sl2e = 1.4426950408889634f / sqrtf((float)dh);
-  if constexpr (std::is_same<T, bf16>::value) {
-    if (dh == kH32) {
-      // 16-byte row chunks: row pitches and head offsets are multiples of 8 elements
-      if (ldq % 8 || ldkv % 8 || ldo % 4 || hsq % 8 || hskv % 8 || hso % 4 || hsq < dh ||
-          hskv < dh || hso < dh)
-        return hipErrorInvalidValue;
-      const int64_t blocks = (int64_t)kAttnBins * bins.max_len * n_heads;
-      if (blocks > 0x7fffffff) return hipErrorInvalidValue;
-      if (blocks == 0) return hipSuccess;
-#define FMD_ATTN32_GO(TPW)                                                                     \
-  do {                                                                                          \
-    if (cross)                                                                                  \
-      hipLaunchKernelGGL((k_attn32_cross<TPW>), dim3((unsigned)blocks), dim3(256), 0, st, Q,     \
-                         ldq, hsq, K, V, ldkv, hskv, O, ldo, hso, work, bins, n_heads, sl2e);   \
-    else                                                                                        \
-      hipLaunchKernelGGL((k_attn32_self<TPW>), dim3((unsigned)blocks), dim3(256), 0, st, Q,      \
-                         ldq, hsq, K, V, ldkv, hskv, O, ldo, hso, work, bins, n_heads, sl2e);   \
-  } while (0)
-      if (qt == 64)
-        FMD_ATTN32_GO(1);
-      else if (qt == 128)
-        FMD_ATTN32_GO(2);
-      else if (qt == 192)
-        FMD_ATTN32_GO(3);
-      else
-        return hipErrorInvalidValue;
-#undef FMD_ATTN32_GO
+  if (dh == kH32) {
+    // 16-byte row chunks: row pitches and head offsets are multiples of 8 elements
+    if (ldq % 8 || ldkv % 8 || ldo % 4 || hsq % 8 || hskv % 8 || hso % 4 || hsq < dh ||
+        hskv < dh || hso < dh || (qt != 64 && qt != 128 && (qt != 192 || sizeof(T) == 4)))
+      return hipErrorInvalidValue;
+    const int64_t blocks = (int64_t)kAttnBins * bins.max_len * n_heads;
+    if (blocks > 0x7fffffff) return hipErrorInvalidValue;
+    if (blocks == 0) return hipSuccess;
+    auto go = [&](auto* k) {
+      hipLaunchKernelGGL(k, dim3((unsigned)blocks), dim3(256), 0, st, Q, ldq, hsq, K, V, ldkv,
+                         hskv, O, ldo, hso, work, bins, n_heads, sl2e);
       return hipGetLastError();
+    };
+    if constexpr (std::is_same<T, bf16>::value) {
+      if (cross) return go(qt == 64 ? k_attn32_cross<1> : qt == 128 ? k_attn32_cross<2> : k_attn32_cross<3>);
+      return go(qt == 64 ? k_attn32_self<1> : qt == 128 ? k_attn32_self<2> : k_attn32_self<3>);
+    } else {
+      if (cross) return go(qt == 64 ? k_attn_cross<1> : k_attn_cross<2>);
+      return go(qt == 64 ? k_attn_self<1> : k_attn_self<2>);
     }
   }
   // the general kernel takes row-major operands only, in work items of QT queries
@@ -613,7 +837,6 @@ hipError_t launch_attention(hipStream_t st, bool cross, int dh, int n_heads, int
   const dim3 grid((unsigned)n_items, n_heads);
   switch (dh) {
     case 16: return go_attn<T, 16>(cross, grid, st, Q, ldq, K, V, ldkv, O, ldo, work, sl2e);
-    case 32: return go_attn<T, 32>(cross, grid, st, Q, ldq, K, V, ldkv, O, ldo, work, sl2e);
     case 64: return go_attn<T, 64>(cross, grid, st, Q, ldq, K, V, ldkv, O, ldo, work, sl2e);
     default: return hipErrorInvalidValue;
   }

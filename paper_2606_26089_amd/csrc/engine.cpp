@@ -481,7 +481,7 @@ int attn_tile_for(const fmd_model* m, int64_t Tp) {
   const int t = m->tune[TS_ATTN][bucket_of(Tp)];
   if (t >= 0 && t < n) return tiles[t];
   return attention_query_tile(m->cfg.precision != FMD_FP32,
-                              m->cfg.d_model / std::max(m->cfg.n_heads, 1), m->cfg.n_heads);
+                              m->cfg.d_model / std::max(m->cfg.n_heads, 1), Tp);
 }
 // Row tile of the fused QKV / OQC kernels (candidate 0: 64 rows, 1: 128 rows); 64 when the
 // call runs a map of 64-row tiles.
@@ -1948,7 +1948,7 @@ int fmd_debug_attention(int32_t precision, int64_t n_events, const int64_t* q_of
   if (dh != 16 && dh != 32 && dh != 64) return fail(FMD_E_UNSUPPORTED, "dh must be 16, 32 or 64");
   if (n_heads < 1 || n_events < 0 || !q_offsets || !kv_offsets) return fail(FMD_E_INVALID, "bad arguments");
   if (q_offsets[0] != 0 || kv_offsets[0] != 0) return fail(FMD_E_INVALID, "offsets must start at 0");
-  const int qt = attention_query_tile(precision == FMD_BF16, dh, n_heads);   // the default tile
+  const int qt = attention_query_tile(precision == FMD_BF16, dh, q_offsets[n_events]);   // the default tile
   std::vector<int64_t> ids((size_t)n_events);
   int64_t n_items = 0;
   for (int64_t e = 0; e < n_events; ++e) {

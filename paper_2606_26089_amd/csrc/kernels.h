@@ -81,11 +81,11 @@ int default_tile_rows(int N);   // a full-row tiling for N, or -1
 hipError_t launch_row_stats(hipStream_t st, const float* A, int ld, int K, int64_t M,
                             float2* stats);
 
-// Queries per attention work item (event, query tile) for a precision and head shape, by
-// default; BF16 with heads of 32 also accepts the tiles of attention_query_tiles (64, 128, 192),
+// Queries per attention work item (event, query tile) for a precision, head width and number of
+// rows, by default; BF16 with heads of 32 also accepts the tiles of attention_query_tiles (64, 128, 192),
 // among which the autotuner chooses. The work lists passed to launch_attention are built
 // with the tile it is given.
-int attention_query_tile(bool bf16, int dh, int n_heads);
+int attention_query_tile(bool bf16, int dh, int64_t rows);
 int attention_query_tiles(bool bf16, int dh, int* tiles);   // candidates; returns their count
 
 // Attention work list split into kAttnBins bins of whole events with about equal work, each
