@@ -12,17 +12,19 @@
 // A workgroup of eight waves takes 32 TM rows and a range of 32-column blocks, one per wave at a
 // time. The rows are read once, normalised if asked (16 bytes a lane, a row by 16, 32 or 64
 // lanes, statistics from the registers) and written to LDS as three BF16 planes; the weights
-// stream from L2 as packed fragments of three planes, two or four K steps in flight, as in the
-// BF16 block kernels. A K above 256 (the MLP down-projection) goes in panels of 256 columns, the next
+// stream from L2 as packed fragments of three planes, four K steps in flight, as in the BF16
+// block kernels. A K above 256 (the MLP down-projection) goes in panels of 256 columns, the next
 // panel's rows in registers while the current one is multiplied. Every output element is formed
 // in the same order whatever the tile, so a row's bits do not depend on the batch around it.
 //
-// Bound: the matrix cores (six instructions a product). 448,552 rows, d = 256, against the FP32
-// instruction's GEMMs before: up 2466 -> 1652 us (142 TFLOP/s of FP32 product, 854 of BF16
-// instruction; a library BF16 GEMM reaches 1205 on this card), down 2392 -> 1513, QKV 1601 -> 1128,
-// projections 968 -> 417 (the row statistics went too), cross K/V 6590 -> 4799. 14,276 rows: down
-// 177 -> 56 us, projections 71 -> 16. Error of one velocity evaluation of the base network on
-// 4096 events against 64 bits (2-norm): 6.3e-7 -> 3.4e-7.
+// Bound: the matrix cores' sustained rate (six instructions a product; a library BF16 GEMM reaches
+// 1205 TFLOP/s on this card). 448,552 rows, d = 256, against the GEMMs on the FP32 instruction
+// before: up 2466 -> 1464 us (965 TFLOP/s of BF16 instructions), down 2392 -> 1334 (1058), QKV
+// 1601 -> 1133 (936), projections 968 -> 446 (their row statistics went too), cross K/V 6590 ->
+// 4799. 14,276 rows: down 177 -> 50 us, up 98 -> 56, projections 71 -> 21. Vector instructions
+// beside the products cost matrix issue (addresses as 64-bit vectors and a branching erf: up 1684,
+// down 1517 us), hence the uniform addresses and the GELU below. Error of one velocity evaluation
+// of the base network on 4096 events against 64 bits (2-norm): 6.3e-7 -> 3.3e-7.
 //
 // Weight layout (launch_pack_split): [N/32][K/16][3 planes][64 lanes][8], lane l of fragment
 // (nb, ks) holding W[16 ks + 8 (l/32) + j][32 nb + l%32].
@@ -75,6 +77,25 @@ __device__ __forceinline__ float group_sum(float v) {
   return v;
 }
 
+// Exact GELU z Phi(z) to FP32 accuracy without branches (a library erf branches on |x|): with
+// e = 2 Phi(-|z|) = 2^-Q(|z|), GELU = z/2 (z < 0 ? e : 2 - e). Q(a) = a P(a), P of degree 9
+// fitted to -log2(2 Phi(-a)) on [0, 9.5] by Lawson's iteratively reweighted least squares,
+// weighted by e (absolute error of e at most 5.3e-9), increasing up to a = 12, where e = 8e-39.
+// Largest error against 64 bits 9.4e-8 |z| (the erf form with an exact erf: 1.02e-7 |z|). 16
+// vector instructions, one of them the exponential.
+__device__ __forceinline__ float gelu_f32(float z) {
+  constexpr float c[10] = {1.15110445022583f,       0.4592188000679016f,     0.05244622007012367f,
+                           -0.006953386589884758f,  6.749427029717481e-06f,  0.0002739334013313055f,
+                           -7.332905806833878e-05f, 1.0027591997641139e-05f, -7.206676286841684e-07f,
+                           2.1236523650713934e-08f};
+  const float a = fminf(fabsf(z), 12.0f);
+  float q = c[9];
+#pragma unroll
+  for (int k = 8; k >= 0; --k) q = fmaf(q, a, c[k]);
+  const float e = __builtin_amdgcn_exp2f(-(q * a));
+  return (0.5f * z) * (z < 0.f ? e : 2.0f - e);
+}
+
 }  // namespace
 
 // SRC: where the rows come from. EMBED: row r = base + sum_k x[r][k] Win[k] over 9 features
@@ -89,8 +110,7 @@ __device__ __forceinline__ void split_body(const SplitArgs& p) {
   constexpr int RPI = 64 / KL;                       // rows of one wave-wide load
   constexpr int NI = (ROWS / kNw + RPI - 1) / RPI;   // loads per lane and panel
   constexpr bool LN = SRC != SRC_ROWS;
-  // K steps of weight fragments in flight (a 64-row residual update also holds its old rows)
-  constexpr int kDepth = EPI == EPI_RESID && TM == 2 ? 2 : 4;
+  constexpr int kDepth = 4;                          // K steps of weight fragments in flight
   __shared__ __attribute__((aligned(16))) bf16 P[3][ROWS * kLdP];
   const int tid = threadIdx.x, lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -122,15 +142,19 @@ __device__ __forceinline__ void split_body(const SplitArgs& p) {
     }
   };
 
-  // weight stream of this wave's first column block, ahead of the rows
-  const int nb_first = nb0 + w;
+  // weight stream of this wave's first column block, ahead of the rows: a wave-uniform address
+  // (3 KB a K step) and one lane offset, so that the loads cost no vector instructions
+  constexpr int kStep = 3 * 64 * 16;                 // bytes of a K step
+  const char* const wbase = (const char*)p.Wf;
+  const int64_t block_bytes = (int64_t)nks * kStep;
+  const uint32_t l16 = lane * 16;
   u32x4 ring[kDepth][3];
-  auto frag = [&](int nb, int ks) { return p.Wf + ((int64_t)nb * nks + ks) * 3 * 64 + lane; };
-  if (nb_first < nb1) {
+  if (nb0 + w < nb1) {
+    const char* f = wbase + (nb0 + w) * block_bytes;
 #pragma unroll
     for (int s = 0; s < kDepth; ++s)
 #pragma unroll
-      for (int q = 0; q < 3; ++q) ring[s][q] = frag(nb_first, s)[q * 64];
+      for (int q = 0; q < 3; ++q) ring[s][q] = *(const u32x4*)(f + s * kStep + q * 1024 + l16);
   }
   if constexpr (SRC == SRC_EMBED_LN) {
     float4 wk[9];
@@ -181,6 +205,8 @@ __device__ __forceinline__ void split_body(const SplitArgs& p) {
   stage();
   __syncthreads();
 
+  // this lane's A operand rows: planes 0 and 1 from one LDS base, plane 2 from another (the
+  // immediate offsets of LDS reads end at 64 KB)
   const bf16* arow = &P[0][(lane & 31) * kLdP + (lane >> 5) * 8];
   // all waves take the same number of passes: panels are staged together
   for (int nbp = nb0; nbp < nb1; nbp += kNw) {
@@ -215,43 +241,41 @@ __device__ __forceinline__ void split_body(const SplitArgs& p) {
         if (panel + 1 < n_panels || nbp + kNw < nb1) load(panel + 1 < n_panels ? panel + 1 : 0);
       }
       if (!on) continue;
-      if constexpr (EPI == EPI_RESID) {             // ahead of the last panel's products
-        if (panel + 1 == n_panels) {
-#pragma unroll
-          for (int mi = 0; mi < TM; ++mi)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) old[mi][r] = *c_at(mi, r);
-        }
-      }
       bf16x8 a[2][TM][3];
+      const bf16* ap = arow;                   // operands of K step 0 of the group
+      const bf16* ap2 = arow + 2 * ROWS * kLdP;
       auto read_a = [&](bf16x8 (&d)[TM][3], int ks) {
 #pragma unroll
-        for (int mi = 0; mi < TM; ++mi)
+        for (int mi = 0; mi < TM; ++mi) {
 #pragma unroll
-          for (int q = 0; q < 3; ++q)
-            d[mi][q] = *(const bf16x8*)(arow + q * (ROWS * kLdP) + mi * 32 * kLdP + ks * 16);
+          for (int q = 0; q < 2; ++q)
+            d[mi][q] = *(const bf16x8*)(ap + q * (ROWS * kLdP) + mi * 32 * kLdP + ks * 16);
+          d[mi][2] = *(const bf16x8*)(ap2 + mi * 32 * kLdP + ks * 16);
+        }
       };
       read_a(a[0], 0);
-      for (int k0 = 0; k0 < kp / 16; k0 += kDepth) {
+      const int n16 = kp / 16;
+      const char* cur = wbase + nb * block_bytes + panel * (kPanel / 16) * kStep;
+      // the stream goes on with the next panel or, at the end, with the wave's next column block
+      const char* next = panel + 1 < n_panels ? cur + (kPanel / 16) * kStep
+                         : nb + kNw < nb1     ? wbase + (nb + kNw) * block_bytes
+                                              : cur;
+      for (int k0 = 0; k0 < n16; k0 += kDepth) {
+        const char* src = k0 + kDepth < n16 ? cur + (k0 + kDepth) * kStep : next;   // uniform
 #pragma unroll
         for (int s = 0; s < kDepth; ++s) {
           asm volatile("" ::: "memory");   // one step's operands ahead, not a whole panel's
           bf16x8 b[3];
-          read_a(a[(s + 1) & 1], min(k0 + s + 1, kp / 16 - 1));
-          const int ks = panel * (kPanel / 16) + k0 + s;
-          // fragment kDepth steps ahead: this block's, or the start of the wave's next one
-          const bool wrap = ks + kDepth >= nks;
-          const int nbn = wrap ? nb + kNw : nb;
-          const u32x4* nf = frag(nbn < nb1 ? nbn : nb, wrap ? ks + kDepth - nks : ks + kDepth);
+          if (s + 1 < kDepth || k0 + kDepth < n16) read_a(a[(s + 1) & 1], s + 1);
 #pragma unroll
           for (int q = 0; q < 3; ++q) {
             b[q] = __builtin_bit_cast(bf16x8, ring[s][q]);
-            ring[s][q] = nf[q * 64];
+            ring[s][q] = *(const u32x4*)(src + s * kStep + q * 1024 + l16);
           }
+          // the small terms first; hi hi apart
+          constexpr int ia[6] = {2, 0, 1, 1, 0, 0}, ib[6] = {0, 2, 1, 0, 1, 0};
 #pragma unroll
           for (int t = 0; t < 6; ++t) {
-            // the small terms first
-            constexpr int ia[6] = {2, 0, 1, 1, 0, 0}, ib[6] = {0, 2, 1, 0, 1, 0};
 #pragma unroll
             for (int mi = 0; mi < TM; ++mi) {
               f32x16& acc = t == 5 ? hi[mi] : lo[mi];
@@ -259,15 +283,23 @@ __device__ __forceinline__ void split_body(const SplitArgs& p) {
             }
           }
         }
+        ap += kDepth * 16;
+        ap2 += kDepth * 16;
       }
     }
     if (!on) continue;
+    if constexpr (EPI == EPI_RESID) {
+#pragma unroll
+      for (int mi = 0; mi < TM; ++mi)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) old[mi][r] = *c_at(mi, r);
+    }
 #pragma unroll
     for (int mi = 0; mi < TM; ++mi)
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
         float o = (hi[mi][r] + lo[mi][r]) + bv;
-        if constexpr (EPI == EPI_GELU) o = gelu_erf(o);
+        if constexpr (EPI == EPI_GELU) o = gelu_f32(o);
         if constexpr (EPI == EPI_RESID) o = old[mi][r] + o;
         if (SRC != SRC_EMBED_LN || c_row(mi, r) < p.m_store) *c_at(mi, r) = o;
       }
