@@ -309,11 +309,11 @@ const char* fmd_kernel_name(fmd_model* m, int32_t kernel_class);
 
 /* ---- launch mode --------------------------------------------------------------------- */
 
-/* While enabled (the default), the kernels of one ODE stage are captured once per call
- * shape into a HIP graph on the model's private stream. The graph is replayed once per
- * stage: time, step and update mode come from a per-call stage table in device memory. A
- * later call with the same token count, event count, output buffer and workspace reuses
- * the graph without re-capturing it. With timing on, or with graphs disabled, the same
+/* While enabled (the default), the kernels of one ODE stage (of four in schedules of 16 stages
+ * and more) are captured once per call shape into a HIP graph on the model's private stream. The
+ * graph is replayed for the stages: time, step, update mode and output buffer come from per-call
+ * tables in device memory. A later call with the same token count, event count and workspace
+ * reuses the graph without re-capturing it, whatever its output buffer. With timing on, or with graphs disabled, the same
  * kernels are launched one by one. Results are identical either way. */
 int fmd_graphs_enable(fmd_model* m, int32_t enable);
 

@@ -492,7 +492,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(TM == 
     float wv[kEmbF9];
 #pragma unroll
     for (int k = 0; k < kEmbF9; ++k) wv[k] = em.W[k * kD + col];
-    const float t0 = em.temb[col];
+    const float t0 = stage_row(em.temb, em.ctl, kD)[col];
 #pragma unroll
     for (int mi = 0; mi < TM; ++mi)
 #pragma unroll
@@ -814,15 +814,9 @@ __global__ __launch_bounds__(kThreads4) __attribute__((amdgpu_waves_per_eu(2))) 
     }
     __syncthreads();
     const OdeArgs& od = nh.ode;
-    int mode = od.mode;
-    float hs = od.h;
-    float* out = od.out;
-    if (od.desc && !od.tok_event) {
-      const StageDesc sd = od.desc[*od.ctr];
-      mode = sd.mode;
-      hs = sd.h;
-      if (!sd.write_out) out = nullptr;
-    }
+    const OdeStage os = ode_stage(od);
+    float* out = os.out;
+    ode_next_stage(od);
     for (int t = tid; t < ROWS * kF; t += kThreads4) {
       const int row = t / kF, f = t % kF;
       const int64_t r = m0 + row;
@@ -835,7 +829,7 @@ __global__ __launch_bounds__(kThreads4) __attribute__((amdgpu_waves_per_eu(2))) 
         ode_update(sd.mode, sd.h, v, od.x + o, od.acc + o, od.xs + o,
                    out && sd.write_out ? out + r * od.ldo + f : nullptr);
       } else {
-        ode_update(mode, hs, v, od.x + o, od.acc + o, od.xs + o, out ? out + r * od.ldo + f : nullptr);
+        ode_update(os.mode, os.h, v, od.x + o, od.acc + o, od.xs + o, out ? out + r * od.ldo + f : nullptr);
       }
     }
   } else {
@@ -956,13 +950,13 @@ hipError_t launch_fused_qkv(hipStream_t st, int64_t Mp, const float* H, const fl
 }
 
 hipError_t launch_fused_embed_qkv(hipStream_t st, int64_t Mp, const float* xs, int ldx, int f,
-                                  int64_t T, const float* temb, const float* W_xin, float* H,
-                                  const float* g, const float* s, const void* Wf,
+                                  int64_t T, const float* temb, StageCtl* ctl, const float* W_xin,
+                                  float* H, const float* g, const float* s, const void* Wf,
                                   const float* bias, void* qkv, int rows) {
   if ((rows != 64 && rows != 128) || Mp % rows || ldx != kEmbLd || f != kEmbF9 || T > Mp)
     return hipErrorInvalidValue;
   if (Mp == 0) return hipSuccess;
-  const EmbedRows em{xs, T, temb, W_xin, H};
+  const EmbedRows em{xs, T, temb, ctl, W_xin, H};
   const RowMap rm{nullptr, Mp};
   if (rows == 64)
     hipLaunchKernelGGL((k_fused_qkv<2, true>), dim3((unsigned)(Mp / 64)), dim3(kThreads), 0, st,

@@ -114,7 +114,8 @@ constexpr int kKeepLoadsAndMfma = 0x2 | 0x4 | 0x100;
 struct EmbedRows {
   const float* xs;             // state rows, pitch kEmbLd floats, first 9 used
   int64_t T;
-  const float* temb;           // [256] time embedding of the stage, b_xin included
+  const float* temb;           // [stages][256] time embeddings, b_xin included
+  StageCtl* ctl;               // the current stage (null: row 0)
   const float* W;              // W_xin [9][256]
   float* H;                    // [Mp][256] output
 };

@@ -239,7 +239,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
     float wv[kEmbF9];
 #pragma unroll
     for (int k = 0; k < kEmbF9; ++k) wv[k] = em.W[k * kD + col];
-    const float t0 = em.temb[col];
+    const float t0 = stage_row(em.temb, em.ctl, kD)[col];
     fill16(ring, wf, lane);
     __syncthreads();
 #pragma unroll
@@ -526,15 +526,9 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
   } else {
     const OdeArgs& od = nh.ode;
     const int j = tid & 15;
-    int mode = od.mode;
-    float hs = od.h;
-    float* out = od.out;
-    if (od.desc && !od.tok_event) {
-      const StageDesc sd = od.desc[*od.ctr];
-      mode = sd.mode;
-      hs = sd.h;
-      if (!sd.write_out) out = nullptr;
-    }
+    const OdeStage os = ode_stage(od);
+    float* out = os.out;
+    ode_next_stage(od);
 #pragma unroll
     for (int m = 0; m < TM; ++m) {
       const int row = (tid >> 4) + 32 * m;
@@ -567,7 +561,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
           ode_update(sd.mode, sd.h, v, od.x + o, od.acc + o, od.xs + o,
                      out && sd.write_out ? out + r * od.ldo + j : nullptr);
         } else {
-          ode_update(mode, hs, v, od.x + o, od.acc + o, od.xs + o,
+          ode_update(os.mode, os.h, v, od.x + o, od.acc + o, od.xs + o,
                      out ? out + r * od.ldo + j : nullptr);
         }
       }
@@ -597,14 +591,14 @@ hipError_t launch_small_qkv(hipStream_t st, int64_t Mp, int rows, const float* H
 }
 
 hipError_t launch_small_embed_qkv(hipStream_t st, int64_t Mp, int rows, const float* xs, int ldx,
-                                  int f, int64_t T, const float* temb, const float* W_xin, float* H,
-                                  const float* g, const float* s, const void* Wf,
-                                  const float* bias, void* qkv) {
+                                  int f, int64_t T, const float* temb, StageCtl* ctl,
+                                  const float* W_xin, float* H, const float* g, const float* s,
+                                  const void* Wf, const float* bias, void* qkv) {
   unsigned grid = 0;
   if (!small_grid(Mp, rows, nullptr, 0, &grid) || ldx != kEmbLd || f != kEmbF9 || T > Mp)
     return hipErrorInvalidValue;
   if (grid == 0) return hipSuccess;
-  const EmbedRows em{xs, T, temb, W_xin, H};
+  const EmbedRows em{xs, T, temb, ctl, W_xin, H};
   auto* k = rows == 32 ? k_small_qkv<1, true> : k_small_qkv<2, true>;
   hipLaunchKernelGGL(k, dim3(grid), dim3(kThreads), 0, st, nullptr, g, s, (const u32x4*)Wf, bias,
                      (bf16*)qkv, em, RowMap{nullptr, Mp});

@@ -100,7 +100,7 @@ size_t elem_size(const fmd_model_config& c) { return c.precision == FMD_FP32 ? 4
 
 void free_ws(Workspace& w) {
   void* dev[] = {w.x, w.acc, w.xs, w.H, w.qkv, w.att, w.qc, w.hid, w.c, w.kv, w.u, w.io,
-                 w.temb, w.tev, w.stats, w.tok_event, w.off, w.work, w.desc, w.ctr};
+                 w.temb, w.tev, w.stats, w.tok_event, w.off, w.work, w.desc, w.tstage, w.ctl};
   for (void* p : dev)
     if (p) (void)hipFree(p);
   for (auto& h : w.hs) {
@@ -142,7 +142,7 @@ int ensure_ws_alloc(fmd_model* m, int64_t T, int64_t E, int64_t items, bool* gre
     FMD_TRY(grow(w.u, (size_t)cap * 9 * 4));
     FMD_TRY(grow(w.io, (size_t)cap * 9 * 4));
     FMD_TRY(grow(w.tok_event, (size_t)cap * 4));
-    if (!w.ctr) FMD_TRY(grow(w.ctr, 64));
+    if (!w.ctl) FMD_TRY(grow(w.ctl, sizeof(StageCtl)));
     if (m->kind == 0) {
       FMD_TRY(grow(w.H, (size_t)cap * d * 4));
       FMD_TRY(grow(w.stats, (size_t)cap * sizeof(float2)));
@@ -588,8 +588,8 @@ int autotune_fused(fmd_model* m, Call& c, int b) {
           return launch_fused_oqc(c.st, c.Tp, w.att, B.Fo, B.bo, w.H, B.g2, B.s2, B.Fqc, B.bqc,
                                   w.qc, rows);
         if (m->fused & FMD_FUSED_EMBED)
-          return launch_fused_embed_qkv(c.st, c.Tp, w.xs, kStateLd, 9, c.T, w.temb, m->W_xin, w.H,
-                                        B.g1, B.s1, B.Fqkv, B.bqkv, w.qkv, rows);
+          return launch_fused_embed_qkv(c.st, c.Tp, w.xs, kStateLd, 9, c.T, w.temb, nullptr,
+                                        m->W_xin, w.H, B.g1, B.s1, B.Fqkv, B.bqkv, w.qkv, rows);
         return launch_fused_qkv(c.st, c.Tp, w.H, B.g1, B.s1, B.Fqkv, B.bqkv, w.qkv, rows);
       });
       if (us < 0.f) {
@@ -637,8 +637,9 @@ SplitArgs split_args(fmd_model* m, const Call& c, int cls, const DevBlock& B, co
       p.A = w.xs;
       p.lda = kStateLd;
       p.Win = m->W_xin;
-      p.base = w.temb;
+      p.base = t_ev ? w.temb : w.tstage;
       p.tok_event = t_ev ? w.tok_event : nullptr;
+      p.ctl = t_ev ? nullptr : w.ctl;
       p.H = w.H;
       p.T = c.T;
       p.m_store = c.Tp;
@@ -781,16 +782,22 @@ hipError_t launch_self_attention(fmd_model* m, const Call& c, int qt, int64_t it
                              (T*)w.att, ldo, hso);
 }
 
+// Per-event calls: the time embedding of each event (a stage loop has its rows from the start).
+int event_times(fmd_model* m, Call& c, const float* t_ev) {
+  if (!t_ev) return FMD_OK;
+  return timed(m, c.st, FMD_K_OTHER, 0, [&] {
+    return launch_time_embed(c.st, t_ev, nullptr, (int)c.E, m->W_time, m->b_time, m->b_xin,
+                             m->cfg.t_embed_dim, m->cfg.d_model, m->ws.temb);
+  });
+}
+
 // The network of net_forward on the FP32 path with split products (d_model <= 256).
 int net_forward_split(fmd_model* m, Call& c, const float* t_ev) {
   Workspace& w = m->ws;
   const int d = m->cfg.d_model, L = m->cfg.n_blocks, Hh = m->cfg.n_heads, dh = d / Hh;
   const double Td = (double)c.T;
   float* kv = (float*)w.kv;
-  FMD_TRY(timed(m, c.st, FMD_K_OTHER, 0, [&] {
-    return launch_time_embed(c.st, t_ev, t_ev ? nullptr : w.desc, w.ctr, 0.f, t_ev ? (int)c.E : 1,
-                             m->W_time, m->b_time, m->b_xin, m->cfg.t_embed_dim, d, w.temb);
-  }));
+  FMD_TRY(event_times(m, c, t_ev));
   auto product = [&](int timer, int cls, const DevBlock& B, const void* A) {
     const SplitArgs p = split_args(m, c, cls, B, A, t_ev);
     // operands read once, results written once (a residual update reads and writes its rows)
@@ -841,10 +848,7 @@ int net_forward(fmd_model* m, Call& c, const float* t_ev) {
   char* kv = (char*)w.kv;
   c.sargs = OdeArgs{};
   c.sargs.stats_out = w.stats;
-  FMD_TRY(timed(m, c.st, FMD_K_OTHER, 0, [&] {
-    return launch_time_embed(c.st, t_ev, t_ev ? nullptr : w.desc, w.ctr, 0.f, t_ev ? (int)c.E : 1,
-                             m->W_time, m->b_time, m->b_xin, cf.t_embed_dim, d, w.temb);
-  }));
+  FMD_TRY(event_times(m, c, t_ev));
   // fused BF16 kernels per block segment (bit 1: LN1 + QKV; bit 2: W_o + residual + LN2 +
   // cross query; bit 4: W_oc + residual + LN3 + MLP + residual; bit 8 with bit 1: the input
   // embedding formed in block 0's QKV kernel); the GEMM kernels otherwise
@@ -853,8 +857,9 @@ int net_forward(fmd_model* m, Call& c, const float* t_ev) {
   const bool embed_in_qkv = (fz & FMD_FUSED_QKV) && (fz & FMD_FUSED_EMBED) && !t_ev && !c.tiles;
   if (!embed_in_qkv)
     FMD_TRY(timed(m, c.st, FMD_K_OTHER, 0, [&] {
-      return launch_embed(c.st, w.xs, kStateLd, 9, c.T, t_ev ? w.tok_event : nullptr, w.temb,
-                          m->W_xin, d, w.H, d, w.stats);
+      return launch_embed(c.st, w.xs, kStateLd, 9, c.T, t_ev ? w.tok_event : nullptr,
+                          t_ev ? w.temb : w.tstage, t_ev ? nullptr : w.ctl, m->W_xin, d, w.H, d,
+                          w.stats);
     }));
   const double dd = (double)d;
   const int sr = small_rows(c), sr_qkv = small_rows_for(m, c, TS_FQKV),
@@ -867,10 +872,10 @@ int net_forward(fmd_model* m, Call& c, const float* t_ev) {
         FMD_TRY(timed(m, c.st, FMD_K_GEMM_QKV, 2.0 * Td * dd * 3 * dd + 2.0 * Td * 9 * dd,
                       Td * (dd * 4 + kStateLd * 4) + (Td + dd) * 3 * dd * es, [&] {
           if (sr_qkv)
-            return launch_small_embed_qkv(c.st, c.Tp, sr_qkv, w.xs, kStateLd, 9, c.T, w.temb, m->W_xin,
-                                          w.H, B.g1, B.s1, B.Fqkv, B.bqkv, w.qkv);
-          return launch_fused_embed_qkv(c.st, c.Tp, w.xs, kStateLd, 9, c.T, w.temb, m->W_xin,
-                                        w.H, B.g1, B.s1, B.Fqkv, B.bqkv, w.qkv,
+            return launch_small_embed_qkv(c.st, c.Tp, sr_qkv, w.xs, kStateLd, 9, c.T, w.tstage,
+                                          w.ctl, m->W_xin, w.H, B.g1, B.s1, B.Fqkv, B.bqkv, w.qkv);
+          return launch_fused_embed_qkv(c.st, c.Tp, w.xs, kStateLd, 9, c.T, w.tstage, w.ctl,
+                                        m->W_xin, w.H, B.g1, B.s1, B.Fqkv, B.bqkv, w.qkv,
                                         fused_rows_for(m, c, TS_FQKV));
         }));
       else if (!qkv_ready)
@@ -984,15 +989,15 @@ int net_forward(fmd_model* m, Call& c, const float* t_ev) {
 OdeArgs head_args(fmd_model* m, Call& c, bool direct, int mode, float* out, int ldo) {
   Workspace& w = m->ws;
   return OdeArgs{w.x, w.acc, w.xs, out, c.T, kStateLd, ldo, 9, mode, 0.f,
-                 direct ? nullptr : w.desc, w.ctr, nullptr};
+                 direct ? nullptr : w.desc, direct ? nullptr : w.ctl, nullptr};
 }
 
 int head(fmd_model* m, Call& c, bool direct, int mode, float* out, int ldo) {
   Workspace& w = m->ws;
   if (m->kind == 1)
     return timed(m, c.st, FMD_K_OTHER, 0, [&] {
-      return launch_linear_update(c.st, (float)m->alpha, (float)m->beta, w.desc, w.ctr, c.T, 9,
-                                  w.x, w.acc, w.xs, kStateLd, out, ldo);
+      return launch_linear_update(c.st, (float)m->alpha, (float)m->beta, w.desc, w.ctl, c.T, 9,
+                                  w.x, w.acc, w.xs, kStateLd, ldo);
     });
   return output_head(m, c, head_args(m, c, direct, mode, out, ldo));
 }
@@ -1036,16 +1041,23 @@ StageDesc stage_desc(const fmd_schedule& s, int i) {
   return d;
 }
 
-// Uploads the stage table of a schedule: stage i = (t, h, update mode, write output).
-int upload_stages(fmd_model* m, Call& c, const fmd_schedule* s, int* n_stages) {
+// Starts the stage loop of a schedule: its table (stage i = (t, h, update mode, write output)),
+// the time embedding of every stage, the counters and the output `out`.
+int begin_stages(fmd_model* m, Call& c, const fmd_schedule* s, float* out, int* n_stages) {
   Workspace& w = m->ws;
   Workspace::HostStage& hs = w.hs[w.cur];   // the call's set (made writable by stage_events)
   const int K = s->n_steps, S = stages_per_step(s->scheme);
   const int n = K * S;
+  const int d = m->cfg.d_model;   // 0: the linear field, which has no time embedding
   if (n > w.cap_desc) {
     FMD_TRY(grow(w.desc, (size_t)n * sizeof(StageDesc)));
     HIP_TRY(hipDeviceSynchronize());
     w.cap_desc = n;
+    w.generation++;
+  }
+  if (n > w.cap_tstage && d > 0) {
+    FMD_TRY(grow(w.tstage, (size_t)n * d * 4));
+    w.cap_tstage = n;
     w.generation++;
   }
   if (n > hs.cap_desc) {
@@ -1055,57 +1067,65 @@ int upload_stages(fmd_model* m, Call& c, const fmd_schedule* s, int* n_stages) {
   for (int i = 0; i < n; ++i) hs.desc[i] = stage_desc(*s, i);
   HIP_TRY(hipMemcpyAsync(w.desc, hs.desc, (size_t)n * sizeof(StageDesc), hipMemcpyHostToDevice, c.st));
   FMD_TRY(mark_host_stage(w, c.st));
-  FMD_TRY(timed(m, c.st, FMD_K_OTHER, 0, [&] { return launch_set_counter(c.st, w.ctr, 0); }));
+  FMD_TRY(timed(m, c.st, FMD_K_OTHER, 0, [&] { return launch_stage_begin(c.st, w.ctl, out); }));
+  if (m->kind == 0)
+    FMD_TRY(timed(m, c.st, FMD_K_OTHER, 0, [&] {
+      return launch_time_embed(c.st, nullptr, w.desc, n, m->W_time, m->b_time, m->b_xin,
+                               m->cfg.t_embed_dim, d, w.tstage);
+    }));
   *n_stages = n;
   return FMD_OK;
 }
 
-// One ODE stage: velocity at the current stage input, fused update, counter advance.
+// One ODE stage: velocity at the current stage input, fused update (which moves the counters on).
 template <typename T>
-int run_stage(fmd_model* m, Call& c, float* out, int ldo) {
-  const OdeArgs ode = head_args(m, c, false, 0, out, ldo);
+int run_stage(fmd_model* m, Call& c, int ldo) {
+  const OdeArgs ode = head_args(m, c, false, 0, nullptr, ldo);
   c.head = &ode;
   c.head_done = false;
   const int rc = m->kind == 0 ? net_forward<T>(m, c, nullptr) : FMD_OK;
   c.head = nullptr;
   FMD_TRY(rc);
-  if (!c.head_done) FMD_TRY(head(m, c, false, 0, out, ldo));
-  return timed(m, c.st, FMD_K_OTHER, 0, [&] { return launch_stage_advance(c.st, m->ws.ctr); });
+  return c.head_done ? FMD_OK : head(m, c, false, 0, nullptr, ldo);
 }
 
-// All stages of a call. With graphs on, one stage is captured into a HIP graph (kernels
-// read time, mode and step from the stage table through the device counter) and the graph
-// is replayed once per stage; the executable graph is kept for later calls with the same
-// shapes, buffers and output pointer.
+// All stages of a call. With graphs on, kGraphStages stages are captured into a HIP graph
+// (kernels read time, mode, step and output through the stage table and its device counters) and
+// the graph is replayed for the whole groups, the rest launched one by one; the executable graph
+// is kept for later calls with the same shapes and workspace. The start of a graph costs 8 us on
+// the device (one stage a graph: 375 us per evaluation of one event, 8 of them that gap), a
+// captured kernel about 2 us on the host once, so four stages pay from some 16 stages on.
 template <typename T>
-int run_stages(fmd_model* m, Call& c, int n_stages, float* out, int ldo) {
-  if (!m->graphs || m->timing) {
-    for (int i = 0; i < n_stages; ++i) FMD_TRY(run_stage<T>(m, c, out, ldo));
-    return FMD_OK;
-  }
-  const GraphKey key{c.Tp,   c.T,       c.E,    c.items,  out,      ldo, m->ws.generation,
-                     m->tune_gen, c.bins, c.items_x, c.work_x, c.bins_x, c.Tt};
-  if (!m->gexec || !(key == m->gkey)) {
-    if (m->gexec) (void)hipGraphExecDestroy(m->gexec);
-    m->gexec = nullptr;
-    HIP_TRY(hipStreamBeginCapture(c.st, hipStreamCaptureModeThreadLocal));
-    const int st = run_stage<T>(m, c, out, ldo);
-    hipGraph_t g = nullptr;
-    const hipError_t ec = hipStreamEndCapture(c.st, &g);
-    if (st != FMD_OK) {
-      if (g) (void)hipGraphDestroy(g);
-      return st;
-    }
-    if (ec != hipSuccess) return fail(FMD_E_DEVICE, "stage capture failed: %s", hipGetErrorString(ec));
-    const hipError_t ei = hipGraphInstantiate(&m->gexec, g, nullptr, nullptr, 0);
-    (void)hipGraphDestroy(g);
-    if (ei != hipSuccess) {
+int run_stages(fmd_model* m, Call& c, int n_stages, int ldo) {
+  const int per = n_stages >= 16 ? 4 : 1;
+  int done = 0;
+  if (m->graphs && !m->timing) {
+    const GraphKey key{c.Tp,   c.T,       c.E,    c.items,  ldo,      per, m->ws.generation,
+                       m->tune_gen, c.bins, c.items_x, c.work_x, c.bins_x, c.Tt};
+    if (!m->gexec || !(key == m->gkey)) {
+      if (m->gexec) (void)hipGraphExecDestroy(m->gexec);
       m->gexec = nullptr;
-      return fail(FMD_E_DEVICE, "graph instantiation failed: %s", hipGetErrorString(ei));
+      HIP_TRY(hipStreamBeginCapture(c.st, hipStreamCaptureModeThreadLocal));
+      int st = FMD_OK;
+      for (int i = 0; i < per && st == FMD_OK; ++i) st = run_stage<T>(m, c, ldo);
+      hipGraph_t g = nullptr;
+      const hipError_t ec = hipStreamEndCapture(c.st, &g);
+      if (st != FMD_OK) {
+        if (g) (void)hipGraphDestroy(g);
+        return st;
+      }
+      if (ec != hipSuccess) return fail(FMD_E_DEVICE, "stage capture failed: %s", hipGetErrorString(ec));
+      const hipError_t ei = hipGraphInstantiate(&m->gexec, g, nullptr, nullptr, 0);
+      (void)hipGraphDestroy(g);
+      if (ei != hipSuccess) {
+        m->gexec = nullptr;
+        return fail(FMD_E_DEVICE, "graph instantiation failed: %s", hipGetErrorString(ei));
+      }
+      m->gkey = key;
     }
-    m->gkey = key;
+    for (; done + per <= n_stages; done += per) HIP_TRY(hipGraphLaunch(m->gexec, c.st));
   }
-  for (int i = 0; i < n_stages; ++i) HIP_TRY(hipGraphLaunch(m->gexec, c.st));
+  for (; done < n_stages; ++done) FMD_TRY(run_stage<T>(m, c, ldo));
   return FMD_OK;
 }
 
@@ -1135,8 +1155,9 @@ int simulate_body(fmd_model* m, const fmd_events_in* truth, const float* x0, uin
                   const int64_t* reco_off) {
   FMD_TRY(stage_events(m, truth, c, reco_off));
   Workspace& w = m->ws;
+  float* out = reco->on_device ? reco->feat : w.io;
   int n_stages = 0;
-  FMD_TRY(upload_stages(m, c, sched, &n_stages));
+  FMD_TRY(begin_stages(m, c, sched, out, &n_stages));
   if (x0) {
     const float* src = x0;
     if (!truth->on_device) {
@@ -1149,12 +1170,11 @@ int simulate_body(fmd_model* m, const fmd_events_in* truth, const float* x0, uin
       return launch_noise(c.st, seed, w.off, w.tok_event, c.T, 9, w.x, w.xs, kStateLd);
     }));
   }
-  float* out = reco->on_device ? reco->feat : w.io;
   if (m->kind == 0) {
     FMD_TRY(truth_cache<T>(m, c));
     FMD_TRY(autotune<T>(m, c));
   }
-  FMD_TRY(run_stages<T>(m, c, n_stages, out, 9));
+  FMD_TRY(run_stages<T>(m, c, n_stages, 9));
   if (!reco->on_device) {
     HIP_TRY(hipMemcpyAsync(reco->feat, w.io, (size_t)c.T * 9 * 4, hipMemcpyDeviceToHost, c.st));
     HIP_TRY(hipStreamSynchronize(c.st));

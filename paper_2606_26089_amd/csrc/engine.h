@@ -43,7 +43,8 @@ struct Workspace {
   int64_t* off = nullptr;          // [E + 1]
   AttnItem* work = nullptr;        // attention work list
   StageDesc* desc = nullptr;       // [stages] stage table of the call
-  int32_t* ctr = nullptr;          // current stage index (device)
+  float* tstage = nullptr;         // [stages, d] time embeddings of the call's stages
+  StageCtl* ctl = nullptr;         // current stage and output of the call (device)
   // Pinned staging of the host-built arrays a call uploads (offsets, attention work lists,
   // stage table), two sets used by alternate calls. A set's event is recorded after the
   // copies that read it; a call waits on it before rewriting the set, so it only waits for
@@ -57,23 +58,22 @@ struct Workspace {
     bool live = false;             // ev recorded and not yet waited for
   } hs[2];
   int cur = 0;                     // set of the current call
-  int cap_desc = 0;
+  int cap_desc = 0, cap_tstage = 0;
   uint64_t generation = 0;         // bumped whenever a buffer is reallocated
 };
 
 // What a captured stage graph depends on besides buffer contents.
 struct GraphKey {
   int64_t Tp, T, E, items;
-  const float* out;
-  int ldo;
+  int ldo, stages;           // stages captured in one graph
   uint64_t ws_gen, tune_gen;
   AttnBins bins;  // kernel arguments and grid size of the attention launches
   int64_t items_x, work_x;   // cross-attention list: size and offset in the work buffer
   AttnBins bins_x;
   int64_t Tt;                // truth rows (the reco side may differ in size)
   bool operator==(const GraphKey& o) const {
-    return Tp == o.Tp && T == o.T && E == o.E && items == o.items && out == o.out &&
-           ldo == o.ldo && ws_gen == o.ws_gen && tune_gen == o.tune_gen &&
+    return Tp == o.Tp && T == o.T && E == o.E && items == o.items && ldo == o.ldo &&
+           stages == o.stages && ws_gen == o.ws_gen && tune_gen == o.tune_gen &&
            std::memcmp(&bins, &o.bins, sizeof(AttnBins)) == 0 && items_x == o.items_x &&
            work_x == o.work_x && std::memcmp(&bins_x, &o.bins_x, sizeof(AttnBins)) == 0 &&
            Tt == o.Tt;

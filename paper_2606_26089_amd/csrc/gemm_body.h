@@ -285,17 +285,12 @@ __device__ __forceinline__ void gemm_body(const void* __restrict__ A_, int lda,
       }
     }
   } else {
-    int mode = ode.mode;
-    float h = ode.h;
-    float* out = ode.out;
+    OdeStage os{};
     if constexpr (EPI == EPI_ODE) {
-      if (ode.desc && !ode.tok_event) {
-        const StageDesc sd = ode.desc[*ode.ctr];
-        mode = sd.mode;
-        h = sd.h;
-        if (!sd.write_out) out = nullptr;
-      }
+      os = ode_stage(ode);
+      ode_next_stage(ode);
     }
+    float* out = os.out;
 #pragma unroll
     for (int nj = 0; nj < TN; ++nj) {
       const int col = n0 + wn * TL::WTN + nj * 32 + (lane & 31);
@@ -314,7 +309,7 @@ __device__ __forceinline__ void gemm_body(const void* __restrict__ A_, int lda,
                 ode_update(sd.mode, sd.h, v, ode.x + o, ode.acc + o, ode.xs + o,
                            out && sd.write_out ? out + row * ode.ldo + col : nullptr);
               } else {
-                ode_update(mode, h, v, ode.x + o, ode.acc + o, ode.xs + o,
+                ode_update(os.mode, os.h, v, ode.x + o, ode.acc + o, ode.xs + o,
                            out ? out + row * ode.ldo + col : nullptr);
               }
             }

@@ -161,7 +161,8 @@ __device__ __forceinline__ void split_body(const SplitArgs& p) {
 #pragma unroll
     for (int k = 0; k < 9; ++k)
       wk[k] = in_row ? *(const float4*)(p.Win + k * p.K + c4) : make_float4(0.f, 0.f, 0.f, 0.f);
-    const float4 b4 = in_row ? *(const float4*)(p.base + c4) : make_float4(0.f, 0.f, 0.f, 0.f);
+    const float* base = stage_row(p.base, p.ctl, p.K);
+    const float4 b4 = in_row ? *(const float4*)(base + c4) : make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
     for (int i = 0; i < NI; ++i) {
       const int64_t r = m0 + row_of(i);

@@ -30,17 +30,27 @@ enum UpdMode {
 constexpr int kStateLd = 16;       // row stride (floats) of the device ODE state arrays
 
 // One ODE stage of a schedule: evaluation time, step, update mode (UpdMode) and whether
-// this stage writes the caller's output. A call uploads its stages once; a device
-// counter selects the current one, so one captured graph replays every stage.
+// this stage writes the caller's output. A call uploads its stages once; device
+// counters select the current one, so one captured graph replays every stage.
 struct StageDesc {
   float t, h;
   int32_t mode, write_out;
 };
 
+// Device side of the stage loop. The first kernel of a stage (the input embedding) reads `first`
+// and hands it to `last`, the last one (the output head with the state update) reads `last` and
+// sets `first` to the next stage, so no kernel of its own counts. `out` is the caller's output of
+// this call: behind a pointer, so that a captured graph serves any output buffer.
+struct StageCtl {
+  int32_t first, last;
+  float* out;
+};
+
 // Fused ODE update in a GEMM epilogue (EPI_ODE): the GEMM result v[r, c] for c < nf and
 // r < m_valid updates state element (r, c). With desc and tok_event set, mode, h and the
 // output write of row r come from desc[tok_event[r]] (one entry per event: the serving
-// loop); with desc alone from desc[*ctr] (one entry per stage); otherwise from the fields.
+// loop); with desc alone from desc[ctl->last] and ctl->out (one entry per stage); otherwise from
+// the fields.
 struct OdeArgs {
   float* x;
   float* acc;
@@ -50,10 +60,35 @@ struct OdeArgs {
   int ldx, ldo, nf, mode;
   float h;
   const StageDesc* desc;
-  const int32_t* ctr;
+  StageCtl* ctl;
   const int32_t* tok_event;
   float2* stats_out;   // EPI_RESID_LN only
 };
+
+// What this launch applies to rows without an entry of their own, and the step to the next stage
+// (every kernel that applies `ode` calls it once, in any one thread).
+struct OdeStage {
+  int mode;
+  float h;
+  float* out;
+};
+__device__ __forceinline__ OdeStage ode_stage(const OdeArgs& ode) {
+  if (!ode.desc || ode.tok_event) return OdeStage{ode.mode, ode.h, ode.out};
+  const StageDesc sd = ode.desc[ode.ctl->last];
+  return OdeStage{sd.mode, sd.h, sd.write_out ? ode.ctl->out : nullptr};
+}
+__device__ __forceinline__ void ode_next_stage(const OdeArgs& ode) {
+  if (ode.desc && !ode.tok_event && blockIdx.x == 0 && threadIdx.x == 0)
+    ode.ctl->first = ode.ctl->last + 1;
+}
+// The time-embedding row of the current stage (temb [stages][d]; ctl null: row 0). Called once by
+// the first kernel of a stage for the counter, by as many threads as need the row.
+__device__ __forceinline__ const float* stage_row(const float* temb, StageCtl* ctl, int d) {
+  if (!ctl) return temb;
+  const int32_t i = ctl->first;
+  if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) ctl->last = i;
+  return temb + (int64_t)i * d;
+}
 constexpr int kGemmBM = 256;       // largest GEMM row tile; token buffers are padded to this
 
 // C = epi(pro(A) W + b). A: float [Mp, lda] if ln, else T [Mp, lda]. Wt: T [N, K]
@@ -142,25 +177,23 @@ hipError_t launch_truth_encode(hipStream_t st, const float* u, int ldu, int f, i
                                const float* W, const float* b, const float* g,
                                const float* s, int d, T* c, int ldc);
 
-// temb[e, :] = b_xin + b_time + phi(t_e) W_time for e < n; t_e = t_ev[e] if t_ev is set,
-// else desc[*ctr].t if desc is set, else t_uniform.
-hipError_t launch_time_embed(hipStream_t st, const float* t_ev, const StageDesc* desc,
-                             const int32_t* ctr, float t_uniform, int n, const float* W_time,
-                             const float* b_time, const float* b_xin, int E_dim, int d,
-                             float* temb);
+// Time embedding rows temb[i] = phi(t_i) W_time + b_time + b_xin, i < n: t_i = t_ev[i], or
+// desc[i].t (one row per stage of a call).
+hipError_t launch_time_embed(hipStream_t st, const float* t_ev, const StageDesc* desc, int n,
+                             const float* W_time, const float* b_time, const float* b_xin,
+                             int E_dim, int d, float* temb);
 
-// Stage counter control: *ctr = v, and *ctr += 1 (one thread; the last kernel of a stage).
-hipError_t launch_set_counter(hipStream_t st, int32_t* ctr, int32_t v);
-hipError_t launch_stage_advance(hipStream_t st, int32_t* ctr);
+// Start of a stage loop: the counters at stage 0 and the call's output.
+hipError_t launch_stage_begin(hipStream_t st, StageCtl* ctl, float* out);
 
-// H[r, :] = temb[tok_event[r] or 0, :] + xs[r, :f] W_xin, with the LayerNorm
-// statistics of every new row written to stats[r].
+// H[r, :] = temb row + xs[r, :f] W_xin, with the LayerNorm statistics of every new row written
+// to stats[r]. The temb row is tok_event[r] (per event), or the current stage of ctl.
 hipError_t launch_embed(hipStream_t st, const float* xs, int ldx, int f, int64_t T,
-                        const int32_t* tok_event, const float* temb, const float* W_xin,
-                        int d, float* H, int ldh, float2* stats);
+                        const int32_t* tok_event, const float* temb, StageCtl* ctl,
+                        const float* W_xin, int d, float* H, int ldh, float2* stats);
 
 // v = (alpha + beta t) xs, then the same ODE update, with t, h, mode and the output write
-// taken from desc[*ctr].
+// taken from desc[ctl->first], which it advances.
 // Output head for d_model 256 and 9 features: ode-update(LN(H; stats, g, s) Wt^T + b) over
 // the ode.m_valid valid rows, Wt float [>= 9, 256] (row c: weights of output c).
 // One block's BF16 cross K/V rows [rows][2d] into the head-major cache planes (plane rows
@@ -193,8 +226,8 @@ hipError_t launch_head256(hipStream_t st, const float* H, const float2* stats, c
                           const float* s, const float* Wt, const float* b, const OdeArgs& ode);
 
 hipError_t launch_linear_update(hipStream_t st, float alpha, float beta, const StageDesc* desc,
-                                const int32_t* ctr, int64_t T, int f, float* x, float* acc,
-                                float* xs, int ldx, float* out, int ldo);
+                                StageCtl* ctl, int64_t T, int f, float* x, float* acc,
+                                float* xs, int ldx, int ldo);
 
 // Wt[n, k] = T(W[k, n]) for a [K, N] row-major FP32 matrix.
 template <typename T>
@@ -216,7 +249,8 @@ struct SplitArgs {
   int ldc;
   const float* Win;      // embedding classes: [9, K] input weights,
   const float* base;     //   [K] bias (with the time embedding), or with
-  const int32_t* tok_event;   // (optional) [T] one row [K] per event,
+  const int32_t* tok_event;   // (optional) [T] one row [K] per event, or
+  StageCtl* ctl;         //   (optional) one row [K] per stage,
   float* H;              //   optional [Mp, K] store of the embedded rows,
   int64_t T;             //   rows with features (the rest are zero),
   int64_t m_store;       //   rows of C that are stored
@@ -244,12 +278,12 @@ hipError_t launch_fused_qkv(hipStream_t st, int64_t Mp, const float* H, const fl
                             const float* s, const void* Wf, const float* bias, void* qkv,
                             int rows = 64, const int32_t* tiles = nullptr, int64_t n_tiles = 0);
 // As launch_fused_qkv for block 0, with the input embedding formed in the kernel for a
-// stage time shared by every row: H rows [0, T) = temb[0..255] + xs[r][0..8] W_xin (the
+// stage time shared by every row: H rows [0, T) = temb row (of ctl's stage) + xs[r][0..8] W_xin (the
 // order of launch_embed's d = 256 kernel, so H is the same; rows [T, Mp) are zero) are
 // written to H and feed LN1 + QKV. xs has pitch 16 and at least Mp rows; f must be 9.
 hipError_t launch_fused_embed_qkv(hipStream_t st, int64_t Mp, const float* xs, int ldx, int f,
-                                  int64_t T, const float* temb, const float* W_xin, float* H,
-                                  const float* g, const float* s, const void* Wf,
+                                  int64_t T, const float* temb, StageCtl* ctl, const float* W_xin,
+                                  float* H, const float* g, const float* s, const void* Wf,
                                   const float* bias, void* qkv, int rows = 64);
 // H += att Wo + b_o;  qc = LN(H; g, s) Wqc + b_qc, head-major: qc [8 heads][Mp][32]. The
 // attention output att is head-major [8 heads][Mp][32] as well. rows: 64 or 128.
@@ -311,9 +345,9 @@ hipError_t launch_small_qkv(hipStream_t st, int64_t Mp, int rows, const float* H
                             const float* s, const void* Wf, const float* bias, void* qkv,
                             const int32_t* tiles = nullptr, int64_t n_tiles = 0);
 hipError_t launch_small_embed_qkv(hipStream_t st, int64_t Mp, int rows, const float* xs, int ldx,
-                                  int f, int64_t T, const float* temb, const float* W_xin, float* H,
-                                  const float* g, const float* s, const void* Wf,
-                                  const float* bias, void* qkv);
+                                  int f, int64_t T, const float* temb, StageCtl* ctl,
+                                  const float* W_xin, float* H, const float* g, const float* s,
+                                  const void* Wf, const float* bias, void* qkv);
 hipError_t launch_small_oqc(hipStream_t st, int64_t Mp, int rows, const void* att, const void* Wf_o,
                             const float* b_o, float* H, const float* g, const float* s,
                             const void* Wf_qc, const float* b_qc, void* qc,

@@ -196,14 +196,13 @@ template hipError_t launch_truth_encode<bf16>(hipStream_t, const float*, int, in
 // phi = [sin(w_k t) | cos(w_k t)], w_k = 10000^(-k/(E/2)). One block per event.
 __global__ __launch_bounds__(256) void k_time_embed(const float* __restrict__ t_ev,
                                                     const StageDesc* __restrict__ desc,
-                                                    const int32_t* __restrict__ ctr,
-                                                    float t_uniform, const float* __restrict__ W,
+                                                    const float* __restrict__ W,
                                                     const float* __restrict__ b_time,
                                                     const float* __restrict__ b_xin, int E_dim,
                                                     int d, float* __restrict__ temb) {
   __shared__ float phi[64];
   const int e = blockIdx.x;
-  const float t = t_ev ? t_ev[e] : desc ? desc[*ctr].t : t_uniform;
+  const float t = t_ev ? t_ev[e] : desc[e].t;
   const int half = E_dim >> 1;
   if (threadIdx.x < half) {
     // ln(10000) / half scales the exponent
@@ -221,26 +220,20 @@ __global__ __launch_bounds__(256) void k_time_embed(const float* __restrict__ t_
   }
 }
 
-hipError_t launch_time_embed(hipStream_t st, const float* t_ev, const StageDesc* desc,
-                             const int32_t* ctr, float t_uniform, int n, const float* W_time,
-                             const float* b_time, const float* b_xin, int E_dim, int d,
-                             float* temb) {
+hipError_t launch_time_embed(hipStream_t st, const float* t_ev, const StageDesc* desc, int n,
+                             const float* W_time, const float* b_time, const float* b_xin,
+                             int E_dim, int d, float* temb) {
   if (n <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_time_embed, dim3(n), dim3(256), 0, st, t_ev, desc, ctr, t_uniform, W_time,
-                     b_time, b_xin, E_dim, d, temb);
+  if (!t_ev && !desc) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(k_time_embed, dim3(n), dim3(256), 0, st, t_ev, desc, W_time, b_time, b_xin,
+                     E_dim, d, temb);
   return hipGetLastError();
 }
 
-__global__ void k_set_counter(int32_t* ctr, int32_t v) { *ctr = v; }
-__global__ void k_stage_advance(int32_t* ctr) { *ctr += 1; }
+__global__ void k_stage_begin(StageCtl* ctl, float* out) { *ctl = StageCtl{0, 0, out}; }
 
-hipError_t launch_set_counter(hipStream_t st, int32_t* ctr, int32_t v) {
-  hipLaunchKernelGGL(k_set_counter, dim3(1), dim3(1), 0, st, ctr, v);
-  return hipGetLastError();
-}
-
-hipError_t launch_stage_advance(hipStream_t st, int32_t* ctr) {
-  hipLaunchKernelGGL(k_stage_advance, dim3(1), dim3(1), 0, st, ctr);
+hipError_t launch_stage_begin(hipStream_t st, StageCtl* ctl, float* out) {
+  hipLaunchKernelGGL(k_stage_begin, dim3(1), dim3(1), 0, st, ctl, out);
   return hipGetLastError();
 }
 
@@ -248,14 +241,15 @@ hipError_t launch_stage_advance(hipStream_t st, int32_t* ctr) {
 // with the row's LayerNorm statistics for the first block.
 __global__ __launch_bounds__(256) void k_embed(const float* __restrict__ xs, int ldx, int f,
                                                int64_t T, const int32_t* __restrict__ tok_event,
-                                               const float* __restrict__ temb,
+                                               const float* __restrict__ temb, StageCtl* ctl,
                                                const float* __restrict__ W, int d,
                                                float* __restrict__ H, int ldh,
                                                float2* __restrict__ stats) {
   const int lane = threadIdx.x & 63;
   const int64_t r = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+  const float* te = stage_row(temb, ctl, d);
   if (r >= T) return;
-  const float* te = temb + (tok_event ? (int64_t)tok_event[r] * d : 0);
+  if (tok_event) te = temb + (int64_t)tok_event[r] * d;
   float xv[16];
   for (int k = 0; k < f; ++k) xv[k] = xs[r * ldx + k];
   const int nj = d >> 6;
@@ -290,7 +284,7 @@ constexpr int kEmbTok = 8;
 constexpr int kEmbF = 9;
 __global__ __launch_bounds__(256) void k_embed256(const float* __restrict__ xs, int ldx,
                                                   int64_t T, const int32_t* __restrict__ tok_event,
-                                                  const float* __restrict__ temb,
+                                                  const float* __restrict__ temb, StageCtl* ctl,
                                                   const float* __restrict__ W,
                                                   float* __restrict__ H, int ldh,
                                                   float2* __restrict__ stats) {
@@ -298,6 +292,7 @@ __global__ __launch_bounds__(256) void k_embed256(const float* __restrict__ xs, 
   const int lane = threadIdx.x & 63;
   const int64_t r0 =
       ((int64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6)) * kEmbTok;
+  const float* stage = stage_row(temb, ctl, D);
   if (r0 >= T) return;
   float4 w[kEmbF];
 #pragma unroll
@@ -310,7 +305,7 @@ __global__ __launch_bounds__(256) void k_embed256(const float* __restrict__ xs, 
     a[t] = make_float4(0.f, 0.f, 0.f, 0.f);
     part[t] = 0.f;
     if (r < T) {
-      const float* te = temb + (tok_event ? (int64_t)tok_event[r] * D : 0);
+      const float* te = tok_event ? temb + (int64_t)tok_event[r] * D : stage;
       float4 v = *(const float4*)(te + 4 * lane);
 #pragma unroll
       for (int k = 0; k < kEmbF; ++k) {
@@ -342,44 +337,47 @@ __global__ __launch_bounds__(256) void k_embed256(const float* __restrict__ xs, 
 }
 
 hipError_t launch_embed(hipStream_t st, const float* xs, int ldx, int f, int64_t T,
-                        const int32_t* tok_event, const float* temb, const float* W_xin,
-                        int d, float* H, int ldh, float2* stats) {
+                        const int32_t* tok_event, const float* temb, StageCtl* ctl,
+                        const float* W_xin, int d, float* H, int ldh, float2* stats) {
   if (T <= 0) return hipSuccess;
   if (d == 256 && f == kEmbF && ldh % 4 == 0) {
     const int64_t waves = (T + kEmbTok - 1) / kEmbTok;
     hipLaunchKernelGGL(k_embed256, dim3((unsigned)((waves + 3) / 4)), dim3(256), 0, st, xs, ldx,
-                       T, tok_event, temb, W_xin, H, ldh, stats);
+                       T, tok_event, temb, ctl, W_xin, H, ldh, stats);
     return hipGetLastError();
   }
   hipLaunchKernelGGL(k_embed, dim3((unsigned)((T + 3) / 4)), dim3(256), 0, st, xs, ldx, f, T,
-                     tok_event, temb, W_xin, d, H, ldh, stats);
+                     tok_event, temb, ctl, W_xin, d, H, ldh, stats);
   return hipGetLastError();
 }
 
 // ---------------------------------------------------------------------------------------
+// The linear field's whole stage. Every thread reads the stage; the thread that moves on to the
+// next one does so in a launch of its own (k_linear_advance), after all have read it.
 __global__ void k_linear_update(float alpha, float beta, const StageDesc* __restrict__ desc,
-                                const int32_t* __restrict__ ctr, int64_t T, int f,
+                                const StageCtl* __restrict__ ctl, int64_t T, int f,
                                 float* __restrict__ x, float* __restrict__ acc,
-                                float* __restrict__ xs, int ldx, float* __restrict__ out,
-                                int ldo) {
+                                float* __restrict__ xs, int ldx, int ldo) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= T * f) return;
-  const StageDesc sd = desc[*ctr];
+  const StageDesc sd = desc[ctl->first];
+  float* out = sd.write_out ? ctl->out : nullptr;
   const int64_t r = i / f;
   const int k = (int)(i % f);
   const int64_t o = r * ldx + k;
   const float v = (alpha + beta * sd.t) * xs[o];
-  ode_update(sd.mode, sd.h, v, x + o, acc + o, xs + o,
-             out && sd.write_out ? out + r * ldo + k : nullptr);
+  ode_update(sd.mode, sd.h, v, x + o, acc + o, xs + o, out ? out + r * ldo + k : nullptr);
 }
+__global__ void k_linear_advance(StageCtl* ctl) { ctl->first += 1; }
 
 hipError_t launch_linear_update(hipStream_t st, float alpha, float beta, const StageDesc* desc,
-                                const int32_t* ctr, int64_t T, int f, float* x, float* acc,
-                                float* xs, int ldx, float* out, int ldo) {
+                                StageCtl* ctl, int64_t T, int f, float* x, float* acc,
+                                float* xs, int ldx, int ldo) {
   if (T <= 0) return hipSuccess;
   const int64_t n = T * f;
   hipLaunchKernelGGL(k_linear_update, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, alpha,
-                     beta, desc, ctr, T, f, x, acc, xs, ldx, out, ldo);
+                     beta, desc, ctl, T, f, x, acc, xs, ldx, ldo);
+  hipLaunchKernelGGL(k_linear_advance, dim3(1), dim3(1), 0, st, ctl);
   return hipGetLastError();
 }
 
@@ -555,15 +553,9 @@ __global__ __launch_bounds__(256) void k_head256(const float* __restrict__ H,
 #pragma unroll
     for (int c = 0; c < kHeadF; ++c) w[c][j] = *(const float4*)(Wt + c * D + 128 * j + 4 * i);
   }
-  int mode = ode.mode;
-  float h = ode.h;
-  float* out = ode.out;
-  if (ode.desc && !ode.tok_event) {
-    const StageDesc sd = ode.desc[*ode.ctr];
-    mode = sd.mode;
-    h = sd.h;
-    if (!sd.write_out) out = nullptr;
-  }
+  const OdeStage os = ode_stage(ode);
+  float* out = os.out;
+  ode_next_stage(ode);
   const float bias = i < kHeadF ? b[i] : 0.f;
 #pragma unroll
   for (int it = 0; it < kHeadIter; ++it) {
@@ -598,7 +590,7 @@ __global__ __launch_bounds__(256) void k_head256(const float* __restrict__ H,
         ode_update(sd.mode, sd.h, v + bias, ode.x + o, ode.acc + o, ode.xs + o,
                    out && sd.write_out ? out + r * ode.ldo + i : nullptr);
       } else {
-        ode_update(mode, h, v + bias, ode.x + o, ode.acc + o, ode.xs + o,
+        ode_update(os.mode, os.h, v + bias, ode.x + o, ode.acc + o, ode.xs + o,
                    out ? out + r * ode.ldo + i : nullptr);
       }
     }
@@ -642,15 +634,9 @@ __global__ __launch_bounds__(256) void k_head_rows(const float* __restrict__ H,
 #pragma unroll
       for (int f = 0; f < kHeadF; ++f) w[f][2 * c + k] = Wt[f * D + col];
     }
-  int mode = ode.mode;
-  float h = ode.h;
-  float* out = ode.out;
-  if (ode.desc && !ode.tok_event) {
-    const StageDesc sd = ode.desc[*ode.ctr];
-    mode = sd.mode;
-    h = sd.h;
-    if (!sd.write_out) out = nullptr;
-  }
+  const OdeStage os = ode_stage(ode);
+  float* out = os.out;
+  ode_next_stage(ode);
   const float bias = i < kHeadF ? b[i] : 0.f;
 #pragma unroll
   for (int it = 0; it < kIter; ++it) {
@@ -687,7 +673,7 @@ __global__ __launch_bounds__(256) void k_head_rows(const float* __restrict__ H,
         ode_update(sd.mode, sd.h, v + bias, ode.x + o, ode.acc + o, ode.xs + o,
                    out && sd.write_out ? out + r * ode.ldo + i : nullptr);
       } else {
-        ode_update(mode, h, v + bias, ode.x + o, ode.acc + o, ode.xs + o,
+        ode_update(os.mode, os.h, v + bias, ode.x + o, ode.acc + o, ode.xs + o,
                    out ? out + r * ode.ldo + i : nullptr);
       }
     }
