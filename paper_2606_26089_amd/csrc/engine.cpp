@@ -413,6 +413,11 @@ int truth_cache(fmd_model* m, Call& c) {
     return timed(m, c.st, FMD_K_OTHER, 2.0 * c.Tt * d * 2 * d * L, [&] {
       return split_truth_cache(m, c.st, c.u, c.Tt, (float*)w.kv);
     });
+  if (m->fused_ok)
+    return timed(m, c.st, FMD_K_OTHER, 2.0 * c.Tt * d * 2 * d * L, [&] {
+      return launch_truth_kv(c.st, c.u, c.Tt, m->W_tin, m->b_tin, m->g_t, m->s_t, m->fragkv,
+                             m->bkv, L, w.kv, w.cap_tok, 0);
+    });
   FMD_TRY(timed(m, c.st, FMD_K_OTHER, 0, [&] {
     return launch_truth_encode<T>(c.st, c.u, 9, 9, c.Tt, m->W_tin, m->b_tin, m->g_t, m->s_t, d,
                                   (T*)w.c, d);
@@ -1313,16 +1318,19 @@ int fmd_model_create(const fmd_model_config* cfg, const float* params, size_t n_
     m->Skv = (const u32x4*)((char*)m->splitw + split_bytes(14 * d * d, L));
   } else {
     if (grow(m->packed, (L * blk_elems) * es) != FMD_OK) return bail(FMD_E_NOMEM);
-    if (grow(m->Wkv, (size_t)(L * 2 * d * d) * es) != FMD_OK) return bail(FMD_E_NOMEM);
   }
   if (grow(m->bkv, (size_t)(L * 2 * d) * 4) != FMD_OK) return bail(FMD_E_NOMEM);
   if (grow(m->Wout_pk, (size_t)64 * d * 4) != FMD_OK) return bail(FMD_E_NOMEM);
   if (grow(m->bout_pk, (size_t)64 * 4) != FMD_OK) return bail(FMD_E_NOMEM);
   m->fused_ok = cfg->precision != FMD_FP32 &&
                 fused_supported(cfg->d_model, cfg->n_heads, cfg->mlp_ratio);
+  if (!m->split && !m->fused_ok && grow(m->Wkv, (size_t)(L * 2 * d * d) * es) != FMD_OK)
+    return bail(FMD_E_NOMEM);
   m->kv_hm = cfg->precision != FMD_FP32 && cfg->d_model == 32 * cfg->n_heads;
   m->fused = m->fused_ok ? FMD_FUSED_ALL : 0;
-  if (m->fused_ok && grow(m->frag, (size_t)(L * blk_elems) * 2) != FMD_OK) return bail(FMD_E_NOMEM);
+  if (m->fused_ok && (grow(m->frag, (size_t)(L * blk_elems) * 2) != FMD_OK ||
+                      grow(m->fragkv, (size_t)(L * 2 * d * d) * 2) != FMD_OK))
+    return bail(FMD_E_NOMEM);
   // FP8 form, per block: e4m3 fragments of W_up and W_dn (4 d^2 bytes each), then the column
   // scales s_up [4d], 1/s_up [4d], s_dn [d], 1/s_dn [d] (FP32)
   const size_t f8_blk = 8 * d * d + (size_t)10 * d * 4;
@@ -1348,6 +1356,13 @@ int fmd_model_create(const fmd_model_config* cfg, const float* params, size_t n_
     if (!m->fused_ok) return;
     *dst = fr + ((size_t)l * blk_elems + elem_off) * 2;
     if (launch_pack_frag(nullptr, m->params + off, (int)rows, (int)cols, *dst) != hipSuccess &&
+        status == FMD_OK)
+      status = fail(FMD_E_DEVICE, "weight packing failed");
+  };
+  auto pack_frag_kv = [&](size_t off, int64_t rows, int64_t cols, size_t elem_off) {
+    if (m->fused_ok &&
+        launch_pack_frag(nullptr, m->params + off, (int)rows, (int)cols,
+                         (char*)m->fragkv + elem_off * 2) != hipSuccess &&
         status == FMD_OK)
       status = fail(FMD_E_DEVICE, "weight packing failed");
   };
@@ -1443,11 +1458,13 @@ int fmd_model_create(const fmd_model_config* cfg, const float* params, size_t n_
         }
         break;
       case P_W_KC:
-        pack(off, rows, cols, wkv + (size_t)l * 2 * d * d * es);
+        if (!m->fused_ok) pack(off, rows, cols, wkv + (size_t)l * 2 * d * d * es);
+        pack_frag_kv(off, rows, cols, (size_t)l * 2 * d * d);
         pack_split(off, rows, cols, L * blk_elems + (size_t)l * 2 * d * d, nullptr);
         break;
       case P_W_VC:
-        pack(off, rows, cols, wkv + ((size_t)l * 2 * d + d) * d * es);
+        if (!m->fused_ok) pack(off, rows, cols, wkv + ((size_t)l * 2 * d + d) * d * es);
+        pack_frag_kv(off, rows, cols, ((size_t)l * 2 + 1) * d * d);
         pack_split(off, rows, cols, L * blk_elems + ((size_t)l * 2 * d + d) * d, nullptr);
         break;
       case P_B_KC:
@@ -1516,6 +1533,7 @@ int fmd_model_destroy(fmd_model* m) {
   if (m->packed) (void)hipFree(m->packed);
   if (m->frag) (void)hipFree(m->frag);
   if (m->splitw) (void)hipFree(m->splitw);
+  if (m->fragkv) (void)hipFree(m->fragkv);
   if (m->frag8) (void)hipFree(m->frag8);
   if (m->Wkv) (void)hipFree(m->Wkv);
   if (m->bkv) (void)hipFree(m->bkv);

@@ -103,6 +103,7 @@ struct fmd_model {
   float* params = nullptr;         // flat FP32 copy on device
   void* packed = nullptr;          // packed matrices in the compute type
   void* frag = nullptr;            // fragment-layout BF16 matrices of the fused kernels
+  void* fragkv = nullptr;          // fragment-layout cross K/V weights of all blocks (with frag)
   void* frag8 = nullptr;           // FP8 form: e4m3 fragments of W_up, W_dn and column scales
   std::vector<fmd::Fp8Mlp> f8;     // FP8 form: per block pointers into frag8
   void* splitw = nullptr;          // FP32 path, d_model <= 256: split fragments of every matrix

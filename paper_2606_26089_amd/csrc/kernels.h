@@ -200,6 +200,13 @@ hipError_t launch_embed(hipStream_t st, const float* xs, int ldx, int f, int64_t
 // each; this block's first plane at dst): rows land at [row0, row0 + rows).
 hipError_t launch_kv_headmajor(hipStream_t st, const void* src, int64_t rows, int d, int dh,
                                int n_heads, void* dst, int64_t plane, int64_t row0);
+// The truth encoding and every block's cross K/V planes in one kernel (d = 256, 8 heads of 32,
+// BF16; kv_bf16.hip): n particles of features u [n, 9] into rows [row0, row0 + n) of the planes
+// [L][K, V][8][plane][32]. Wf: launch_pack_frag of [W_kc | W_vc] of every block in turn, bias
+// [L][512]. Bitwise what launch_truth_encode, launch_gemm and launch_kv_headmajor give.
+hipError_t launch_truth_kv(hipStream_t st, const float* u, int64_t n, const float* W_tin,
+                           const float* b_tin, const float* g, const float* s, const void* Wf,
+                           const float* bias, int n_layers, void* kv, int64_t plane, int64_t row0);
 // Event observables (H_T, MET per event; lepton isolation per particle, NaN otherwise) of
 // reconstructed particles feat [rows, ldf] FP32 with device CSR offsets.
 hipError_t launch_event_observables(hipStream_t st, const float* feat, int ldf,

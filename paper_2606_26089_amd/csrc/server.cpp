@@ -213,6 +213,11 @@ int admit_device(fmd_server* S, Req* r, const int64_t* roff_pin, const float* fe
     HIP_TRY(split_truth_cache(m, S->st, w.u + b * 9, nT, (float*)w.kv + b * 2 * d * L));
     return FMD_OK;
   }
+  if (m->fused_ok) {
+    HIP_TRY(launch_truth_kv(S->st, w.u + b * 9, nT, m->W_tin, m->b_tin, m->g_t, m->s_t, m->fragkv,
+                            m->bkv, L, w.kv, w.cap_tok, b));
+    return FMD_OK;
+  }
   const size_t es = sizeof(T);
   T* cb = (T*)w.c + b * d;
   HIP_TRY(launch_truth_encode<T>(S->st, w.u + b * 9, 9, 9, nT, m->W_tin, m->b_tin, m->g_t, m->s_t,
