@@ -1614,8 +1614,8 @@ int fmd_event_observables(const fmd_events_in* reco, float* ht, float* met, floa
   if (!reco || !reco->offsets || reco->n_events < 0) return fail(FMD_E_INVALID, "bad events");
   const int64_t E = reco->n_events;
   fmd_events_in ev = *reco;
-  int64_t T = 0;
-  FMD_TRY(check_events(nullptr, &ev, &T, nullptr));
+  int64_t T = 0, max_n = 0;
+  FMD_TRY(check_events(nullptr, &ev, &T, &max_n));
   if (E == 0) return FMD_OK;
   if (!ht || !met || (T > 0 && (!iso || !reco->feat))) return fail(FMD_E_INVALID, "null output");
   hipStream_t st = (hipStream_t)hip_stream;
@@ -1651,7 +1651,7 @@ int fmd_event_observables(const fmd_events_in* reco, float* ht, float* met, floa
   hipError_t e = hipMemcpyAsync(d_off, reco->offsets, b_off, hipMemcpyHostToDevice, st);
   if (e == hipSuccess && !dev && T > 0)
     e = hipMemcpyAsync((void*)d_feat, reco->feat, b_feat, hipMemcpyHostToDevice, st);
-  if (e == hipSuccess) e = launch_event_observables(st, d_feat, 9, d_off, E, d_ht, d_met, d_iso);
+  if (e == hipSuccess) e = launch_event_observables(st, d_feat, 9, d_off, E, max_n, d_ht, d_met, d_iso);
   if (e == hipSuccess && !dev) {
     e = hipMemcpyAsync(ht, d_ht, (size_t)E * 4, hipMemcpyDeviceToHost, st);
     if (e == hipSuccess) e = hipMemcpyAsync(met, d_met, (size_t)E * 4, hipMemcpyDeviceToHost, st);

@@ -208,10 +208,10 @@ hipError_t launch_truth_kv(hipStream_t st, const float* u, int64_t n, const floa
                            const float* b_tin, const float* g, const float* s, const void* Wf,
                            const float* bias, int n_layers, void* kv, int64_t plane, int64_t row0);
 // Event observables (H_T, MET per event; lepton isolation per particle, NaN otherwise) of
-// reconstructed particles feat [rows, ldf] FP32 with device CSR offsets.
+// reconstructed particles feat [rows, ldf] FP32 with device CSR offsets; max_n: the largest event.
 hipError_t launch_event_observables(hipStream_t st, const float* feat, int ldf,
-                                    const int64_t* off_device, int64_t n_events, float* ht,
-                                    float* met, float* iso);
+                                    const int64_t* off_device, int64_t n_events, int64_t max_n,
+                                    float* ht, float* met, float* iso);
 // Truth preprocessing: per-event keep flags and counts (pass 1), then the kept rows in input
 // order at off_out (pass 2); see fmd_truth_select.
 // Reco multiplicity per event under the stand-in law (cnt [E] int32; off device [E + 1]).

@@ -733,8 +733,11 @@ hipError_t launch_kv_headmajor(hipStream_t st, const void* src, int64_t rows, in
 // particles inside Delta R < 0.4, over the lepton's pT. One workgroup per event. pT, the
 // trigonometric terms and every sum are FP64; the class maximum and the cone test are taken
 // in FP32 with separate multiplies and adds (integer decisions in the input's precision).
-// The event's particles stream through LDS in tiles of kObsTile; each thread takes
-// particles i = tid, tid + 256, ... and sums its cone members in order of j.
+// Each particle is decoded once into an LDS tile (an event of up to kObsTile particles is one
+// tile; longer ones stage their tiles again for every batch of leptons) while its leptons are
+// gathered, so that the cone sums run on leptons only, four threads each taking every fourth
+// particle: with a thread per particle two of five waves' lanes did all of that work, one
+// particle at a time, and every particle was decoded three times.
 namespace {
 constexpr int kObsTile = 1024;
 constexpr float kObsTwoPi = (float)(2.0 * 3.14159265358979323846);
@@ -757,86 +760,123 @@ __device__ __forceinline__ bool obs_in_cone(float eta_i, float phi_i, float eta_
   return deta * deta + dphi * dphi < 0.16f;
 }
 
-__device__ __forceinline__ double obs_block_sum(double v, double* red) {
+__device__ __forceinline__ double obs_wave_sum(double v) {
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, kWave);
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  __syncthreads();
-  if (lane == 0) red[wave] = v;
-  __syncthreads();
-  double t = 0.0;
-#pragma unroll
-  for (int q = 0; q < 4; ++q) t += red[q];       // the same order in every thread
-  return t;
+  return v;
 }
+
+struct ObsItem {       // a decoded particle, 16 bytes
+  double pt;
+  float eta, phi;
+};
+constexpr int kObsParts = 4;          // threads per lepton
 }  // namespace
 
-__global__ __launch_bounds__(256) void k_event_observables(const float* __restrict__ feat,
-                                                           int ldf,
-                                                           const int64_t* __restrict__ off,
-                                                           float* __restrict__ ht,
-                                                           float* __restrict__ met,
-                                                           float* __restrict__ iso) {
-  __shared__ double s_pt[kObsTile];
-  __shared__ float s_eta[kObsTile], s_phi[kObsTile];
-  __shared__ double red[4];
-  const int e = blockIdx.x, tid = threadIdx.x;
+template <int NT>
+__global__ __launch_bounds__(NT) void k_event_observables(const float* __restrict__ feat, int ldf,
+                                                          const int64_t* __restrict__ off,
+                                                          float* __restrict__ ht,
+                                                          float* __restrict__ met,
+                                                          float* __restrict__ iso) {
+  constexpr int NW = NT / 64;
+  __shared__ ObsItem item[kObsTile];
+  __shared__ uint16_t lep[kObsTile];             // the tile's leptons, in any order
+  __shared__ int n_lep;
+  __shared__ double red[NW][3];
+  const int e = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int64_t a = off[e], n = off[e + 1] - a;
+  const bool one_tile = n <= kObsTile;
+  auto decode = [&](const float* f) { return ObsItem{10.0 * exp((double)f[0]), f[1], f[2]}; };
   double h = 0.0, px = 0.0, py = 0.0;
-  for (int64_t i = tid; i < n; i += 256) {
-    const float* f = feat + (a + i) * ldf;
-    const double pt = 10.0 * exp((double)f[0]);
-    const double phi = (double)f[2];
-    h += pt;
-    px += pt * cos(phi);
-    py += pt * sin(phi);
-  }
-  h = obs_block_sum(h, red);
-  px = obs_block_sum(px, red);
-  py = obs_block_sum(py, red);
-  if (tid == 0) {
-    ht[e] = (float)h;
-    met[e] = (float)sqrt(px * px + py * py);
-  }
-  for (int64_t i0 = 0; i0 < n; i0 += 256) {
-    const int64_t i = i0 + tid;
-    bool lep = false;
-    double pt_i = 0.0;
-    float eta_i = 0.f, phi_i = 0.f;
-    if (i < n) {
-      const float* f = feat + (a + i) * ldf;
-      const int c = obs_class(f);
-      lep = c == 1 || c == 2;                      // electron, muon
-      pt_i = 10.0 * exp((double)f[0]);
-      eta_i = f[1];
-      phi_i = f[2];
-    }
-    double sum = 0.0;
-    for (int64_t j0 = 0; j0 < n; j0 += kObsTile) {
-      const int nt = (int)min<int64_t>(kObsTile, n - j0);
-      __syncthreads();
-      for (int j = tid; j < nt; j += 256) {
-        const float* f = feat + (a + j0 + j) * ldf;
-        s_pt[j] = 10.0 * exp((double)f[0]);
-        s_eta[j] = f[1];
-        s_phi[j] = f[2];
+  for (int64_t i0 = 0; i0 < n; i0 += kObsTile) {
+    const int nt = (int)min<int64_t>(kObsTile, n - i0);
+    if (i0) __syncthreads();                     // the tile before is consumed
+    if (tid == 0) n_lep = 0;
+    __syncthreads();
+    for (int c = 0; c < nt; c += NT) {
+      const int i = c + tid;
+      bool is_lep = false;
+      if (i < nt) {
+        const float* f = feat + (a + i0 + i) * ldf;
+        const ObsItem it = decode(f);
+        double sn, cs;
+        sincos((double)it.phi, &sn, &cs);
+        h += it.pt;
+        px += it.pt * cs;
+        py += it.pt * sn;
+        item[i] = it;
+        const int cl = obs_class(f);
+        is_lep = cl == 1 || cl == 2;             // electron, muon
+        if (!is_lep) iso[a + i0 + i] = __builtin_nanf("");
       }
-      __syncthreads();
-      if (lep)
-        for (int j = 0; j < nt; ++j)
-          if (j0 + j != i && obs_in_cone(eta_i, phi_i, s_eta[j], s_phi[j])) sum += s_pt[j];
+      const uint64_t bal = __ballot(is_lep);
+      if (bal) {
+        int base = 0;
+        if (lane == 0) base = atomicAdd(&n_lep, __popcll(bal));
+        base = __shfl(base, 0, kWave);
+        if (is_lep) lep[base + __popcll(bal & (lane ? ~0ull >> (64 - lane) : 0ull))] = (uint16_t)i;
+      }
     }
-    if (i < n) iso[a + i] = lep ? (float)(sum / pt_i) : __builtin_nanf("");
+    __syncthreads();
+    const int nl = n_lep, part = tid % kObsParts;
+    for (int b0 = 0; b0 < nl; b0 += NT / kObsParts) {
+      const int b = b0 + tid / kObsParts;
+      const bool on = b < nl;
+      const int64_t i = i0 + (on ? lep[b] : 0);
+      const ObsItem me = one_tile ? item[i] : decode(feat + (a + i) * ldf);
+      double sum = 0.0;
+      for (int64_t j0 = 0; j0 < n; j0 += kObsTile) {
+        const int mt = (int)min<int64_t>(kObsTile, n - j0);
+        if (!one_tile) {
+          __syncthreads();
+          for (int j = tid; j < mt; j += NT) item[j] = decode(feat + (a + j0 + j) * ldf);
+          __syncthreads();
+        }
+        if (on) {
+          const int self = i >= j0 && i < j0 + mt ? (int)(i - j0) : -1;
+#pragma unroll 4
+          for (int j = part; j < mt; j += kObsParts) {
+            const ObsItem o = item[j];
+            const bool in = obs_in_cone(me.eta, me.phi, o.eta, o.phi) && j != self;
+            sum += in ? o.pt : 0.0;
+          }
+        }
+      }
+#pragma unroll
+      for (int o = 1; o < kObsParts; o <<= 1) sum += __shfl_xor(sum, o, kWave);
+      if (on && part == 0) iso[a + i] = (float)(sum / me.pt);
+    }
+  }
+  h = obs_wave_sum(h);
+  px = obs_wave_sum(px);
+  py = obs_wave_sum(py);
+  if (lane == 0) red[wave][0] = h, red[wave][1] = px, red[wave][2] = py;
+  __syncthreads();
+  if (tid == 0) {
+    double t[3] = {0.0, 0.0, 0.0};
+    for (int q = 0; q < NW; ++q)
+      for (int k = 0; k < 3; ++k) t[k] += red[q][k];
+    ht[e] = (float)t[0];
+    met[e] = (float)sqrt(t[1] * t[1] + t[2] * t[2]);
   }
 }
 
 hipError_t launch_event_observables(hipStream_t st, const float* feat, int ldf,
-                                    const int64_t* off_device, int64_t n_events, float* ht,
-                                    float* met, float* iso) {
+                                    const int64_t* off_device, int64_t n_events, int64_t max_n,
+                                    float* ht, float* met, float* iso) {
   if (n_events <= 0) return hipSuccess;
   if (n_events > 0x7fffffff || ldf < 8) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_event_observables, dim3((unsigned)n_events), dim3(256), 0, st, feat, ldf,
-                     off_device, ht, met, iso);
+  // Threads per event: enough events fill the chip, and idle threads of small ones then cost more
+  // than they shorten (4096 events of 20-200: 61 us a call with 128, 63 with 256, 77 with 512;
+  // 16,384 heavy-tailed ones of up to 1000: 237, 180 and 230); few events are bound by the
+  // longest one (64 heavy-tailed: 92, 60 and 46 us; before, a thread per particle: 88, 545, 238)
+  const bool small = max_n <= 256;
+  const int nt = n_events > 2048 ? (small ? 128 : 256) : n_events > 512 && small ? 256 : 512;
+  auto* k = nt == 128   ? k_event_observables<128>
+            : nt == 256 ? k_event_observables<256>
+                        : k_event_observables<512>;
+  hipLaunchKernelGGL(k, dim3((unsigned)n_events), dim3(nt), 0, st, feat, ldf, off_device, ht, met, iso);
   return hipGetLastError();
 }
 
