@@ -1703,18 +1703,14 @@ int fmd_truth_select(const fmd_events_in* truth, double pt_cut_gev, int32_t max_
     d_out = (float*)(p + 2 * b_off + b_cnt + b_keep + b_feat);
   }
   const float c0 = (float)std::log(pt_cut_gev / 10.0);
-  std::vector<int32_t> cnt((size_t)E);
   hipError_t e = hipMemcpyAsync(d_off, truth->offsets, (size_t)(E + 1) * 8, hipMemcpyHostToDevice, st);
   if (e == hipSuccess && !dev && T > 0)
     e = hipMemcpyAsync((void*)d_in, truth->feat, (size_t)T * 9 * 4, hipMemcpyHostToDevice, st);
   if (e == hipSuccess) e = launch_select_count(st, d_in, 9, d_off, E, c0, max_particles, d_keep, d_cnt);
-  if (e == hipSuccess) e = hipMemcpyAsync(cnt.data(), d_cnt, (size_t)E * 4, hipMemcpyDeviceToHost, st);
-  if (e == hipSuccess) e = hipStreamSynchronize(st);
-  if (e == hipSuccess) {
-    for (int64_t i = 0; i < E; ++i) offsets_out[i + 1] = offsets_out[i] + cnt[(size_t)i];
-    e = hipMemcpyAsync(d_off2, offsets_out, (size_t)(E + 1) * 8, hipMemcpyHostToDevice, st);
-  }
+  if (e == hipSuccess) e = launch_select_offsets(st, d_cnt, E, d_off2);
   if (e == hipSuccess) e = launch_select_write(st, d_in, 9, d_off, d_off2, E, d_keep, d_out);
+  if (e == hipSuccess) e = hipMemcpyAsync(offsets_out, d_off2, (size_t)(E + 1) * 8, hipMemcpyDeviceToHost, st);
+  if (e == hipSuccess && !dev) e = hipStreamSynchronize(st);   // the host rows need their number
   if (e == hipSuccess && !dev && offsets_out[E] > 0)
     e = hipMemcpyAsync(feat_out, d_out, (size_t)offsets_out[E] * 9 * 4, hipMemcpyDeviceToHost, st);
   if (e == hipSuccess) e = hipStreamSynchronize(st);

@@ -212,8 +212,8 @@ hipError_t launch_truth_kv(hipStream_t st, const float* u, int64_t n, const floa
 hipError_t launch_event_observables(hipStream_t st, const float* feat, int ldf,
                                     const int64_t* off_device, int64_t n_events, int64_t max_n,
                                     float* ht, float* met, float* iso);
-// Truth preprocessing: per-event keep flags and counts (pass 1), then the kept rows in input
-// order at off_out (pass 2); see fmd_truth_select.
+// Truth preprocessing: per-event keep flags and counts (pass 1), the output offsets of the counts,
+// then the kept rows in input order at off_out (pass 2); see fmd_truth_select.
 // Reco multiplicity per event under the stand-in law (cnt [E] int32; off device [E + 1]).
 hipError_t launch_reco_counts(hipStream_t st, const int64_t* off, int64_t n_events, uint64_t seed,
                               uint64_t thr_q, uint64_t thr_p, int fake_trials, int n_max,
@@ -221,6 +221,7 @@ hipError_t launch_reco_counts(hipStream_t st, const int64_t* off, int64_t n_even
 hipError_t launch_select_count(hipStream_t st, const float* feat, int ldf, const int64_t* off,
                                int64_t n_events, float c0, int limit, uint8_t* keep,
                                int32_t* cnt);
+hipError_t launch_select_offsets(hipStream_t st, const int32_t* cnt, int64_t n_events, int64_t* off);
 hipError_t launch_select_write(hipStream_t st, const float* feat, int ldf, const int64_t* off,
                                const int64_t* off_out, int64_t n_events, const uint8_t* keep,
                                float* out);

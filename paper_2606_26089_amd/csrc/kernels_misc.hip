@@ -884,51 +884,108 @@ hipError_t launch_event_observables(hipStream_t st, const float* feat, int ldf,
 // Truth preprocessing before the sampler: the model's pT cut and particle limit (stream
 // compaction per event). Pass 1, one workgroup per event: a particle survives when
 // x0 > c0 (x0 = ln(pT / 10 GeV), c0 = ln(cut / 10 GeV) in float32); if more than `limit`
-// survive, a survivor is kept when fewer than `limit` survivors rank before it (larger x0,
-// or equal x0 and an earlier position). Writes keep[row] and the event's count. Pass 2
-// writes the kept rows in input order at the event's output offset (a block-wide prefix
-// sum of the keep flags).
+// survive, the `limit` largest x0 are kept (equal x0: the earlier particles). Writes keep[row]
+// and the event's count. A prefix sum turns the counts into the output offsets, and pass 2 writes
+// the kept rows in input order.
+// The cut-off of an event above the limit is found by radix selection on order-preserving
+// integer keys: four histograms of eight bits, linear in the event where a rank per particle was
+// quadratic (64 heavy-tailed events of up to 1000: 224 -> 53 us a call; 4096 of 20-200: 48 -> 14 us
+// a launch). Pass 2 copies an event as one run of floats, not a row per thread (19 -> 10 us). With
+// the prefix sum on the device (4 us) the host waits once, for the offsets: 123 -> 66 us a call.
 namespace {
-constexpr int kSelTile = 1024;
+constexpr int kSelKeys = 2048;        // keys held in LDS; longer events read theirs again
+
+// Order-preserving key of a survivor: larger x, larger key; +0 and -0 alike; never 0.
+__device__ __forceinline__ uint32_t sel_key(float x) {
+  const uint32_t b = __float_as_uint(x + 0.f);
+  return b ^ ((b >> 31) ? 0xffffffffu : 0x80000000u);
+}
 }  // namespace
 
 __global__ __launch_bounds__(256) void k_select_count(const float* __restrict__ feat, int ldf,
                                                       const int64_t* __restrict__ off, float c0,
                                                       int limit, uint8_t* __restrict__ keep,
                                                       int32_t* __restrict__ cnt) {
-  __shared__ float s_x[kSelTile];
-  __shared__ int s_n;
-  const int e = blockIdx.x, tid = threadIdx.x;
+  __shared__ uint32_t s_key[kSelKeys];   // 0: not a survivor
+  __shared__ int s_n[4], s_hist[256], s_bin, s_above;
+  const int e = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int64_t a = off[e], n = off[e + 1] - a;
-  if (tid == 0) s_n = 0;
-  __syncthreads();
+  auto load_key = [&](int64_t i) -> uint32_t {
+    const float x = feat[(a + i) * ldf];
+    return x > c0 ? sel_key(x) : 0u;
+  };
   int mine = 0;
-  for (int64_t i = tid; i < n; i += 256) mine += feat[(a + i) * ldf] > c0;
-  atomicAdd(&s_n, mine);                 // LDS atomic: an integer count, order-free
+  for (int64_t i = tid; i < n; i += 256) {
+    const uint32_t k = load_key(i);
+    if (i < kSelKeys) s_key[i] = k;
+    mine += k != 0;
+  }
+  auto key = [&](int64_t i) { return i < kSelKeys ? s_key[i] : load_key(i); };   // own particles
+  for (int o = 32; o > 0; o >>= 1) mine += __shfl_xor(mine, o, kWave);
+  if (lane == 0) s_n[wave] = mine;
   __syncthreads();
-  const int surv = s_n;
-  const bool all = surv <= limit;
-  for (int64_t i0 = 0; i0 < n; i0 += 256) {
-    const int64_t i = i0 + tid;
-    const float xi = i < n ? feat[(a + i) * ldf] : 0.f;
-    const bool si = i < n && xi > c0;
-    int rank = 0;
-    if (!all) {
-      for (int64_t j0 = 0; j0 < n; j0 += kSelTile) {
-        const int nt = (int)min<int64_t>(kSelTile, n - j0);
-        __syncthreads();
-        for (int j = tid; j < nt; j += 256) s_x[j] = feat[(a + j0 + j) * ldf];
-        __syncthreads();
-        if (si)
-          for (int j = 0; j < nt; ++j) {
-            const float xj = s_x[j];
-            rank += xj > c0 && (xj > xi || (xj == xi && j0 + j < i));
-          }
+  const int surv = s_n[0] + s_n[1] + s_n[2] + s_n[3];
+  if (tid == 0) cnt[e] = min(surv, limit);
+  if (surv <= limit || limit <= 0) {
+    for (int64_t i = tid; i < n; i += 256) keep[a + i] = limit > 0 && key(i) != 0;
+    return;
+  }
+  // the limit-th largest key, eight bits at a time: `need` keys are left to take among those
+  // that agree with `top` in the bits fixed so far
+  uint32_t top = 0, fixed = 0;
+  int need = limit;
+  for (int shift = 24; shift >= 0; shift -= 8) {
+    s_hist[tid] = 0;
+    __syncthreads();
+    for (int64_t i = tid; i < n; i += 256) {
+      const uint32_t k = key(i);
+      if (k != 0 && (k & fixed) == top) atomicAdd(&s_hist[(k >> shift) & 255], 1);
+    }
+    __syncthreads();
+    if (wave == 0) {
+      // lane l: bins 255 - 4l .. 252 - 4l, largest keys first; the bin where the running count
+      // reaches `need`
+      int c[4], sum = 0;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) sum += c[q] = s_hist[255 - 4 * lane - q];
+      int run = sum;
+#pragma unroll
+      for (int o = 1; o < 64; o <<= 1) {
+        const int v = __shfl_up(run, o, kWave);
+        if (lane >= o) run += v;
+      }
+      int before = run - sum;
+      if (before < need && run >= need) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          if (before < need && before + c[q] >= need) s_bin = 255 - 4 * lane - q, s_above = before;
+          before += c[q];
+        }
       }
     }
-    if (i < n) keep[a + i] = si && (all || rank < limit);
+    __syncthreads();
+    need -= s_above;
+    top |= (uint32_t)s_bin << shift;
+    fixed |= 255u << shift;
+    __syncthreads();   // s_bin and s_hist are rewritten
   }
-  if (tid == 0) cnt[e] = all ? surv : limit;
+  // keys above `top` stay, and the first `need` of those equal to it
+  int taken = 0;
+  for (int64_t i0 = 0; i0 < n; i0 += 256) {
+    const int64_t i = i0 + tid;
+    const uint32_t k = i < n ? key(i) : 0;
+    const bool eq = k == top;
+    const uint64_t bal = __ballot(eq);
+    if (lane == 0) s_n[wave] = __popcll(bal);
+    __syncthreads();
+    int before = taken + __popcll(bal & (lane ? ~0ull >> (64 - lane) : 0ull));
+    for (int q = 0; q < 4; ++q) {
+      if (q < wave) before += s_n[q];
+      taken += s_n[q];
+    }
+    if (i < n) keep[a + i] = k > top || (eq && before < need);
+    __syncthreads();
+  }
 }
 
 __global__ __launch_bounds__(256) void k_select_write(const float* __restrict__ feat, int ldf,
@@ -936,28 +993,68 @@ __global__ __launch_bounds__(256) void k_select_write(const float* __restrict__ 
                                                       const int64_t* __restrict__ off_out,
                                                       const uint8_t* __restrict__ keep,
                                                       float* __restrict__ out) {
+  constexpr int kRows = 256;
   __shared__ int s_tot[4];
+  __shared__ int16_t s_pos[kRows];       // kept row -> position in the chunk's output, else -1
   const int e = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int64_t a = off[e], n = off[e + 1] - a;
   int64_t base = off_out[e];
-  for (int64_t i0 = 0; i0 < n; i0 += 256) {
+  for (int64_t i0 = 0; i0 < n; i0 += kRows) {
     const int64_t i = i0 + tid;
     const bool k = i < n && keep[a + i];
     // block prefix of the flags: ballot within the wave, wave totals through LDS
     const uint64_t bal = __ballot(k);
-    const int before_w = __popcll(bal & ((lane ? (~0ull >> (64 - lane)) : 0ull)));
-    __syncthreads();
     if (lane == 0) s_tot[wave] = __popcll(bal);
     __syncthreads();
-    int before = before_w;
+    int before = __popcll(bal & (lane ? ~0ull >> (64 - lane) : 0ull));
     for (int q = 0; q < wave; ++q) before += s_tot[q];
-    if (k) {
-      const float* src = feat + (a + i) * ldf;
-      float* dst = out + (base + before) * ldf;
-      for (int f = 0; f < ldf; ++f) dst[f] = src[f];
+    s_pos[tid] = k ? (int16_t)before : (int16_t)-1;
+    __syncthreads();
+    const int floats = (int)min<int64_t>(kRows, n - i0) * ldf;
+    const float* src = feat + (a + i0) * ldf;
+    float* dst = out + base * ldf;
+    for (int t = tid; t < floats; t += 256) {
+      const int row = t / ldf, pos = s_pos[row];
+      if (pos >= 0) dst[pos * ldf + (t - row * ldf)] = src[t];
     }
     base += s_tot[0] + s_tot[1] + s_tot[2] + s_tot[3];
+    __syncthreads();                     // s_tot and s_pos are rewritten
   }
+}
+
+// Exclusive prefix sum of the per-event counts into int64 offsets (off[0] = 0, off[E] = total),
+// one workgroup: wave w of the sixteen scans events 64 per step in registers, sixteen such runs a
+// round, the running total carried through LDS.
+__global__ __launch_bounds__(1024) void k_select_offsets(const int32_t* __restrict__ cnt, int64_t E,
+                                                         int64_t* __restrict__ off) {
+  constexpr int kPer = 4;                // events per thread and round
+  __shared__ int64_t s_wave[16];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  int64_t carry = 0;
+  for (int64_t e0 = 0; e0 < E; e0 += 1024 * kPer) {
+    const int64_t i0 = e0 + (int64_t)tid * kPer;
+    int c[kPer], sum = 0;
+#pragma unroll
+    for (int q = 0; q < kPer; ++q) sum += c[q] = i0 + q < E ? cnt[i0 + q] : 0;
+    int64_t run = sum;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const int64_t v = __shfl_up(run, o, kWave);
+      if (lane >= o) run += v;
+    }
+    if (lane == 63) s_wave[wave] = run;
+    __syncthreads();
+    int64_t p = carry + run - sum;
+    for (int q = 0; q < 16; ++q) {
+      if (q < wave) p += s_wave[q];
+      carry += s_wave[q];
+    }
+#pragma unroll
+    for (int q = 0; q < kPer; ++q)
+      if (i0 + q < E) off[i0 + q] = p, p += c[q];
+    __syncthreads();                     // s_wave is rewritten
+  }
+  if (tid == 0) off[E] = carry;
 }
 
 // Reco multiplicity per event (a stand-in law; the model can emit particles that match no
@@ -1014,6 +1111,11 @@ hipError_t launch_select_count(hipStream_t st, const float* feat, int ldf, const
   if (n_events > 0x7fffffff || limit < 0) return hipErrorInvalidValue;
   hipLaunchKernelGGL(k_select_count, dim3((unsigned)n_events), dim3(256), 0, st, feat, ldf, off,
                      c0, limit, keep, cnt);
+  return hipGetLastError();
+}
+
+hipError_t launch_select_offsets(hipStream_t st, const int32_t* cnt, int64_t n_events, int64_t* off) {
+  hipLaunchKernelGGL(k_select_offsets, dim3(1), dim3(1024), 0, st, cnt, n_events, off);
   return hipGetLastError();
 }
 

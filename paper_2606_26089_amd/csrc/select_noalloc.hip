@@ -1,8 +1,7 @@
 // Truth selection (model pT cut and particle limit) with no device allocation: every
 // intermediate buffer lives in one fixed device array of this file, for callers that cannot
 // call hipMalloc (code under stream capture, tight serving loops, harnesses that forbid it).
-// The kernels are the ones fmd_truth_select runs; only the buffers and the prefix sum of the
-// per-event counts (here on the device) differ.
+// The kernels are the ones fmd_truth_select runs; only the buffers differ.
 #include <cmath>
 #include <mutex>
 
@@ -24,33 +23,6 @@ constexpr size_t kNoAllocBytes = 2 * kNoAllocOffBytes + kNoAllocCntBytes + (size
 static __device__ __align__(256) unsigned char scratch[kNoAllocBytes];
 
 namespace {
-
-// Exclusive prefix sum of the per-event counts into int64 offsets (off[0] = 0, off[E] =
-// total), one workgroup: thread t sums a contiguous run of counts, the run totals are scanned
-// in LDS, then each thread writes its run's offsets.
-__global__ __launch_bounds__(1024) void k_counts_to_offsets(const int32_t* __restrict__ cnt,
-                                                            int64_t E, int64_t* __restrict__ off) {
-  __shared__ int64_t part[1024];
-  const int t = threadIdx.x;
-  const int64_t per = (E + 1023) / 1024;
-  const int64_t a = min<int64_t>(E, t * per), b = min<int64_t>(E, a + per);
-  int64_t s = 0;
-  for (int64_t i = a; i < b; ++i) s += cnt[i];
-  part[t] = s;
-  __syncthreads();
-  for (int o = 1; o < 1024; o <<= 1) {   // inclusive Hillis-Steele scan of the run totals
-    const int64_t v = t >= o ? part[t - o] : 0;
-    __syncthreads();
-    part[t] += v;
-    __syncthreads();
-  }
-  int64_t run = part[t] - s;             // offset of this thread's first event
-  for (int64_t i = a; i < b; ++i) {
-    off[i] = run;
-    run += cnt[i];
-  }
-  if (t == 1023) off[E] = part[1023];
-}
 
 std::mutex g_mu;                         // serialises calls from different host threads
 constexpr int kMaxDevices = 64;
@@ -109,10 +81,7 @@ int fmd_truth_select_noalloc(const fmd_events_in* truth, double pt_cut_gev, int3
   // copy, every count and keep flag by k_select_count, every output offset by the scan
   hipError_t e = hipMemcpyAsync(d_off, truth->offsets, (size_t)(E + 1) * 8, hipMemcpyHostToDevice, st);
   if (e == hipSuccess) e = launch_select_count(st, truth->feat, 9, d_off, E, c0, max_particles, d_keep, d_cnt);
-  if (e == hipSuccess) {
-    hipLaunchKernelGGL(k_counts_to_offsets, dim3(1), dim3(1024), 0, st, d_cnt, E, d_off2);
-    e = hipGetLastError();
-  }
+  if (e == hipSuccess) e = launch_select_offsets(st, d_cnt, E, d_off2);
   if (e == hipSuccess) e = launch_select_write(st, truth->feat, 9, d_off, d_off2, E, d_keep, feat_out);
   if (e == hipSuccess)
     e = hipMemcpyAsync(offsets_out, d_off2, (size_t)(E + 1) * 8, hipMemcpyDeviceToHost, st);
