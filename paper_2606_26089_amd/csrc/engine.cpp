@@ -796,6 +796,31 @@ int event_times(fmd_model* m, Call& c, const float* t_ev) {
   });
 }
 
+// Whether the blocks run as two chained kernels instead of six products (block_split.hip): width
+// 64. With per-kernel timing on, the separate products run, so that the classes keep their
+// meaning. The results are bitwise the same.
+bool split_blocks(const fmd_model* m) { return m->cfg.d_model == 64 && !m->timing; }
+
+SplitBlockArgs split_block_args(const fmd_model* m, int l, bool mlp) {
+  const Workspace& w = m->ws;
+  const DevBlock& B = m->blk[l];
+  SplitBlockArgs a{};
+  a.att = (const float*)w.att;
+  a.H = w.H;
+  if (!mlp) {
+    a.Wf_o = B.So, a.b_o = B.bo, a.g = B.g2, a.s = B.s2;
+    a.Wf_qc = B.Sqc, a.b_qc = B.bqc, a.qc = (float*)w.qc;
+    return a;
+  }
+  a.Wf_o = B.Soc, a.b_o = B.boc, a.g = B.g3, a.s = B.s3;
+  a.Wf_up = B.Sup, a.b_up = B.bup, a.Wf_dn = B.Sdn, a.b_dn = B.bdn;
+  if (l + 1 < m->cfg.n_blocks) {
+    const DevBlock& N = m->blk[l + 1];
+    a.gn = N.g1, a.sn = N.s1, a.Wf_qkv = N.Sqkv, a.b_qkv = N.bqkv, a.qkv = (float*)w.qkv;
+  }
+  return a;
+}
+
 // The network of net_forward on the FP32 path with split products (d_model <= 256).
 int net_forward_split(fmd_model* m, Call& c, const float* t_ev) {
   Workspace& w = m->ws;
@@ -814,20 +839,34 @@ int net_forward_split(fmd_model* m, Call& c, const float* t_ev) {
       return launch_split_gemm(c.st, cls, c.Tp, p, m->tune[split_slot(cls)][bucket_of(c.Tp)]);
     });
   };
+  const bool chained = split_blocks(m);
   for (int l = 0; l < L; ++l) {
     const DevBlock& B = m->blk[l];
-    FMD_TRY(product(FMD_K_GEMM_QKV, l == 0 ? SPLIT_QKV_EMBED : SPLIT_QKV, B, w.H));
+    if (l == 0 || !chained)
+      FMD_TRY(product(FMD_K_GEMM_QKV, l == 0 ? SPLIT_QKV_EMBED : SPLIT_QKV, B, w.H));
     FMD_TRY(timed(m, c.st, FMD_K_ATTN_SELF, 4.0 * c.sum_n2 * d, Td * 4 * d * 4, [&] {
       return launch_self_attention<float>(m, c, c.qt, c.items, c.bins, w.work);
     }));
-    FMD_TRY(product(FMD_K_GEMM_PROJ, SPLIT_PROJ, B, w.att));
-    FMD_TRY(product(FMD_K_GEMM_QC, SPLIT_QC, B, w.H));
+    if (chained) {
+      FMD_TRY(timed(m, c.st, FMD_K_GEMM_QC, 0, [&] {
+        return launch_split_oqc(c.st, c.Tp, split_block_args(m, l, false));
+      }));
+    } else {
+      FMD_TRY(product(FMD_K_GEMM_PROJ, SPLIT_PROJ, B, w.att));
+      FMD_TRY(product(FMD_K_GEMM_QC, SPLIT_QC, B, w.H));
+    }
     FMD_TRY(timed(m, c.st, FMD_K_ATTN_CROSS, 4.0 * c.sum_nx * d, (Td * 2 + c.Tt * 2.0) * d * 4, [&] {
       const float* kb = kv + (size_t)l * 2 * d;
       return launch_attention<float>(c.st, true, dh, Hh, c.qt, c.items_x, c.bins_x, w.work + c.work_x,
                                      (const float*)w.qc, d, dh, kb, kb + d, 2 * d * L, dh,
                                      (float*)w.att, d, dh);
     }));
+    if (chained) {
+      FMD_TRY(timed(m, c.st, FMD_K_GEMM_UP, 0, [&] {
+        return launch_split_mlp(c.st, c.Tp, split_block_args(m, l, true));
+      }));
+      continue;
+    }
     FMD_TRY(product(FMD_K_GEMM_PROJ, SPLIT_PROJ_CROSS, B, w.att));
     FMD_TRY(product(FMD_K_GEMM_UP, SPLIT_UP, B, w.H));
     FMD_TRY(product(FMD_K_GEMM_DOWN, SPLIT_DOWN, B, w.hid));

@@ -32,8 +32,7 @@
 //
 // Weight layout (launch_pack_split): [N/32][K/16][3 planes][64 lanes][8], lane l of fragment
 // (nb, ks) holding W[16 ks + 8 (l/32) + j][32 nb + l%32].
-#include "common.h"
-#include "kernels.h"
+#include "split_common.h"
 
 namespace fmd {
 namespace {
@@ -44,63 +43,6 @@ constexpr int kPanel = 256;            // K columns in LDS at a time
 constexpr int kLdP = kPanel + 8;       // LDS pitch (bf16) of a plane row
 // sched_group_barrier instruction classes
 constexpr int kSchedValu = 0x002, kSchedMfma = 0x008, kSchedVmemRead = 0x020, kSchedDsRead = 0x100;
-
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-
-// x = hi + mid + lo for four values
-__device__ __forceinline__ void split4(float4 x, bf16x4 (&p)[3]) {
-  const float v[4] = {x.x, x.y, x.z, x.w};
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const uint32_t hb = __float_as_uint(v[i]) & 0xffff0000u;
-    const float r = v[i] - __uint_as_float(hb);
-    const bf16 mid = (bf16)r;
-    p[0][i] = __builtin_bit_cast(bf16, (uint16_t)(hb >> 16));
-    p[1][i] = mid;
-    p[2][i] = (bf16)(r - (float)mid);
-  }
-}
-
-// Sum over groups of KL lanes (16, 32 or 64), the same in every lane of the group.
-template <int CTRL>
-__device__ __forceinline__ float dpp_plus(float v) {
-  return v + __builtin_amdgcn_update_dpp(0.f, v, CTRL, 0xF, 0xF, false);
-}
-template <int KL>
-__device__ __forceinline__ float group_sum(float v) {
-  v = dpp_plus<0x128>(v);   // row_ror 8, 4, 2, 1
-  v = dpp_plus<0x124>(v);
-  v = dpp_plus<0x122>(v);
-  v = dpp_plus<0x121>(v);
-  if constexpr (KL >= 32) {
-    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-    v = __uint_as_float(r[0]) + __uint_as_float(r[1]);
-  }
-  if constexpr (KL >= 64) {
-    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-    v = __uint_as_float(r[0]) + __uint_as_float(r[1]);
-  }
-  return v;
-}
-
-// Exact GELU z Phi(z) to FP32 accuracy without branches (a library erf branches on |x|): with
-// e = 2 Phi(-|z|) = 2^-Q(|z|), GELU = z/2 (z < 0 ? e : 2 - e). Q(a) = a P(a), P of degree 9
-// fitted to -log2(2 Phi(-a)) on [0, 9.5] by Lawson's iteratively reweighted least squares,
-// weighted by e (absolute error of e at most 5.3e-9), increasing up to a = 12, where e = 8e-39.
-// Largest error against 64 bits 9.4e-8 |z| (the erf form with an exact erf: 1.02e-7 |z|). 16
-// vector instructions, one of them the exponential.
-__device__ __forceinline__ float gelu_f32(float z) {
-  constexpr float c[10] = {1.15110445022583f,       0.4592188000679016f,     0.05244622007012367f,
-                           -0.006953386589884758f,  6.749427029717481e-06f,  0.0002739334013313055f,
-                           -7.332905806833878e-05f, 1.0027591997641139e-05f, -7.206676286841684e-07f,
-                           2.1236523650713934e-08f};
-  const float a = fminf(fabsf(z), 12.0f);
-  float q = c[9];
-#pragma unroll
-  for (int k = 8; k >= 0; --k) q = fmaf(q, a, c[k]);
-  const float e = __builtin_amdgcn_exp2f(-(q * a));
-  return (0.5f * z) * (z < 0.f ? e : 2.0f - e);
-}
 
 }  // namespace
 
@@ -201,14 +143,7 @@ __device__ __forceinline__ void split_body(const SplitArgs& p) {
     const float4 s4 = in_row ? *(const float4*)(p.s + c4) : make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
     for (int i = 0; i < NI; ++i) {
-      const float mu = group_sum<KL>((v[i].x + v[i].y) + (v[i].z + v[i].w)) * inv;
-      const float dx = v[i].x - mu, dy = v[i].y - mu, dz = v[i].z - mu, dw = v[i].w - mu;
-      const float q = in_row ? fmaf(dw, dw, fmaf(dz, dz, fmaf(dy, dy, dx * dx))) : 0.f;
-      const float rs = rsqrtf(group_sum<KL>(q) * inv + kLnEps);
-      v[i].x = fmaf(dx * rs, g4.x, s4.x);
-      v[i].y = fmaf(dy * rs, g4.y, s4.y);
-      v[i].z = fmaf(dz * rs, g4.z, s4.z);
-      v[i].w = fmaf(dw * rs, g4.w, s4.w);
+      v[i] = layer_norm4<KL>(v[i], g4, s4, inv, in_row);
     }
   }
 #pragma unroll

@@ -273,6 +273,29 @@ constexpr int kSplitCands = 4;
 bool split_tile(int cand, int64_t Mp, int N, int* rows, int* parts);
 hipError_t launch_split_gemm(hipStream_t st, int cls, int64_t Mp, SplitArgs p, int cand = -1);
 
+// FP32 block segments at width 64 with a 4x MLP (block_split.hip), bitwise the separate products:
+// H += att W_o + b_o, qc = LN(H; g, s) W_qc + b_qc; or H += att W_o + b_o (the cross output
+// projection), H += MLP(LN(H; g, s)) and, with Wf_qkv, qkv = LN(H; gn, sn) W_qkv + b_qkv. Rows are
+// row-major, Mp a multiple of 32.
+struct SplitBlockArgs {
+  const float* att;            // [Mp, 64]
+  float* H;                    // [Mp, 64]
+  const u32x4* Wf_o;
+  const float *b_o, *g, *s;
+  const u32x4* Wf_qc;
+  const float* b_qc;
+  float* qc;                   // [Mp, 64]
+  const u32x4* Wf_up;
+  const float* b_up;
+  const u32x4* Wf_dn;
+  const float *b_dn, *gn, *sn;
+  const u32x4* Wf_qkv;
+  const float* b_qkv;
+  float* qkv;                  // [Mp, 192]
+};
+hipError_t launch_split_oqc(hipStream_t st, int64_t Mp, const SplitBlockArgs& a);
+hipError_t launch_split_mlp(hipStream_t st, int64_t Mp, const SplitBlockArgs& a);
+
 // Fused BF16 block kernels for d = 256 with 8 heads of 32 and a 4x MLP (block_bf16.hip):
 // their Q/K/V and cross-query stores are 8 head-major planes of width 32. Row counts Mp are
 // multiples of 128; weights are in the fragment layout of launch_pack_frag.

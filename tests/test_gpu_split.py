@@ -98,3 +98,26 @@ def test_powers_of_two_move_exactly():
     m = fmd.Model(cfg, scaled)
     assert np.array_equal(_velocity(torch, m, off, feat, x, t), v)
     m.close()
+
+
+@pytest.mark.parametrize("blocks,heads", [(1, 4), (2, 4), (3, 1)])
+def test_chained_blocks_match_the_separate_products(blocks, heads):
+    """Width 64 runs a block's six products as two kernels, the separate ones while per-kernel
+    timing is on: the same bits, for single evaluations and sampler stages, at the edges of the
+    32-row tiles and in a call that fills the chip."""
+    torch, fmd = torch_cuda(), fmd_lib()
+    cfg, flat, off, feat, x, t = _case(64, heads, blocks)
+    rng = np.random.default_rng(3)
+    m = fmd.Model(cfg, flat)
+    for n in ([1], [31], [32], [33], SIZES, list(rng.integers(20, 201, size=160))):
+        o = np.r_[0, np.cumsum(n)].astype(np.int64)
+        f = torch.from_numpy(events.particles(rng, int(o[-1]))).cuda()
+        xs = torch.from_numpy(rng.standard_normal((int(o[-1]), 9)).astype(np.float32)).cuda()
+        te = torch.from_numpy(rng.uniform(0, 1, len(n)).astype(np.float32)).cuda()
+        got = []
+        for timing in (True, False):
+            m.timing_enable(timing)
+            got.append((m.velocity(o, f, xs, te),
+                        m.simulate_from_state(o, f, xs, configs.Schedule(configs.RK4, 2))))
+        assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1]), int(o[-1])
+    m.close()
