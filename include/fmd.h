@@ -293,7 +293,9 @@ enum { FMD_K_GEMM_QKV = 0, FMD_K_GEMM_PROJ = 1, FMD_K_GEMM_QC = 2, FMD_K_GEMM_UP
        FMD_K_ATTN_CROSS = 8, FMD_K_OTHER = 9, FMD_K_COUNT = 10 };
 
 /* Turns on (1) or off (0) per-launch timing of the kernel classes above and clears the
- * counters. Timing brackets each launch with events and adds a little host overhead. */
+ * counters. Timing brackets each launch with events and adds a little host overhead. An FP32
+ * model of width 64 then runs its blocks as the classes' separate kernels, which it otherwise
+ * chains in two; the results are the same bits. */
 int fmd_timing_enable(fmd_model* m, int32_t enable);
 
 /* Reads the counters of one class: total device milliseconds, number of launches, and the

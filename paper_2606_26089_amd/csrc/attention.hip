@@ -1,11 +1,11 @@
 // Masked multi-head attention over ragged CSR events on gfx950 matrix cores.
 //
-// The general kernel (heads of 16 and 64; heads of 32 have their own below): each workgroup takes one (event, 64-query tile) work item for one head. Each of its four
-// waves owns 16 queries. Keys and values of the event stream through LDS in chunks of 64
-// keys, with an online (running max / running sum) softmax. Keys of other events are
-// never touched. Slots past the end of the event are excluded by a select before the
-// exponential, and their K and V rows are zero-filled in LDS, so garbage cannot reach
-// the result.
+// The general kernel (heads of 16 and 64; heads of 32 have their own below): each workgroup
+// takes one (event, 64-query tile) work item for one head. Each of its four waves owns 16
+// queries. Keys and values of the event stream through LDS in chunks of 64 keys, with an
+// online (running max / running sum) softmax. Keys of other events are never touched. Slots
+// past the end of the event are excluded by a select before the exponential, and their K and
+// V rows are zero-filled in LDS, so garbage cannot reach the result.
 //
 // The scores are formed transposed, S^T = K Q^T, on 16 x 16 MFMA tiles. Lane l then
 // holds query l%16 and keys 4(l/16) + r, so a query's statistics need only two

@@ -7,7 +7,9 @@
 // [32w, 32w + 32), so each wave has a quarter (TM = 1) of the chain and the two waves of a SIMD
 // hide each other's waits. What bounds it then is the weight stream: a segment's weights pass
 // through one CU at about 64 bytes per cycle, so every product phase is 16 fragments per wave,
-// all 16 in flight (each consumed fragment is replaced by the next phase's at once).
+// all 16 in flight (each consumed fragment is replaced by the next phase's at once). Per launch
+// with 105 rows: MLP 33 -> 21 us (10 of them the stream), OQC 10.8 -> 6.5, embedding + QKV 15 ->
+// 9.5; an evaluation of 4,103 rows 406 -> 295 us, of 14,276 (64-row tiles) 510 -> 465.
 //
 // LayerNorm: the rows go through LDS once in FP32 and 16 lanes take each row, lane j the
 // columns 16 k + j. Sums are formed in the order of the throughput kernels (partial sums over
