@@ -277,7 +277,8 @@ template <typename F>
 float time_best_us(hipStream_t st, hipEvent_t e0, hipEvent_t e1, F&& launch, int reps = 3);
 template <typename T>
 hipError_t launch_self_attention(fmd_model* m, const Call& c, int qt, int64_t items,
-                                 const AttnBins& bins, const AttnItem* work);
+                                 const AttnBins& bins, const AttnItem* work,
+                                 L2Touch touch = L2Touch{nullptr, 0, 0});
 
 // Uploads offsets and the attention work lists; runs the token map. With reco_off (host,
 // [E + 1], already checked) the reco slots of event e are reco_off[e] .. reco_off[e + 1]
@@ -767,7 +768,7 @@ int autotune(fmd_model* m, Call& c) {
 // it, row-major [Tp][d] otherwise.
 template <typename T>
 hipError_t launch_self_attention(fmd_model* m, const Call& c, int qt, int64_t items,
-                                 const AttnBins& bins, const AttnItem* work) {
+                                 const AttnBins& bins, const AttnItem* work, L2Touch touch) {
   Workspace& w = m->ws;
   const int d = m->cfg.d_model, Hh = m->cfg.n_heads, dh = d / Hh;
   const size_t es = sizeof(T);
@@ -780,7 +781,7 @@ hipError_t launch_self_attention(fmd_model* m, const Call& c, int qt, int64_t it
     const int64_t pl = c.Tp * dh;
     return launch_attention<T>(c.st, false, dh, Hh, qt, items, bins, work, (const T*)qkv, dh, pl,
                                (const T*)(qkv + Hh * pl * es), (const T*)(qkv + 2 * Hh * pl * es),
-                               dh, pl, (T*)w.att, ldo, hso);
+                               dh, pl, (T*)w.att, ldo, hso, touch);
   }
   return launch_attention<T>(c.st, false, dh, Hh, qt, items, bins, work, (const T*)qkv, 3 * d, dh,
                              (const T*)(qkv + d * es), (const T*)(qkv + 2 * d * es), 3 * d, dh,
@@ -908,6 +909,15 @@ int net_forward(fmd_model* m, Call& c, const float* t_ev) {
   const double dd = (double)d;
   const int sr = small_rows(c), sr_qkv = small_rows_for(m, c, TS_FQKV),
             sr_oqc = small_rows_for(m, c, TS_FOQC);
+  // Very few rows: each attention launch reads the weights of the kernels up to the next one into L2
+  // (a block's fragments lie as W_qkv, W_o, W_qc, W_oc, W_up, W_dn, the next block's after them).
+  // At most four tiles per XCD: more of them share each line's fetch, and attention needs the CUs
+  // (us an evaluation without and with: 105 rows 253 and 240, 689 rows 265 and 253, 1,142 rows 268
+  // and 268, 4,103 rows 281 and 286).
+  constexpr int kBlocks = FMD_FUSED_QKV | FMD_FUSED_OQC | FMD_FUSED_MLP;
+  constexpr int64_t kWarmRows = 4 * 8 * 32;
+  const bool warm = (fz & kBlocks) == kBlocks && sr == 32 && m->f8.empty() &&
+                    (c.tiles ? c.n_tiles * 64 : c.Tp) <= kWarmRows;
   bool qkv_ready = false;   // the previous block's MLP kernel formed this block's [Q|K|V]
   for (int l = 0; l < L; ++l) {
     const DevBlock& B = m->blk[l];
@@ -940,7 +950,8 @@ int net_forward(fmd_model* m, Call& c, const float* t_ev) {
       }));
     }
     FMD_TRY(timed(m, c.st, FMD_K_ATTN_SELF, 4.0 * c.sum_n2 * d, Td * 4 * d * es, [&] {
-      return launch_self_attention<T>(m, c, c.qt, c.items, c.bins, w.work);
+      return launch_self_attention<T>(m, c, c.qt, c.items, c.bins, w.work,
+                                      warm ? L2Touch{B.Fo, (uint32_t)(2 * d * d * es), 0} : L2Touch{});
     }));
     if (fz & FMD_FUSED_OQC) {
       FMD_TRY(timed(m, c.st, FMD_K_FUSED_OQC, 2.0 * Td * dd * dd * 2,
@@ -977,7 +988,9 @@ int net_forward(fmd_model* m, Call& c, const float* t_ev) {
         const char* kb = kv + (size_t)l * 2 * Hh * pl * es;
         return launch_attention<T>(c.st, true, dh, Hh, c.qt, c.items_x, c.bins_x, w.work + c.work_x, (const T*)w.qc,
                                    hm ? dh : d, hm ? c.Tp * dh : dh, (const T*)kb,
-                                   (const T*)(kb + Hh * pl * es), dh, pl, (T*)w.att, ldo, hso);
+                                   (const T*)(kb + Hh * pl * es), dh, pl, (T*)w.att, ldo, hso,
+                                   warm ? L2Touch{B.Foc, (uint32_t)((l + 1 < L ? 12 : 9) * d * d * es), 0}
+                                        : L2Touch{});
       }
       return launch_attention<T>(c.st, true, dh, Hh, c.qt, c.items_x, c.bins_x, w.work + c.work_x, (const T*)w.qc,
                                  hm ? dh : d, hm ? c.Tp * dh : dh, (const T*)(kv + o),

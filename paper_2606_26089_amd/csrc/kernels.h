@@ -149,6 +149,14 @@ int64_t build_attention_work_kv(const int64_t* q_off, const int64_t* kv_start,
                                 const int64_t* kv_len, const int64_t* ids, int64_t n, int qt,
                                 AttnItem* items, AttnBins* bins);
 
+// Weights that the kernels after an attention launch will stream, read into every XCD's L2 beside
+// it (BF16 with dh 32; bytes 0: none).
+struct L2Touch {
+  const void* p;
+  uint32_t bytes;
+  uint32_t first;   // first workgroup that does so (set by the launcher)
+};
+
 // Masked multi-head attention over ragged events, one work item per (event, query tile).
 // Element (row, head, dim) of Q sits at Q[row * ldq + head * hsq + dim], of K / V at
 // [row * ldkv + head * hskv + dim], of O at [row * ldo + head * hso + dim]: hs = dh for
@@ -158,7 +166,8 @@ template <typename T>
 hipError_t launch_attention(hipStream_t st, bool cross, int dh, int n_heads, int qt,
                             int64_t n_items, const AttnBins& bins,
                             const AttnItem* work, const T* Q, int ldq, int64_t hsq, const T* K,
-                            const T* V, int ldkv, int64_t hskv, T* O, int ldo, int64_t hso);
+                            const T* V, int ldkv, int64_t hskv, T* O, int ldo, int64_t hso,
+                            L2Touch touch = L2Touch{nullptr, 0, 0});
 
 hipError_t launch_token_map(hipStream_t st, const int64_t* off, int64_t E, int64_t T,
                             int32_t* tok_event);
