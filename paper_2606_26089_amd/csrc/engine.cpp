@@ -174,6 +174,16 @@ int ensure_ws_alloc(fmd_model* m, int64_t T, int64_t E, int64_t items, bool* gre
   return FMD_OK;
 }
 
+// Room for n entries in the device stage table. The server's iterations use the same table, so
+// every growth goes through here: a captured stage graph holds its address.
+int ensure_desc(Workspace& w, int64_t n) {
+  if (n <= w.cap_desc) return FMD_OK;
+  w.generation++;
+  FMD_TRY(grow(w.desc, (size_t)n * sizeof(StageDesc)));   // (waits for the device to go idle)
+  w.cap_desc = (int)n;
+  return FMD_OK;
+}
+
 // Switches to the other pinned staging set and makes it writable (waits for the uploads of
 // the call that used it last) with room for E events and `items` work items.
 int next_host_stage(Workspace& w, int64_t E, int64_t items) {
@@ -1106,12 +1116,7 @@ int begin_stages(fmd_model* m, Call& c, const fmd_schedule* s, float* out, int* 
   const int K = s->n_steps, S = stages_per_step(s->scheme);
   const int n = K * S;
   const int d = m->cfg.d_model;   // 0: the linear field, which has no time embedding
-  if (n > w.cap_desc) {
-    FMD_TRY(grow(w.desc, (size_t)n * sizeof(StageDesc)));
-    HIP_TRY(hipDeviceSynchronize());
-    w.cap_desc = n;
-    w.generation++;
-  }
+  FMD_TRY(ensure_desc(w, n));
   if (n > w.cap_tstage && d > 0) {
     FMD_TRY(grow(w.tstage, (size_t)n * d * 4));
     w.cap_tstage = n;

@@ -315,10 +315,7 @@ int iterate(fmd_server* S, int k, std::vector<Req*>& finished) {
                                 (int64_t)real.size(), qt, g.work + items, &bins_x) != items)
       return fail(FMD_E_INVALID, "token rows beyond 2^31");
   }
-  if (E > w.cap_desc) {   // (the reallocation waits for the device to go idle)
-    FMD_TRY(grow(w.desc, (size_t)E * sizeof(StageDesc)));
-    w.cap_desc = (int)E;
-  }
+  FMD_TRY(ensure_desc(w, E));
   HIP_TRY(hipMemcpyAsync(w.off, g.off, (size_t)(E + 1) * 8, hipMemcpyHostToDevice, S->st));
   HIP_TRY(hipMemcpyAsync(w.work, g.work, (size_t)(2 * items) * sizeof(AttnItem), hipMemcpyHostToDevice, S->st));
   HIP_TRY(hipMemcpyAsync(w.desc, g.desc, (size_t)E * sizeof(StageDesc), hipMemcpyHostToDevice, S->st));

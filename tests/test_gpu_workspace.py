@@ -1,0 +1,44 @@
+"""The workspace that a model's own calls, its server and its captured stage graphs share (GPU):
+buffers that move under a cached graph."""
+
+import numpy as np
+import pytest
+
+from tests._gpu import fmd_lib, torch_cuda
+from workload import configs, events, params
+
+pytestmark = pytest.mark.gpu
+
+CFG = configs.SMALL_MODEL
+
+
+def _events(torch, sizes, seed=0):
+    off = np.r_[0, np.cumsum(sizes)].astype(np.int64)
+    return off, torch.from_numpy(events.particles(np.random.default_rng(seed), int(off[-1]))).cuda()
+
+
+def test_a_server_that_grows_the_stage_table_does_not_leave_a_graph_behind():
+    """The server's iterations hold one stage-table entry per event. One with more events than
+    the stages of the model's last call moves the table, and nothing else here: the pool, the
+    events and the work items fit the workspace of that call, and nothing is tuned. The same
+    call afterwards has the key of the graph captured before."""
+    torch, fmd = torch_cuda(), fmd_lib()
+    m = fmd.Model(CFG, params.draw(CFG, 5, perturbed=True))
+    m.autotune_enable(False)
+    off, feat = _events(torch, [40] * 200)
+    sched = configs.Schedule(configs.EULER, 20)
+    first = m.simulate(off, feat, 3, sched)
+    probe = fmd.Server(m, hbm_budget_bytes=4 << 20)
+    bpt = probe.info()["bytes_per_token"]
+    probe.close()
+    req_off, req_feat = _events(torch, [20] * 60, seed=1)       # 60 entries, more than 20
+    short = configs.Schedule(configs.EULER, 3)
+    srv = fmd.Server(m, hbm_budget_bytes=bpt * (2048 + 256 + 8))
+    assert srv.info()["pool_tokens"] + 256 <= 8000
+    got, _ = srv.wait(srv.submit(req_off, req_feat.cpu().numpy(), 9, short))
+    srv.close()
+    again = m.simulate(off, feat, 3, sched)                     # another output buffer
+    assert torch.equal(first, again)
+    assert np.array_equal(got, m.simulate(req_off, req_feat, 9, short).cpu().numpy())
+    assert torch.equal(first, m.simulate(off, feat, 3, sched))
+    m.close()
