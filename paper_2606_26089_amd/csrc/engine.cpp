@@ -127,6 +127,8 @@ int ensure_ws(fmd_model* m, int64_t T, int64_t E, int64_t items) {
   return FMD_OK;
 }
 
+// A capacity is zero while its buffers are exchanged: after a growth that failed half way (device
+// memory is short) they are partly gone, and the next call has to grow them whatever its size.
 int ensure_ws_alloc(fmd_model* m, int64_t T, int64_t E, int64_t items, bool* grew) {
   Workspace& w = m->ws;
   const fmd_model_config& c = m->cfg;
@@ -136,6 +138,7 @@ int ensure_ws_alloc(fmd_model* m, int64_t T, int64_t E, int64_t items, bool* gre
   if (Tp > w.cap_tok) {
     const int64_t cap = std::max(Tp, round_up(w.cap_tok + w.cap_tok / 4, kGemmBM));
     const size_t st = (size_t)cap * kStateLd * 4;
+    w.cap_tok = 0;
     FMD_TRY(grow(w.x, st));
     FMD_TRY(grow(w.acc, st));
     FMD_TRY(grow(w.xs, st));
@@ -159,6 +162,7 @@ int ensure_ws_alloc(fmd_model* m, int64_t T, int64_t E, int64_t items, bool* gre
   }
   if (E + 1 > w.cap_ev) {
     const int64_t cap = std::max(E + 1, w.cap_ev + w.cap_ev / 4);
+    w.cap_ev = 0;
     FMD_TRY(grow(w.off, (size_t)cap * 8));
     FMD_TRY(grow(w.tev, (size_t)cap * 4));
     FMD_TRY(grow(w.temb, (size_t)cap * d * 4));
@@ -167,6 +171,7 @@ int ensure_ws_alloc(fmd_model* m, int64_t T, int64_t E, int64_t items, bool* gre
   }
   if (items > w.cap_items) {
     const int64_t cap = std::max(items, w.cap_items + w.cap_items / 4);
+    w.cap_items = 0;
     FMD_TRY(grow(w.work, (size_t)cap * sizeof(AttnItem)));
     w.cap_items = cap;
     *grew = true;
@@ -179,6 +184,7 @@ int ensure_ws_alloc(fmd_model* m, int64_t T, int64_t E, int64_t items, bool* gre
 int ensure_desc(Workspace& w, int64_t n) {
   if (n <= w.cap_desc) return FMD_OK;
   w.generation++;
+  w.cap_desc = 0;
   FMD_TRY(grow(w.desc, (size_t)n * sizeof(StageDesc)));   // (waits for the device to go idle)
   w.cap_desc = (int)n;
   return FMD_OK;
@@ -195,10 +201,12 @@ int next_host_stage(Workspace& w, int64_t E, int64_t items) {
     h.live = false;
   }
   if (E + 1 > h.cap_ev) {
+    h.cap_ev = 0;
     FMD_TRY(grow_host(h.off, (size_t)(E + 1) * 8));
     h.cap_ev = E + 1;
   }
   if (items > h.cap_items) {
+    h.cap_items = 0;
     FMD_TRY(grow_host(h.work, (size_t)std::max<int64_t>(items, 1) * sizeof(AttnItem)));
     h.cap_items = std::max<int64_t>(items, 1);
   }
@@ -1118,11 +1126,13 @@ int begin_stages(fmd_model* m, Call& c, const fmd_schedule* s, float* out, int* 
   const int d = m->cfg.d_model;   // 0: the linear field, which has no time embedding
   FMD_TRY(ensure_desc(w, n));
   if (n > w.cap_tstage && d > 0) {
+    w.cap_tstage = 0;
     FMD_TRY(grow(w.tstage, (size_t)n * d * 4));
     w.cap_tstage = n;
     w.generation++;
   }
   if (n > hs.cap_desc) {
+    hs.cap_desc = 0;
     FMD_TRY(grow_host(hs.desc, (size_t)n * sizeof(StageDesc)));
     hs.cap_desc = n;
   }
@@ -1573,7 +1583,7 @@ int fmd_linear_field_create(double alpha, double beta, fmd_model** out) {
 int fmd_model_destroy(fmd_model* m) {
   if (!m) return FMD_OK;
   if (m->server) return fail(FMD_E_STATE, "destroy the model's server first");
-  if (m->kind == 1 && m->ws.cap_tok == 0 && m->ev_pool.empty() && m->trec.empty()) {
+  if (m->kind == 1 && !m->pstream && m->ev_pool.empty() && m->trec.empty()) {
     delete m;   // never touched a device
     return FMD_OK;
   }

@@ -42,3 +42,24 @@ def test_a_server_that_grows_the_stage_table_does_not_leave_a_graph_behind():
     assert np.array_equal(got, m.simulate(req_off, req_feat, 9, short).cpu().numpy())
     assert torch.equal(first, m.simulate(off, feat, 3, sched))
     m.close()
+
+
+@pytest.mark.parametrize("cfg", [CFG, configs.BASE_MODEL.with_precision(configs.BF16)],
+                         ids=["small-fp32", "base-bf16"])
+def test_a_workspace_that_could_not_grow_is_grown_by_the_next_call(cfg):
+    """A server whose pool no device can hold is refused with the workspace half exchanged (the
+    first buffer is already given up). The model's next calls get their buffers back."""
+    torch, fmd = torch_cuda(), fmd_lib()
+    m = fmd.Model(cfg, params.draw(cfg, 5, perturbed=True))
+    off, feat = _events(torch, [30] * 20)
+    sched = configs.Schedule(configs.RK4, 4)
+    first = m.simulate(off, feat, 3, sched)
+    t = torch.full((20,), 0.25, device="cuda")
+    v = m.velocity(off, feat, first, t)
+    torch.cuda.synchronize()
+    with pytest.raises(fmd.FmdError) as e:
+        fmd.Server(m, hbm_budget_bytes=1 << 48)       # its ODE state alone is above 1 TiB
+    assert e.value.status == fmd.E_NOMEM
+    assert torch.equal(m.simulate(off, feat, 3, sched), first)
+    assert torch.equal(m.velocity(off, feat, first, t), v)
+    m.close()
