@@ -1161,22 +1161,26 @@ int run_stage(fmd_model* m, Call& c, int ldo) {
   return c.head_done ? FMD_OK : head(m, c, false, 0, nullptr, ldo);
 }
 
-// All stages of a call. With graphs on, kGraphStages stages are captured into a HIP graph
-// (kernels read time, mode, step and output through the stage table and its device counters) and
-// the graph is replayed for the whole groups, the rest launched one by one; the executable graph
-// is kept for later calls with the same shapes and workspace. The start of a graph costs 8 us on
-// the device (one stage a graph: 375 us per evaluation of one event, 8 of them that gap), a
-// captured kernel about 2 us on the host once, so four stages pay from some 16 stages on.
+// All stages of a call. With graphs on, one or four stages are captured into a HIP graph (kernels
+// read time, mode, step and output through the stage table and its device counters) and the graph
+// is replayed for the whole groups, the rest launched one by one; an executable graph of each
+// length is kept for later calls with the same shapes and workspace. The start of a graph costs
+// 8 us on the device (one stage a graph: 375 us per evaluation of one event, 8 of them that gap),
+// which four stages a graph save three times of four, against a longer capture once per shape
+// (d = 256, 6 blocks: 0.3 ms against 0.1; d = 64, 2 blocks: 0.13 against 0.09). From 16 stages on
+// a repeated shape gains 0.1 ms and more a call; one that is never seen again breaks even at some
+// 35 stages (d = 256) or 8 (d = 64).
 template <typename T>
 int run_stages(fmd_model* m, Call& c, int n_stages, int ldo) {
   const int per = n_stages >= 16 ? 4 : 1;
   int done = 0;
   if (m->graphs && !m->timing) {
-    const GraphKey key{c.Tp,   c.T,       c.E,    c.items,  ldo,      per, m->ws.generation,
+    const GraphKey key{c.Tp,   c.T,       c.E,    c.items,  ldo,  m->ws.generation,
                        m->tune_gen, c.bins, c.items_x, c.work_x, c.bins_x, c.Tt};
-    if (!m->gexec || !(key == m->gkey)) {
-      if (m->gexec) (void)hipGraphExecDestroy(m->gexec);
-      m->gexec = nullptr;
+    StageGraph& sg = m->graph[per == 4];
+    if (!sg.exec || !(key == sg.key)) {
+      if (sg.exec) (void)hipGraphExecDestroy(sg.exec);
+      sg.exec = nullptr;
       HIP_TRY(hipStreamBeginCapture(c.st, hipStreamCaptureModeThreadLocal));
       int st = FMD_OK;
       for (int i = 0; i < per && st == FMD_OK; ++i) st = run_stage<T>(m, c, ldo);
@@ -1187,15 +1191,15 @@ int run_stages(fmd_model* m, Call& c, int n_stages, int ldo) {
         return st;
       }
       if (ec != hipSuccess) return fail(FMD_E_DEVICE, "stage capture failed: %s", hipGetErrorString(ec));
-      const hipError_t ei = hipGraphInstantiate(&m->gexec, g, nullptr, nullptr, 0);
+      const hipError_t ei = hipGraphInstantiate(&sg.exec, g, nullptr, nullptr, 0);
       (void)hipGraphDestroy(g);
       if (ei != hipSuccess) {
-        m->gexec = nullptr;
+        sg.exec = nullptr;
         return fail(FMD_E_DEVICE, "graph instantiation failed: %s", hipGetErrorString(ei));
       }
-      m->gkey = key;
+      sg.key = key;
     }
-    for (; done + per <= n_stages; done += per) HIP_TRY(hipGraphLaunch(m->gexec, c.st));
+    for (; done + per <= n_stages; done += per) HIP_TRY(hipGraphLaunch(sg.exec, c.st));
   }
   for (; done < n_stages; ++done) FMD_TRY(run_stage<T>(m, c, ldo));
   return FMD_OK;
@@ -1591,7 +1595,8 @@ int fmd_model_destroy(fmd_model* m) {
   (void)hipDeviceSynchronize();
   flush_timing(m);
   for (hipEvent_t e : m->ev_pool) (void)hipEventDestroy(e);
-  if (m->gexec) (void)hipGraphExecDestroy(m->gexec);
+  for (StageGraph& sg : m->graph)
+    if (sg.exec) (void)hipGraphExecDestroy(sg.exec);
   if (m->pstream) (void)hipStreamDestroy(m->pstream);
   if (m->ev_in) (void)hipEventDestroy(m->ev_in);
   if (m->ev_out) (void)hipEventDestroy(m->ev_out);

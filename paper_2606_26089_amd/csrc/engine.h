@@ -65,7 +65,7 @@ struct Workspace {
 // What a captured stage graph depends on besides buffer contents.
 struct GraphKey {
   int64_t Tp, T, E, items;
-  int ldo, stages;           // stages captured in one graph
+  int ldo;
   uint64_t ws_gen, tune_gen;
   AttnBins bins;  // kernel arguments and grid size of the attention launches
   int64_t items_x, work_x;   // cross-attention list: size and offset in the work buffer
@@ -73,11 +73,15 @@ struct GraphKey {
   int64_t Tt;                // truth rows (the reco side may differ in size)
   bool operator==(const GraphKey& o) const {
     return Tp == o.Tp && T == o.T && E == o.E && items == o.items && ldo == o.ldo &&
-           stages == o.stages && ws_gen == o.ws_gen && tune_gen == o.tune_gen &&
+           ws_gen == o.ws_gen && tune_gen == o.tune_gen &&
            std::memcmp(&bins, &o.bins, sizeof(AttnBins)) == 0 && items_x == o.items_x &&
            work_x == o.work_x && std::memcmp(&bins_x, &o.bins_x, sizeof(AttnBins)) == 0 &&
            Tt == o.Tt;
   }
+};
+struct StageGraph {
+  hipGraphExec_t exec = nullptr;
+  GraphKey key{};
 };
 
 // Sites the autotuner chooses a variant for: the GEMM sites (a tiling of the matrix-core
@@ -126,8 +130,7 @@ struct fmd_model {
   int graphs = 1;                  // 1: capture one ODE stage as a HIP graph and replay it
   hipStream_t pstream = nullptr;   // private stream of the model (captured, non-blocking)
   hipEvent_t ev_in = nullptr, ev_out = nullptr;
-  hipGraphExec_t gexec = nullptr;
-  fmd::GraphKey gkey{};
+  fmd::StageGraph graph[2];        // captured stages of the last shape: one, and four
   fmd_server* server = nullptr;    // attached server (the model's own calls are refused)
   int8_t tune[fmd::TS_COUNT][fmd::kTuneBuckets];   // chosen tiling, -1 = not tuned yet
   bool tune_fixed[fmd::TS_COUNT][fmd::kTuneBuckets] = {};   // set by the caller, not timed
