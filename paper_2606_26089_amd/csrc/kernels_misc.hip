@@ -763,10 +763,31 @@ __device__ __forceinline__ bool obs_in_cone(float eta_i, float phi_i, float eta_
   return deta * deta + dphi * dphi < 0.16f;
 }
 
+// Sum over the wave, pairs across lane bits 5 to 0 in turn: half and row swaps, then rotations in
+// the 16-lane rows (after the bits above, lanes that differ only in those hold the same value, so
+// a rotation by 2^b serves as the exchange over bit b). No LDS permutes, which a workgroup of two
+// waves waits for.
+template <int CTRL>
+__device__ __forceinline__ double obs_plus_ror(double v) {
+  const uint64_t u = __builtin_bit_cast(uint64_t, v);
+  const uint32_t lo = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)u, CTRL, 0xF, 0xF, false);
+  const uint32_t hi = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)(u >> 32), CTRL, 0xF, 0xF, false);
+  return v + __builtin_bit_cast(double, (uint64_t)hi << 32 | lo);
+}
+template <typename S>
+__device__ __forceinline__ double obs_plus_swap(double v, S&& swap) {
+  const uint64_t u = __builtin_bit_cast(uint64_t, v);
+  const auto lo = swap((uint32_t)u), hi = swap((uint32_t)(u >> 32));
+  return __builtin_bit_cast(double, (uint64_t)hi[0] << 32 | lo[0]) +
+         __builtin_bit_cast(double, (uint64_t)hi[1] << 32 | lo[1]);
+}
 __device__ __forceinline__ double obs_wave_sum(double v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, kWave);
-  return v;
+  v = obs_plus_swap(v, [](uint32_t x) { return __builtin_amdgcn_permlane32_swap(x, x, false, false); });
+  v = obs_plus_swap(v, [](uint32_t x) { return __builtin_amdgcn_permlane16_swap(x, x, false, false); });
+  v = obs_plus_ror<0x128>(v);   // row_ror 8, 4, 2, 1
+  v = obs_plus_ror<0x124>(v);
+  v = obs_plus_ror<0x122>(v);
+  return obs_plus_ror<0x121>(v);
 }
 
 struct ObsItem {       // a decoded particle, 16 bytes
@@ -774,6 +795,20 @@ struct ObsItem {       // a decoded particle, 16 bytes
   float eta, phi;
 };
 constexpr int kObsParts = 4;          // threads per lepton
+// Running sums of an event: particle i adds to number i % 256, in order of i, whatever the number
+// of threads, so that an event's bits do not depend on the call around it.
+constexpr int kObsSums = 256;
+struct ObsSums {
+  double h = 0.0, px = 0.0, py = 0.0;
+  __device__ __forceinline__ void add(double pt, double cs, double sn) {
+    h += pt;
+    px = fma(pt, cs, px);
+    py = fma(pt, sn, py);
+  }
+};
+struct ObsTerm {
+  double pt, cs, sn;
+};
 }  // namespace
 
 template <int NT>
@@ -782,16 +817,22 @@ __global__ __launch_bounds__(NT) void k_event_observables(const float* __restric
                                                           float* __restrict__ ht,
                                                           float* __restrict__ met,
                                                           float* __restrict__ iso) {
-  constexpr int NW = NT / 64;
   __shared__ ObsItem item[kObsTile];
+  __shared__ ObsTerm upper[NT > kObsSums ? NT - kObsSums : 1];   // terms of the threads past the sums
   __shared__ uint16_t lep[kObsTile];             // the tile's leptons, in any order
   __shared__ int n_lep;
-  __shared__ double red[NW][3];
+  __shared__ double red[kObsSums / 64][3];
   const int e = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int64_t a = off[e], n = off[e + 1] - a;
   const bool one_tile = n <= kObsTile;
   auto decode = [&](const float* f) { return ObsItem{10.0 * exp((double)f[0]), f[1], f[2]}; };
-  double h = 0.0, px = 0.0, py = 0.0;
+  ObsSums sums;
+  // the sum of running sums 64 w to 64 w + 63
+  auto reduce = [&](int w) {
+    const double h = obs_wave_sum(sums.h), px = obs_wave_sum(sums.px), py = obs_wave_sum(sums.py);
+    if (lane == 0) red[w][0] = h, red[w][1] = px, red[w][2] = py;
+  };
+  if (tid < kObsSums / 64 * 3) red[tid / 3][tid % 3] = 0.0;
   for (int64_t i0 = 0; i0 < n; i0 += kObsTile) {
     const int nt = (int)min<int64_t>(kObsTile, n - i0);
     if (i0) __syncthreads();                     // the tile before is consumed
@@ -805,9 +846,10 @@ __global__ __launch_bounds__(NT) void k_event_observables(const float* __restric
         const ObsItem it = decode(f);
         double sn, cs;
         sincos((double)it.phi, &sn, &cs);
-        h += it.pt;
-        px += it.pt * cs;
-        py += it.pt * sn;
+        if (NT <= kObsSums || tid < kObsSums)
+          sums.add(it.pt, cs, sn);
+        else
+          upper[tid - kObsSums] = ObsTerm{it.pt, cs, sn};
         item[i] = it;
         const int cl = obs_class(f);
         is_lep = cl == 1 || cl == 2;             // electron, muon
@@ -819,6 +861,17 @@ __global__ __launch_bounds__(NT) void k_event_observables(const float* __restric
         if (lane == 0) base = atomicAdd(&n_lep, __popcll(bal));
         base = __shfl(base, 0, kWave);
         if (is_lep) lep[base + __popcll(bal & (lane ? ~0ull >> (64 - lane) : 0ull))] = (uint16_t)i;
+      }
+      if constexpr (NT < kObsSums) {             // (events of up to 256: one term a running sum)
+        if (c + wave * 64 < nt) reduce(c / 64 + wave);
+        sums = ObsSums{};
+      }
+      if constexpr (NT > kObsSums) {
+        static_assert(NT == 2 * kObsSums, "one upper term per running sum");
+        __syncthreads();
+        if (tid < kObsSums && c + kObsSums + tid < nt)
+          sums.add(upper[tid].pt, upper[tid].cs, upper[tid].sn);
+        __syncthreads();                         // the upper terms are rewritten
       }
     }
     __syncthreads();
@@ -851,14 +904,11 @@ __global__ __launch_bounds__(NT) void k_event_observables(const float* __restric
       if (on && part == 0) iso[a + i] = (float)(sum / me.pt);
     }
   }
-  h = obs_wave_sum(h);
-  px = obs_wave_sum(px);
-  py = obs_wave_sum(py);
-  if (lane == 0) red[wave][0] = h, red[wave][1] = px, red[wave][2] = py;
+  if (NT >= kObsSums && wave * 64 < min<int64_t>(n, kObsSums)) reduce(wave);
   __syncthreads();
   if (tid == 0) {
     double t[3] = {0.0, 0.0, 0.0};
-    for (int q = 0; q < NW; ++q)
+    for (int q = 0; q < kObsSums / 64; ++q)
       for (int k = 0; k < 3; ++k) t[k] += red[q][k];
     ht[e] = (float)t[0];
     met[e] = (float)sqrt(t[1] * t[1] + t[2] * t[2]);
@@ -874,7 +924,8 @@ hipError_t launch_event_observables(hipStream_t st, const float* feat, int ldf,
   // than they shorten (4096 events of 20-200: 61 us a call with 128, 63 with 256, 77 with 512;
   // 16,384 heavy-tailed ones of up to 1000: 237, 180 and 230); few events are bound by the
   // longest one (64 heavy-tailed: 92, 60 and 46 us; before, a thread per particle: 88, 545, 238)
-  const bool small = max_n <= 256;
+  // 128 threads hold one term a running sum, so their events have at most 256 particles.
+  const bool small = max_n <= kObsSums;
   const int nt = n_events > 2048 ? (small ? 128 : 256) : n_events > 512 && small ? 256 : 512;
   auto* k = nt == 128   ? k_event_observables<128>
             : nt == 256 ? k_event_observables<256>
