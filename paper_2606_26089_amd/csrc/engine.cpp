@@ -292,7 +292,8 @@ int bucket_of(int64_t Tp);
 int attn_tiles(const fmd_model* m, int* tiles);
 int attn_tile_for(const fmd_model* m, int64_t Tp);
 template <typename F>
-float time_best_us(hipStream_t st, hipEvent_t e0, hipEvent_t e1, F&& launch, int reps = 3);
+float time_best_us(hipStream_t st, hipEvent_t e0, hipEvent_t e1, F&& launch, int reps = 3,
+                   int reps_long = 3);
 template <typename T>
 hipError_t launch_self_attention(fmd_model* m, const Call& c, int qt, int64_t items,
                                  const AttnBins& bins, const AttnItem* work,
@@ -563,16 +564,17 @@ hipError_t slot_gemm(fmd_model* m, Call& c, int slot, int tile, const DevBlock& 
 // k-slice accumulation order per element), so the choice affects speed only. Runs before
 // the first evaluation of a call, while the activation buffers hold nothing that is used
 // later (the residual stream is rebuilt by the next input embedding).
-// Times one launch sequence: 1 warm-up + `reps` timed launches, the best of them, in
-// microseconds (negative if a launch failed).
+// Times one launch sequence: 1 warm-up + `reps` timed launches (`reps_long` of one that takes 50 us
+// or more), the best of them, in microseconds (negative if a launch failed).
 template <typename F>
-float time_best_us(hipStream_t st, hipEvent_t e0, hipEvent_t e1, F&& launch, int reps) {
+float time_best_us(hipStream_t st, hipEvent_t e0, hipEvent_t e1, F&& launch, int reps,
+                   int reps_long) {
   if (launch() != hipSuccess) {
     (void)hipGetLastError();
     return -1.f;
   }
   float best = 1e30f;
-  for (int rep = 0; rep < reps; ++rep) {
+  for (int rep = 0; rep < (best < 50.f ? reps : reps_long); ++rep) {
     float ms = 0.f;
     if (hipEventRecord(e0, st) != hipSuccess || launch() != hipSuccess ||
         hipEventRecord(e1, st) != hipSuccess || hipEventSynchronize(e1) != hipSuccess ||
@@ -686,8 +688,8 @@ SplitArgs split_args(fmd_model* m, const Call& c, int cls, const DevBlock& B, co
 }
 
 // Times the candidates of every site of the split products (see autotune). Launches of a few
-// microseconds are close together and timed no better than that, so each takes the best of
-// eight, and a later candidate has to be clearly faster.
+// microseconds are close together and timed no better than that, so each of them takes the best of
+// eight, and a later candidate has to be clearly faster; longer ones take the best of two.
 int autotune_split(fmd_model* m, Call& c) {
   const int b = bucket_of(c.Tp);
   const DevBlock& B = m->blk[0];
@@ -705,9 +707,13 @@ int autotune_split(fmd_model* m, Call& c) {
     int best = -1, rows = 0, parts = 0;
     float best_us = 0.f;
     for (int k = 0; k < kSplitCands; ++k) {
+      // Columns spread over workgroups: while the 32-row tiles are fewer than two a CU. From there
+      // on it only reads the rows again (51,000 rows, d = 256: up 154 us with 64 rows, 175 with 32,
+      // 162 and 191 spread; 14,000 rows: 44, 48, 47 and 48; 4,100 rows: 39, 25, 18 and 18).
+      if (k >= 2 && c.Tp / 32 >= 2 * 256) continue;
       if (!split_tile(k, c.Tp, p.N, &rows, &parts)) continue;
       const float us = time_best_us(
-          c.st, e0, e1, [&] { return launch_split_gemm(c.st, cls[sl], c.Tp, p, k); }, 8);
+          c.st, e0, e1, [&] { return launch_split_gemm(c.st, cls[sl], c.Tp, p, k); }, 8, 2);
       if (us < 0.f) {
         status = fail(FMD_E_DEVICE, "autotune launch failed");
         break;
