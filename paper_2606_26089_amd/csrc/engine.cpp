@@ -1122,8 +1122,17 @@ StageDesc stage_desc(const fmd_schedule& s, int i) {
   return d;
 }
 
+// Before stage i of n: the time embeddings of the kStageRows stages that start there, if any do.
+int stage_times(fmd_model* m, Call& c, int i, int n) {
+  if (m->kind != 0 || i % kStageRows || i >= n) return FMD_OK;
+  return timed(m, c.st, FMD_K_OTHER, 0, [&] {
+    return launch_time_embed(c.st, nullptr, m->ws.desc + i, std::min(n - i, kStageRows), m->W_time,
+                             m->b_time, m->b_xin, m->cfg.t_embed_dim, m->cfg.d_model, m->ws.tstage);
+  });
+}
+
 // Starts the stage loop of a schedule: its table (stage i = (t, h, update mode, write output)),
-// the time embedding of every stage, the counters and the output `out`.
+// the time embedding of the first stages, the counters and the output `out`.
 int begin_stages(fmd_model* m, Call& c, const fmd_schedule* s, float* out, int* n_stages) {
   Workspace& w = m->ws;
   Workspace::HostStage& hs = w.hs[w.cur];   // the call's set (made writable by stage_events)
@@ -1131,10 +1140,11 @@ int begin_stages(fmd_model* m, Call& c, const fmd_schedule* s, float* out, int* 
   const int n = K * S;
   const int d = m->cfg.d_model;   // 0: the linear field, which has no time embedding
   FMD_TRY(ensure_desc(w, n));
-  if (n > w.cap_tstage && d > 0) {
+  const int rows = std::min(n, kStageRows);
+  if (rows > w.cap_tstage && d > 0) {
     w.cap_tstage = 0;
-    FMD_TRY(grow(w.tstage, (size_t)n * d * 4));
-    w.cap_tstage = n;
+    FMD_TRY(grow(w.tstage, (size_t)rows * d * 4));
+    w.cap_tstage = rows;
     w.generation++;
   }
   if (n > hs.cap_desc) {
@@ -1146,13 +1156,8 @@ int begin_stages(fmd_model* m, Call& c, const fmd_schedule* s, float* out, int* 
   HIP_TRY(hipMemcpyAsync(w.desc, hs.desc, (size_t)n * sizeof(StageDesc), hipMemcpyHostToDevice, c.st));
   FMD_TRY(mark_host_stage(w, c.st));
   FMD_TRY(timed(m, c.st, FMD_K_OTHER, 0, [&] { return launch_stage_begin(c.st, w.ctl, out); }));
-  if (m->kind == 0)
-    FMD_TRY(timed(m, c.st, FMD_K_OTHER, 0, [&] {
-      return launch_time_embed(c.st, nullptr, w.desc, n, m->W_time, m->b_time, m->b_xin,
-                               m->cfg.t_embed_dim, d, w.tstage);
-    }));
   *n_stages = n;
-  return FMD_OK;
+  return stage_times(m, c, 0, n);
 }
 
 // One ODE stage: velocity at the current stage input, fused update (which moves the counters on).
@@ -1205,9 +1210,15 @@ int run_stages(fmd_model* m, Call& c, int n_stages, int ldo) {
       }
       sg.key = key;
     }
-    for (; done + per <= n_stages; done += per) HIP_TRY(hipGraphLaunch(sg.exec, c.st));
+    for (; done + per <= n_stages; done += per) {
+      if (done) FMD_TRY(stage_times(m, c, done, n_stages));
+      HIP_TRY(hipGraphLaunch(sg.exec, c.st));
+    }
   }
-  for (; done < n_stages; ++done) FMD_TRY(run_stage<T>(m, c, ldo));
+  for (; done < n_stages; ++done) {
+    if (done) FMD_TRY(stage_times(m, c, done, n_stages));
+    FMD_TRY(run_stage<T>(m, c, ldo));
+  }
   return FMD_OK;
 }
 

@@ -43,7 +43,7 @@ struct Workspace {
   int64_t* off = nullptr;          // [E + 1]
   AttnItem* work = nullptr;        // attention work list
   StageDesc* desc = nullptr;       // [stages] stage table of the call
-  float* tstage = nullptr;         // [stages, d] time embeddings of the call's stages
+  float* tstage = nullptr;         // [up to kStageRows, d] time embeddings of stages
   StageCtl* ctl = nullptr;         // current stage and output of the call (device)
   // Pinned staging of the host-built arrays a call uploads (offsets, attention work lists,
   // stage table), two sets used by alternate calls. A set's event is recorded after the

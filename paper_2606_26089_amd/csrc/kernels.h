@@ -81,13 +81,16 @@ __device__ __forceinline__ void ode_next_stage(const OdeArgs& ode) {
   if (ode.desc && !ode.tok_event && blockIdx.x == 0 && threadIdx.x == 0)
     ode.ctl->first = ode.ctl->last + 1;
 }
-// The time-embedding row of the current stage (temb [stages][d]; ctl null: row 0). Called once by
+// Time-embedding rows kept at a time: stage i uses row i % kStageRows, and a longer schedule forms
+// the rows anew every kStageRows stages (a multiple of the stages of a graph).
+constexpr int kStageRows = 1024;
+// The time-embedding row of the current stage (temb [kStageRows][d]; ctl null: row 0). Called once by
 // the first kernel of a stage for the counter, by as many threads as need the row.
 __device__ __forceinline__ const float* stage_row(const float* temb, StageCtl* ctl, int d) {
   if (!ctl) return temb;
   const int32_t i = ctl->first;
   if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) ctl->last = i;
-  return temb + (int64_t)i * d;
+  return temb + (int64_t)(i % kStageRows) * d;
 }
 constexpr int kGemmBM = 256;       // largest GEMM row tile; token buffers are padded to this
 

@@ -1,11 +1,12 @@
 """The workspace that a model's own calls, its server and its captured stage graphs share (GPU):
-buffers that move under a cached graph."""
+buffers that move under a cached graph, growths that fail, tables that stay bounded."""
 
 import numpy as np
 import pytest
 
+from oracle import sample
 from tests._gpu import fmd_lib, torch_cuda
-from workload import configs, events, params
+from workload import configs, errors, events, params
 
 pytestmark = pytest.mark.gpu
 
@@ -63,3 +64,40 @@ def test_a_workspace_that_could_not_grow_is_grown_by_the_next_call(cfg):
     assert torch.equal(m.simulate(off, feat, 3, sched), first)
     assert torch.equal(m.velocity(off, feat, first, t), v)
     m.close()
+
+
+def test_time_embeddings_of_a_long_schedule_are_bounded():
+    """A schedule of 60,000 stages needs 16 bytes of the stage table each (0.96 MB); the time
+    embeddings, 256 bytes a stage at this width, are formed 1,024 stages at a time instead of
+    taking 15 MB more. The device's free memory moves by less than 6 MB (allocations come in units
+    of 2 MB), and a short call afterwards is unchanged."""
+    torch, fmd = torch_cuda(), fmd_lib()
+    m = fmd.Model(CFG, params.draw(CFG, 5, perturbed=True))
+    off, feat = _events(torch, [3, 2])
+    out = torch.empty((5, 9), device="cuda")
+    short = m.simulate(off, feat, 3, configs.Schedule(configs.EULER, 20)).clone()
+    torch.cuda.synchronize()
+    free = torch.cuda.mem_get_info()[0]
+    m.simulate(off, feat, 3, configs.Schedule(configs.EULER, 60000), out=out)
+    torch.cuda.synchronize()
+    assert free - torch.cuda.mem_get_info()[0] < 6 << 20
+    assert torch.isfinite(out).all()
+    assert torch.equal(m.simulate(off, feat, 3, configs.Schedule(configs.EULER, 20)), short)
+    m.close()
+
+
+@pytest.mark.parametrize("graphs", [True, False])
+def test_a_schedule_longer_than_the_time_rows_matches_the_oracle(graphs):
+    """1,100 Euler stages (two sets of time embeddings) on one event, against the oracle within
+    the bar of the FP32 parity tests."""
+    torch, fmd = torch_cuda(), fmd_lib()
+    cfg = configs.ModelCfg(d_model=64, n_blocks=1, n_heads=4, n_max=64)
+    flat = params.draw(cfg, 6, perturbed=True)
+    off, feat = _events(torch, [3], seed=4)
+    sched = configs.Schedule(configs.EULER, 1100)
+    m = fmd.Model(cfg, flat)
+    m.graphs_enable(graphs)
+    got = m.simulate(off, feat, 8, sched).cpu().numpy()
+    m.close()
+    ref = sample.simulate(flat, cfg, off, feat.cpu().numpy(), sched, seed=8)
+    assert errors.normwise_rel_err(got, ref).max() < 1e-4
