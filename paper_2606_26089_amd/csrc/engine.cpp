@@ -148,12 +148,12 @@ int ensure_ws_alloc(fmd_model* m, int64_t T, int64_t E, int64_t items, bool* gre
     if (!w.ctl) FMD_TRY(grow(w.ctl, sizeof(StageCtl)));
     if (m->kind == 0) {
       FMD_TRY(grow(w.H, (size_t)cap * d * 4));
-      FMD_TRY(grow(w.stats, (size_t)cap * sizeof(float2)));
+      if (uses_row_stats(m)) FMD_TRY(grow(w.stats, (size_t)cap * sizeof(float2)));
       FMD_TRY(grow(w.qkv, (size_t)cap * 3 * d * es));
       FMD_TRY(grow(w.att, (size_t)cap * d * es));
       FMD_TRY(grow(w.qc, (size_t)cap * d * es));
       FMD_TRY(grow(w.hid, (size_t)cap * 4 * d * es));
-      FMD_TRY(grow(w.c, (size_t)cap * d * es));
+      if (uses_truth_rows(m)) FMD_TRY(grow(w.c, (size_t)cap * d * es));
       FMD_TRY(grow(w.kv, (size_t)cap * 2 * d * L * es));
     }
     w.cap_tok = cap;

@@ -135,6 +135,10 @@ inline void same_truth(Call& c) {
   c.sum_nx = c.sum_n2;
 }
 
+// Buffers that not every model has: the LayerNorm statistics between kernels (the split products
+// form their own) and the truth encoding (which the split products and k_truth_kv keep on chip).
+inline bool uses_row_stats(const fmd_model* m) { return !m->split; }
+inline bool uses_truth_rows(const fmd_model* m) { return !m->split && !m->fused_ok; }
 int ensure_ws(fmd_model* m, int64_t T, int64_t E, int64_t items);
 int ensure_desc(Workspace& w, int64_t n);
 int check_events(const fmd_model* m, const fmd_events_in* ev, int64_t* T_out, int64_t* max_n);

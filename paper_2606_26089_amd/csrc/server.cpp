@@ -180,10 +180,11 @@ namespace {
 
 // Device bytes one resident token costs: ODE state, residual stream and LayerNorm
 // statistics, activations, truth features and encoding, cross K/V cache, output.
-size_t bytes_per_token(const fmd_model_config& c) {
+size_t bytes_per_token(const fmd_model* m) {
+  const fmd_model_config& c = m->cfg;
   const size_t d = c.d_model, L = c.n_blocks, es = c.precision == FMD_FP32 ? 4 : 2;
-  return 3 * kStateLd * 4 + d * 4 + sizeof(float2) + 4 + (3 * d + d + d + 4 * d + d) * es +
-         2 * d * L * es + 9 * 4 * 2;
+  return 3 * kStateLd * 4 + d * 4 + (uses_row_stats(m) ? sizeof(float2) : 0) + 4 +
+         (3 * d + d + d + 4 * d + (uses_truth_rows(m) ? d : 0)) * es + 2 * d * L * es + 9 * 4 * 2;
 }
 
 // Enqueues the admission of r: noise, truth encoding and cross K/V cache in its pool range.
@@ -523,7 +524,7 @@ int fmd_server_create(fmd_model* m, const fmd_server_config* cfg, fmd_server** o
   if (m->server) return fail(FMD_E_STATE, "the model already has a server");
   if (cfg->max_requests < 0 || cfg->max_tokens_per_iter < 0)
     return fail(FMD_E_INVALID, "negative limits");
-  const size_t bpt = bytes_per_token(m->cfg);
+  const size_t bpt = bytes_per_token(m);
   const int64_t pool = ((int64_t)(cfg->hbm_budget_bytes / bpt) - kPoolSlack) / kTile * kTile;
   if (pool < kTile)
     return fail(FMD_E_BUDGET, "HBM budget below one 64-row tile (%zu bytes per row)", bpt);

@@ -101,3 +101,33 @@ def test_a_schedule_longer_than_the_time_rows_matches_the_oracle(graphs):
     m.close()
     ref = sample.simulate(flat, cfg, off, feat.cpu().numpy(), sched, seed=8)
     assert errors.normwise_rel_err(got, ref).max() < 1e-4
+
+
+@pytest.mark.parametrize("cfg,stats,encoding", [
+    (configs.BASE_MODEL.with_precision(configs.BF16), 8, 0),        # k_truth_kv keeps the encoding
+    (configs.BASE_MODEL, 0, 0),                                     # split products: neither
+    (configs.ModelCfg(d_model=128, n_blocks=2, n_heads=4, n_max=64, precision=configs.BF16), 8, 1),
+    (configs.ModelCfg(d_model=320, n_blocks=1, n_heads=10, n_max=64), 8, 1)],
+    ids=["base-bf16", "base-fp32", "d128-bf16", "d320-fp32"])
+def test_a_row_of_the_server_pool_costs_the_buffers_the_model_uses(cfg, stats, encoding):
+    """bytes_per_token is the sum of a row's buffers: three state arrays of 16 floats, the residual
+    row, its event index, Q/K/V, attention output, cross query, hidden layer, cross K/V of every
+    block, features and output; the LayerNorm statistics and the truth encoding only where kernels
+    leave them in memory. The device memory of a pool of a gibibyte is that per row, within 2%."""
+    torch, fmd = torch_cuda(), fmd_lib()
+    m = fmd.Model(cfg, params.draw(cfg, 0))
+    d, es = cfg.d_model, 2 if cfg.precision == configs.BF16 else 4
+    row = 3 * 64 + 4 * d + 4 + 9 * d * es + 2 * d * cfg.n_blocks * es + 72 + stats + encoding * d * es
+    torch.cuda.synchronize()
+    free = torch.cuda.mem_get_info()[0]
+    srv = fmd.Server(m, hbm_budget_bytes=1 << 30)
+    used = free - torch.cuda.mem_get_info()[0]
+    info = srv.info()
+    assert info["bytes_per_token"] == row
+    assert 0.98 < used / (row * (info["pool_tokens"] + 256)) < 1.02, used
+    off, feat = events.truth_events(5, ("uniform", 1, 50), seed=8)
+    sched = configs.Schedule(configs.EULER, 3)
+    got, _ = srv.wait(srv.submit(off, feat, 9, sched))
+    srv.close()
+    assert np.array_equal(got, m.simulate(off, feat, 9, sched))
+    m.close()
