@@ -84,13 +84,14 @@ __device__ __forceinline__ void ode_next_stage(const OdeArgs& ode) {
 // Time-embedding rows kept at a time: stage i uses row i % kStageRows, and a longer schedule forms
 // the rows anew every kStageRows stages (a multiple of the stages of a graph).
 constexpr int kStageRows = 1024;
+static_assert((kStageRows & (kStageRows - 1)) == 0, "a mask");
 // The time-embedding row of the current stage (temb [kStageRows][d]; ctl null: row 0). Called once by
 // the first kernel of a stage for the counter, by as many threads as need the row.
 __device__ __forceinline__ const float* stage_row(const float* temb, StageCtl* ctl, int d) {
   if (!ctl) return temb;
   const int32_t i = ctl->first;
   if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) ctl->last = i;
-  return temb + (int64_t)(i % kStageRows) * d;
+  return temb + (uint32_t)(i & (kStageRows - 1)) * (uint32_t)d;
 }
 constexpr int kGemmBM = 256;       // largest GEMM row tile; token buffers are padded to this
 
