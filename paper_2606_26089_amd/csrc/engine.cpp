@@ -153,7 +153,7 @@ int ensure_ws_alloc(fmd_model* m, int64_t T, int64_t E, int64_t items, bool* gre
       FMD_TRY(grow(w.att, (size_t)cap * d * es));
       FMD_TRY(grow(w.qc, (size_t)cap * d * es));
       FMD_TRY(grow(w.hid, (size_t)cap * 4 * d * es));
-      if (uses_truth_rows(m)) FMD_TRY(grow(w.c, (size_t)cap * d * es));
+      if (has_truth_rows(m)) FMD_TRY(grow(w.c, (size_t)cap * d * es));
       FMD_TRY(grow(w.kv, (size_t)cap * 2 * d * L * es));
     }
     w.cap_tok = cap;

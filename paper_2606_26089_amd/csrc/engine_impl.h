@@ -136,9 +136,12 @@ inline void same_truth(Call& c) {
 }
 
 // Buffers that not every model has: the LayerNorm statistics between kernels (the split products
-// form their own) and the truth encoding (which the split products and k_truth_kv keep on chip).
+// form their own) and the rows of the truth encoding (k_truth_kv keeps them on chip). The split
+// products do not read the latter either, but without that buffer between the hidden layer and the
+// K/V cache an FP32 call of 14,276 rows takes 0.5 to 2% longer (several models in turn; 27,300 and
+// 27,450 us and more, and likewise with the cache moved elsewhere), so they keep it.
 inline bool uses_row_stats(const fmd_model* m) { return !m->split; }
-inline bool uses_truth_rows(const fmd_model* m) { return !m->split && !m->fused_ok; }
+inline bool has_truth_rows(const fmd_model* m) { return !m->fused_ok; }
 int ensure_ws(fmd_model* m, int64_t T, int64_t E, int64_t items);
 int ensure_desc(Workspace& w, int64_t n);
 int check_events(const fmd_model* m, const fmd_events_in* ev, int64_t* T_out, int64_t* max_n);

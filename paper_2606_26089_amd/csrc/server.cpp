@@ -184,7 +184,7 @@ size_t bytes_per_token(const fmd_model* m) {
   const fmd_model_config& c = m->cfg;
   const size_t d = c.d_model, L = c.n_blocks, es = c.precision == FMD_FP32 ? 4 : 2;
   return 3 * kStateLd * 4 + d * 4 + (uses_row_stats(m) ? sizeof(float2) : 0) + 4 +
-         (3 * d + d + d + 4 * d + (uses_truth_rows(m) ? d : 0)) * es + 2 * d * L * es + 9 * 4 * 2;
+         (3 * d + d + d + 4 * d + (has_truth_rows(m) ? d : 0)) * es + 2 * d * L * es + 9 * 4 * 2;
 }
 
 // Enqueues the admission of r: noise, truth encoding and cross K/V cache in its pool range.

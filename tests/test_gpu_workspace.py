@@ -105,15 +105,15 @@ def test_a_schedule_longer_than_the_time_rows_matches_the_oracle(graphs):
 
 @pytest.mark.parametrize("cfg,stats,encoding", [
     (configs.BASE_MODEL.with_precision(configs.BF16), 8, 0),        # k_truth_kv keeps the encoding
-    (configs.BASE_MODEL, 0, 0),                                     # split products: neither
+    (configs.BASE_MODEL, 0, 1),                                     # split products: own statistics
     (configs.ModelCfg(d_model=128, n_blocks=2, n_heads=4, n_max=64, precision=configs.BF16), 8, 1),
     (configs.ModelCfg(d_model=320, n_blocks=1, n_heads=10, n_max=64), 8, 1)],
     ids=["base-bf16", "base-fp32", "d128-bf16", "d320-fp32"])
 def test_a_row_of_the_server_pool_costs_the_buffers_the_model_uses(cfg, stats, encoding):
     """bytes_per_token is the sum of a row's buffers: three state arrays of 16 floats, the residual
     row, its event index, Q/K/V, attention output, cross query, hidden layer, cross K/V of every
-    block, features and output; the LayerNorm statistics and the truth encoding only where kernels
-    leave them in memory. The device memory of a pool of a gibibyte is that per row, within 2%."""
+    block, features and output; the LayerNorm statistics and the rows of the truth encoding only
+    where the model has them. The device memory of a pool of a gibibyte is that per row, within 2%."""
     torch, fmd = torch_cuda(), fmd_lib()
     m = fmd.Model(cfg, params.draw(cfg, 0))
     d, es = cfg.d_model, 2 if cfg.precision == configs.BF16 else 4
