@@ -16,6 +16,7 @@
 //   BF16: v_mfma_f32_16x16x32_bf16 (8 consecutive k per lane group), or 16x16x16 for dh 16
 // Accumulator layout: lane l, register r holds row 4(l/16) + r, column l%16.
 #include <algorithm>
+#include <limits>
 #include <vector>
 
 #include "common.h"
@@ -743,9 +744,11 @@ namespace {
 // The builder over accessors: queries of event k at q_off[ids[k]], nq(k) rows; its keys at
 // k0(k), nk(k) rows.
 template <typename Nq, typename K0, typename Nk>
-int64_t build_work(const int64_t* q_off, const int64_t* ids, int64_t n, int qt, Nq nq, K0 k0,
-                   Nk nk, AttnItem* items, AttnBins* bins) {
-  // longest-processing-time assignment of whole events to bins; cost = query tiles x keys
+int64_t build_work(const int64_t* q_off, const int64_t* ids, int64_t n, int qt, bool deal, Nq nq,
+                   K0 k0, Nk nk, AttnItem* items, AttnBins* bins) {
+  // longest-processing-time assignment of whole events to bins; cost = query tiles x keys. With
+  // `deal`, the tiles of an event that holds more than a quarter of a bin's fair share go to the
+  // least loaded bin one by one.
   std::vector<int64_t> order;
   order.reserve((size_t)n);
   for (int64_t k = 0; k < n; ++k) {
@@ -756,16 +759,31 @@ int64_t build_work(const int64_t* q_off, const int64_t* ids, int64_t n, int qt, 
   auto tiles = [&](int64_t k) { return (nq(k) + qt - 1) / qt; };
   auto cost = [&](int64_t k) { return tiles(k) * nk(k); };
   std::stable_sort(order.begin(), order.end(), [&](int64_t a, int64_t b) { return cost(a) > cost(b); });
-  std::vector<int> bin_of(order.size());
+  int64_t whole = std::numeric_limits<int64_t>::max();   // largest cost of an event kept whole
+  if (deal) {
+    int64_t total = 0;
+    for (int64_t k : order) total += cost(k);
+    whole = total / (4 * kAttnBins);
+  }
+  std::vector<int8_t> bin_of, tile_bin;   // per event (-1: dealt); per tile of the dealt ones, in turn
+  bin_of.reserve(order.size());
   int64_t load[kAttnBins] = {0};
   int64_t cnt[kAttnBins] = {0};
-  for (size_t i = 0; i < order.size(); ++i) {
+  auto assign = [&](int64_t c, int64_t t) {
     int best = 0;
     for (int b = 1; b < kAttnBins; ++b)
       if (load[b] < load[best]) best = b;
-    bin_of[i] = best;
-    load[best] += cost(order[i]);
-    cnt[best] += tiles(order[i]);
+    load[best] += c;
+    cnt[best] += t;
+    return (int8_t)best;
+  };
+  for (int64_t k : order) {
+    if (cost(k) <= whole) {
+      bin_of.push_back(assign(cost(k), tiles(k)));
+      continue;
+    }
+    bin_of.push_back(-1);
+    for (int64_t q = 0; q < tiles(k); ++q) tile_bin.push_back(assign(nk(k), 1));
   }
   int64_t pos = 0;
   bins->max_len = 0;
@@ -773,13 +791,16 @@ int64_t build_work(const int64_t* q_off, const int64_t* ids, int64_t n, int qt, 
     bins->start[b] = (int32_t)pos;
     bins->len[b] = (int32_t)cnt[b];
     bins->max_len = std::max<int32_t>(bins->max_len, (int32_t)cnt[b]);
+    size_t dealt = 0;
     for (size_t i = 0; i < order.size(); ++i) {
-      if (bin_of[i] != b) continue;
+      if (bin_of[i] >= 0 && bin_of[i] != b) continue;
       const int64_t k = order[i], e = ids[k];
-      for (int64_t q = 0; q < tiles(k); ++q)
+      for (int64_t q = 0; q < tiles(k); ++q) {
+        if (bin_of[i] < 0 && tile_bin[dealt++] != b) continue;
         items[pos++] = AttnItem{(int32_t)(q_off[e] + q * qt),
                                 (int32_t)std::min<int64_t>(qt, nq(k) - q * qt),
                                 (int32_t)k0(k), (int32_t)nk(k)};
+      }
     }
   }
   return pos;
@@ -787,18 +808,18 @@ int64_t build_work(const int64_t* q_off, const int64_t* ids, int64_t n, int qt, 
 }  // namespace
 
 int64_t build_attention_work(const int64_t* q_off, const int64_t* kv_off, const int64_t* ids,
-                             int64_t n, int qt, AttnItem* items, AttnBins* bins) {
+                             int64_t n, int qt, bool deal, AttnItem* items, AttnBins* bins) {
   return build_work(
-      q_off, ids, n, qt, [&](int64_t k) { return q_off[ids[k] + 1] - q_off[ids[k]]; },
+      q_off, ids, n, qt, deal, [&](int64_t k) { return q_off[ids[k] + 1] - q_off[ids[k]]; },
       [&](int64_t k) { return kv_off[ids[k]]; },
       [&](int64_t k) { return kv_off[ids[k] + 1] - kv_off[ids[k]]; }, items, bins);
 }
 
 int64_t build_attention_work_kv(const int64_t* q_off, const int64_t* kv_start,
                                 const int64_t* kv_len, const int64_t* ids, int64_t n, int qt,
-                                AttnItem* items, AttnBins* bins) {
+                                bool deal, AttnItem* items, AttnBins* bins) {
   return build_work(
-      q_off, ids, n, qt, [&](int64_t k) { return q_off[ids[k] + 1] - q_off[ids[k]]; },
+      q_off, ids, n, qt, deal, [&](int64_t k) { return q_off[ids[k] + 1] - q_off[ids[k]]; },
       [&](int64_t k) { return kv_start[ids[k]]; }, [&](int64_t k) { return kv_len[ids[k]]; },
       items, bins);
 }
@@ -810,6 +831,12 @@ int attention_query_tile(bool bf16, int dh, int64_t rows) {
   // with 128; 14,276 rows: 30.2 and 30.5; 58,499 rows: 99 and 90; three tiles a wave spill)
   return bf16 || rows > 16384 ? 128 : 64;
 }
+
+// The FP32 kernel of heads of 32 takes several times as long as the BF16 one for the same keys, so
+// one event on one XCD (32 of the 256 CUs) is the launch's time where a few large events make up
+// a call. Their tiles go to all XCDs, which then read the keys from the last-level cache each (one
+// event of 4,000, 8 heads: 858 us a launch whole, 143 dealt; the general kernel before: 230).
+bool attention_deal(bool bf16, int dh) { return !bf16 && dh == kH32; }
 
 int attention_query_tiles(bool bf16, int dh, int* tiles) {
   if (bf16 && dh == kH32) {

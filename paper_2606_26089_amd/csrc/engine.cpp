@@ -291,6 +291,7 @@ void flush_timing(fmd_model* m) {
 int bucket_of(int64_t Tp);
 int attn_tiles(const fmd_model* m, int* tiles);
 int attn_tile_for(const fmd_model* m, int64_t Tp);
+bool attn_deal(const fmd_model* m);
 template <typename F>
 float time_best_us(hipStream_t st, hipEvent_t e0, hipEvent_t e1, F&& launch, int reps = 3,
                    int reps_long = 3);
@@ -310,6 +311,7 @@ int stage_events(fmd_model* m, const fmd_events_in* ev, Call& c, const int64_t* 
   // work items: (event, query tile), in bins of whole events balanced by attention work
   int tiles[4];
   const int n_tiles = attn_tiles(m, tiles);
+  const bool deal = attn_deal(m);
   std::vector<int64_t> ids((size_t)E);
   auto count_items = [&](int qt) {
     int64_t k = 0;
@@ -343,7 +345,7 @@ int stage_events(fmd_model* m, const fmd_events_in* ev, Call& c, const int64_t* 
     for (int k = 0; k < n_tiles && status == FMD_OK; ++k) {
       const int64_t nk = count_items(tiles[k]);
       AttnBins bk{};
-      if (build_attention_work(roff, roff, ids.data(), E, tiles[k], hs.work, &bk) != nk) {
+      if (build_attention_work(roff, roff, ids.data(), E, tiles[k], deal, hs.work, &bk) != nk) {
         status = fail(FMD_E_INVALID, "token rows beyond 2^31");
         break;
       }
@@ -378,7 +380,7 @@ int stage_events(fmd_model* m, const fmd_events_in* ev, Call& c, const int64_t* 
   c.items = items;
   const int64_t all_items = reco_off ? 2 * items : items;
   std::memcpy(hs.off, roff, (size_t)(E + 1) * 8);
-  if (build_attention_work(hs.off, hs.off, ids.data(), E, qt, hs.work, &c.bins) != items)
+  if (build_attention_work(hs.off, hs.off, ids.data(), E, qt, deal, hs.work, &c.bins) != items)
     return fail(FMD_E_INVALID, "token rows beyond 2^31");
   same_truth(c);
   if (reco_off) {
@@ -386,7 +388,7 @@ int stage_events(fmd_model* m, const fmd_events_in* ev, Call& c, const int64_t* 
     c.Ttp = round_up(std::max<int64_t>(Tt, 1), kGemmBM);
     c.work_x = items;
     c.sum_nx = sx;
-    if (build_attention_work(hs.off, ev->offsets, ids.data(), E, qt, hs.work + items,
+    if (build_attention_work(hs.off, ev->offsets, ids.data(), E, qt, deal, hs.work + items,
                              &c.bins_x) != items)
       return fail(FMD_E_INVALID, "token rows beyond 2^31");
   }
@@ -499,6 +501,9 @@ int resid_epi(const fmd_model* m) { return m->fuse_stats ? EPI_RESID_LN : EPI_RE
 int attn_tiles(const fmd_model* m, int* tiles) {
   return attention_query_tiles(m->cfg.precision != FMD_FP32,
                                m->cfg.d_model / std::max(m->cfg.n_heads, 1), tiles);
+}
+bool attn_deal(const fmd_model* m) {
+  return attention_deal(m->cfg.precision != FMD_FP32, m->cfg.d_model / std::max(m->cfg.n_heads, 1));
 }
 int attn_tile_for(const fmd_model* m, int64_t Tp) {
   int tiles[4];
@@ -2083,8 +2088,8 @@ int fmd_debug_attention(int32_t precision, int64_t n_events, const int64_t* q_of
   }
   std::vector<AttnItem> work((size_t)n_items);
   AttnBins bins{};
-  if (build_attention_work(q_offsets, kv_offsets, ids.data(), n_events, qt, work.data(), &bins) !=
-      n_items)
+  if (build_attention_work(q_offsets, kv_offsets, ids.data(), n_events, qt,
+                           attention_deal(precision == FMD_BF16, dh), work.data(), &bins) != n_items)
     return fail(FMD_E_INVALID, "rows beyond 2^31");
   const int64_t Tq = q_offsets[n_events], Tk = kv_offsets[n_events];
   if (work.empty()) return FMD_OK;

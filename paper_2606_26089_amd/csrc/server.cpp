@@ -311,9 +311,9 @@ int iterate(fmd_server* S, int k, std::vector<Req*>& finished) {
     std::vector<int64_t> ids(real.size());
     for (size_t i = 0; i < real.size(); ++i) ids[i] = real[i].first;
     if (build_attention_work(off.data(), off.data(), ids.data(), (int64_t)real.size(),
-                             qt, g.work, &bins) != items ||
+                             qt, attn_deal(m), g.work, &bins) != items ||
         build_attention_work_kv(off.data(), kv0.data(), kvn.data(), ids.data(),
-                                (int64_t)real.size(), qt, g.work + items, &bins_x) != items)
+                                (int64_t)real.size(), qt, attn_deal(m), g.work + items, &bins_x) != items)
       return fail(FMD_E_INVALID, "token rows beyond 2^31");
   }
   FMD_TRY(ensure_desc(w, E));
