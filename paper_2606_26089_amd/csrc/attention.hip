@@ -862,27 +862,45 @@ hipError_t launch_attention(hipStream_t st, bool cross, int dh, int n_heads, int
     if (ldq % 8 || ldkv % 8 || ldo % 4 || hsq % 8 || hskv % 8 || hso % 4 || hsq < dh ||
         hskv < dh || hso < dh || (qt != 64 && qt != 128 && (qt != 192 || sizeof(T) == 4)))
       return hipErrorInvalidValue;
-    const int64_t blocks = (int64_t)kAttnBins * bins.max_len * n_heads;
-    if (blocks > 0x7fffffff) return hipErrorInvalidValue;
-    if (blocks == 0) return hipSuccess;
+    // The grid holds every bin's items times the heads. A launch has at most 2^32 - 1 work items,
+    // which millions of small events exceed (the runtime drops the excess without an error): then
+    // a part of every bin at a time.
+    const int64_t step = 0xffffffff / 256 / ((int64_t)kAttnBins * n_heads);
+    auto parts = [&](auto&& launch) {
+      for (int64_t i = 0; i < bins.max_len; i += step) {
+        AttnBins part = bins;
+        for (int b = 0; b < kAttnBins; ++b) {
+          part.len[b] = (int32_t)std::min(step, std::max<int64_t>(bins.len[b] - i, 0));
+          part.start[b] = (int32_t)(bins.start[b] + (part.len[b] ? i : 0));
+        }
+        part.max_len = (int32_t)std::min<int64_t>(step, bins.max_len - i);
+        launch(part, (unsigned)(kAttnBins * part.max_len * n_heads));
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+      }
+      return hipSuccess;
+    };
     if constexpr (std::is_same<T, bf16>::value) {
-      // the grid's attention part is a multiple of the XCD count
-      const int64_t parts = touch.p ? (touch.bytes + (int64_t)kTouchPart - 1) / kTouchPart : 0;
-      const int64_t grid = blocks + kAttnBins * parts;
-      if (grid > 0x7fffffff) return hipErrorInvalidValue;
-      touch.first = (uint32_t)blocks;
+      // workgroups that read weights follow the attention part, a multiple of the XCD count (few
+      // rows, so one launch)
+      const int64_t warm = touch.p ? kAttnBins * ((touch.bytes + (int64_t)kTouchPart - 1) / kTouchPart) : 0;
+      if (warm && (bins.max_len > step || kAttnBins * bins.max_len * n_heads + warm > 0xffffffff / 256))
+        return hipErrorInvalidValue;
       auto go = [&](auto* k) {
-        hipLaunchKernelGGL(k, dim3((unsigned)grid), dim3(256), 0, st, Q, ldq, hsq, K, V, ldkv, hskv,
-                           O, ldo, hso, work, bins, n_heads, sl2e, touch);
-        return hipGetLastError();
+        return parts([&](const AttnBins& part, unsigned blocks) {
+          touch.first = blocks;
+          hipLaunchKernelGGL(k, dim3(blocks + (unsigned)warm), dim3(256), 0, st, Q, ldq, hsq, K, V, ldkv,
+                             hskv, O, ldo, hso, work, part, n_heads, sl2e, touch);
+        });
       };
       if (cross) return go(qt == 64 ? k_attn32_cross<1> : qt == 128 ? k_attn32_cross<2> : k_attn32_cross<3>);
       return go(qt == 64 ? k_attn32_self<1> : qt == 128 ? k_attn32_self<2> : k_attn32_self<3>);
     } else {
       auto go = [&](auto* k) {
-        hipLaunchKernelGGL(k, dim3((unsigned)blocks), dim3(256), 0, st, Q, ldq, hsq, K, V, ldkv,
-                           hskv, O, ldo, hso, work, bins, n_heads, sl2e);
-        return hipGetLastError();
+        return parts([&](const AttnBins& part, unsigned blocks) {
+          hipLaunchKernelGGL(k, dim3(blocks), dim3(256), 0, st, Q, ldq, hsq, K, V, ldkv, hskv, O, ldo,
+                             hso, work, part, n_heads, sl2e);
+        });
       };
       if (cross) return go(qt == 64 ? k_attn_cross<1> : k_attn_cross<2>);
       return go(qt == 64 ? k_attn_self<1> : k_attn_self<2>);

@@ -1,5 +1,6 @@
-"""FP32 attention of heads of 32 over few and large events (GPU): the work items of an event that is
-large against the call are dealt to all XCDs instead of one."""
+"""Attention of heads of 32 at the ends of its range of work lists (GPU). FP32, few and large events:
+the work items of an event that is large against the call are dealt to all XCDs instead of one.
+Millions of small events: more workgroups than one launch holds."""
 
 import numpy as np
 import pytest
@@ -72,3 +73,25 @@ def test_dealt_events_keep_their_bits(d, heads):
     big = m.simulate(off2, feat2, 5, sched, reco_offsets=roff)
     assert torch.equal(big[:int(roff[len(sizes)])], small)
     m.close()
+
+
+@pytest.mark.parametrize("precision", [configs.FP32, configs.BF16])
+def test_millions_of_small_events(precision):
+    """2.2 million events of one particle are 17.6 million (item, head) workgroups at 8 heads, more
+    than the 2^32 - 1 work items of one launch. Each event's velocity is that of a small call; in BF16 as well."""
+    torch, fmd = torch_cuda(), fmd_lib()
+    cfg = configs.ModelCfg(d_model=256, n_blocks=1, n_heads=8, n_max=16, precision=precision)
+    m = fmd.Model(cfg, params.draw(cfg, 3, perturbed=True))
+    E = 2_200_000
+    g = torch.Generator(device="cuda")
+    g.manual_seed(7)
+    off = np.arange(E + 1, dtype=np.int64)
+    feat, x = (torch.randn((E, 9), generator=g, device="cuda") for _ in range(2))
+    t = torch.rand(E, generator=g, device="cuda")
+    v = m.velocity(off, feat, x, t)
+    for a in (0, E // 2, E - 1000):
+        part = [q[a:a + 1000].contiguous() for q in (feat, x, t)]
+        assert torch.equal(m.velocity(off[:1001], *part), v[a:a + 1000])
+    assert torch.isfinite(v).all()
+    m.close()
+    torch.cuda.empty_cache()
