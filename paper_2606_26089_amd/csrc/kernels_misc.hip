@@ -1,6 +1,8 @@
 // Bandwidth-bound kernels of the sampling path: CSR token map, Philox noise, truth
 // encoder, time and input embeddings, the fused output head + ODE update, ragged
 // packing and parameter packing.
+#include <algorithm>
+
 #include "common.h"
 #include "kernels.h"
 
@@ -790,6 +792,19 @@ __device__ __forceinline__ double obs_wave_sum(double v) {
   return obs_plus_ror<0x121>(v);
 }
 
+// A workgroup per event: a launch has at most 2^32 - 1 work items, and the runtime cuts a larger
+// grid short without an error, so millions of events go in parts (of 512 threads at most each).
+template <typename F>
+hipError_t event_parts(int64_t n_events, F&& launch) {
+  constexpr int64_t kPart = 1 << 22;
+  for (int64_t e0 = 0; e0 < n_events; e0 += kPart) {
+    launch(e0, (unsigned)std::min(kPart, n_events - e0));
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
+}
+
 struct ObsItem {       // a decoded particle, 16 bytes
   double pt;
   float eta, phi;
@@ -930,8 +945,9 @@ hipError_t launch_event_observables(hipStream_t st, const float* feat, int ldf,
   auto* k = nt == 128   ? k_event_observables<128>
             : nt == 256 ? k_event_observables<256>
                         : k_event_observables<512>;
-  hipLaunchKernelGGL(k, dim3((unsigned)n_events), dim3(nt), 0, st, feat, ldf, off_device, ht, met, iso);
-  return hipGetLastError();
+  return event_parts(n_events, [&](int64_t e0, unsigned n) {
+    hipLaunchKernelGGL(k, dim3(n), dim3(nt), 0, st, feat, ldf, off_device + e0, ht + e0, met + e0, iso);
+  });
 }
 
 // ---------------------------------------------------------------------------------------
@@ -1163,9 +1179,10 @@ hipError_t launch_select_count(hipStream_t st, const float* feat, int ldf, const
                                int32_t* cnt) {
   if (n_events <= 0) return hipSuccess;
   if (n_events > 0x7fffffff || limit < 0) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_select_count, dim3((unsigned)n_events), dim3(256), 0, st, feat, ldf, off,
-                     c0, limit, keep, cnt);
-  return hipGetLastError();
+  return event_parts(n_events, [&](int64_t e0, unsigned n) {
+    hipLaunchKernelGGL(k_select_count, dim3(n), dim3(256), 0, st, feat, ldf, off + e0, c0, limit, keep,
+                       cnt + e0);
+  });
 }
 
 hipError_t launch_select_offsets(hipStream_t st, const int32_t* cnt, int64_t n_events, int64_t* off) {
@@ -1178,9 +1195,10 @@ hipError_t launch_select_write(hipStream_t st, const float* feat, int ldf, const
                                float* out) {
   if (n_events <= 0) return hipSuccess;
   if (n_events > 0x7fffffff) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_select_write, dim3((unsigned)n_events), dim3(256), 0, st, feat, ldf, off,
-                     off_out, keep, out);
-  return hipGetLastError();
+  return event_parts(n_events, [&](int64_t e0, unsigned n) {
+    hipLaunchKernelGGL(k_select_write, dim3(n), dim3(256), 0, st, feat, ldf, off + e0, off_out + e0, keep,
+                       out);
+  });
 }
 
 }  // namespace fmd
