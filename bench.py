@@ -146,7 +146,7 @@ def select_leg(fmd, torch, off, feat_d, cut, limit, reps):
     torch.cuda.synchronize()
     dt = (time.perf_counter() - t0) / reps
     E = len(off) - 1
-    return {"kernels": ["k_select_count", "k_select_write"], "pt_cut_gev": cut,
+    return {"kernels": ["k_select_count", "k_select_offsets", "k_select_write"], "pt_cut_gev": cut,
             "max_particles": limit, "ms_per_call": round(dt * 1e3, 4),
             "events_per_s": round(E / dt, 1), "particles_in": int(off[-1]),
             "particles_out": int(o2[-1]), "calls": reps}

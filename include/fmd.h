@@ -67,9 +67,12 @@ enum { FMD_EULER = 0, FMD_RK4 = 1, FMD_MIDPOINT = 2 };
 /* Network shape. Supported: d_model = n_heads * dh with dh in {16, 32, 64}; d_model a
  * multiple of 64; mlp_ratio = 4; t_embed_dim = 32; f_truth = f_reco = 9; 1 <= n_max <= 4096.
  * precision FMD_FP32 computes every product to FP32 accuracy: the GEMMs of d_model up to 256 and
- * the attention of heads of 32 with both operands split into three BF16 parts and the six partial
- * products that matter on BF16 MFMA, the others as FP32 MFMA. FMD_BF16 feeds
- * BF16 operands to the MFMA with FP32 accumulation. In both, the residual stream,
+ * the attention of heads of 32 with both operands split into three BF16 parts and the six largest
+ * partial products on BF16 MFMA, the others as FP32 MFMA. The parts hold a value exactly (down to
+ * magnitudes of 2^-100; the third part of smaller ones is subnormal). Of a single product up to
+ * 2^-22 is left out, where the FP32 instruction has it exact; whole evaluations come out closer to
+ * 64 bits than with that instruction. FMD_BF16 feeds BF16 operands to the MFMA with FP32
+ * accumulation. In both, the residual stream,
  * LayerNorm and softmax statistics, the output head and the ODE state stay FP32. */
 typedef struct {
   int32_t d_model, n_blocks, n_heads, mlp_ratio, t_embed_dim, f_truth, f_reco, n_max, precision;
@@ -225,10 +228,10 @@ int fmd_noise(uint64_t seed, const int64_t* offsets, int64_t n_events, int32_t n
  * maximum of x3..x7 (charged hadron, electron, muon, neutral hadron, photon).
  * ht, met [n_events] and iso [offsets[n_events]] FP32 are written in the memory reco->feat
  * lives in (reco->on_device). Delta phi is wrapped by multiples of 2 pi; the cone test and
- * the class maximum are taken in FP32, pT and all sums in FP64. The final-state-radiation
- * photon exclusion is not applied (the paper does not define it). The call returns after
- * the results are complete. Errors: FMD_E_INVALID (bad offsets, null pointers),
- * FMD_E_NOMEM, FMD_E_DEVICE. */
+ * the class maximum are taken in FP32, pT and all sums in FP64, in an order that depends on the
+ * event alone. The final-state-radiation photon exclusion is not applied (the paper does not
+ * define it). The call returns after the results are complete. Errors: FMD_E_INVALID (bad
+ * offsets, null pointers), FMD_E_NOMEM, FMD_E_DEVICE. */
 int fmd_event_observables(const fmd_events_in* reco, float* ht, float* met, float* iso,
                           void* hip_stream);
 
@@ -315,8 +318,9 @@ const char* fmd_kernel_name(fmd_model* m, int32_t kernel_class);
  * and more) are captured once per call shape into a HIP graph on the model's private stream. The
  * graph is replayed for the stages: time, step, update mode and output buffer come from per-call
  * tables in device memory. A later call with the same token count, event count and workspace
- * reuses the graph without re-capturing it, whatever its output buffer. With timing on, or with graphs disabled, the same
- * kernels are launched one by one. Results are identical either way. */
+ * reuses the graph of its length without re-capturing it, whatever its output buffer. With timing
+ * on, or with graphs disabled, the same kernels are launched one by one. Results are identical
+ * either way. */
 int fmd_graphs_enable(fmd_model* m, int32_t enable);
 
 /* Fused block kernels (BF16 models with d_model 256 and MLP ratio 4; on by default there).
@@ -357,7 +361,8 @@ int fmd_autotune_enable(fmd_model* m, int32_t enable);
  * [2^tokens_log2, 2^(tokens_log2 + 1)) (rows padded to a multiple of 256), e.g. to reuse a
  * table measured earlier or to compare candidates.
  * Calls of at most 16384 padded rows whose choice is not fixed run these two kernels (and the
- * fused MLP kernel, which has no site) in a form for few rows, with the same results.
+ * fused MLP kernel, which has no site) in a form for few rows, with the same results; the table
+ * still lists the two sites, with the candidates that fmd_tuning_set would put in their place.
  * Errors: FMD_E_INVALID for a null model, another site, a bucket outside [0, 40) or a
  * candidate the model's kernels do not offer. */
 enum { FMD_TUNE_ATTN_QUERY_TILE = 5, FMD_TUNE_FUSED_QKV = 6, FMD_TUNE_FUSED_OQC = 7 };
@@ -370,7 +375,8 @@ int fmd_tuning_table(fmd_model* m, char* buf, size_t cap, size_t* needed);
 
 /* ---- kernel test hooks (used by the parity tests) --------------------------------------- */
 
-/* C[M,N] = epi(pro(A) W + b) with the model's GEMM kernel, all operands DEVICE FP32.
+/* C[M,N] = epi(pro(A) W + b) with the general GEMM kernel (FP32 models of d_model up to 256 run
+ * split products instead), all operands DEVICE FP32.
  * W is [K,N] row-major. With ln != 0, pro(A) = LN(A; g, s) over K features, otherwise
  * pro(A) = A. epi: 0 = store, 1 = exact GELU, 2 = accumulate (C += ...). For FMD_BF16,
  * A (after LN), W and the GELU output are rounded to BF16 as in the model.
@@ -396,8 +402,9 @@ int fmd_debug_attention(int32_t precision, int64_t n_events, const int64_t* q_of
 /* A continuous-batching server over one model. Requests are admitted FIFO when a
  * contiguous range of their particle count, rounded up to whole 64-row tiles, is free in a
  * device token pool. The pool is sized as hbm_budget_bytes divided by the per-token
- * footprint (ODE state, activations, truth encoding, cross K/V cache and output), rounded
- * down to whole tiles. An admitted request's state stays on the device until it completes.
+ * footprint (ODE state, activations, truth encoding where the model keeps it, cross K/V cache and
+ * output), rounded down to whole tiles. An admitted request's state stays on the device until it
+ * completes.
  * Each server iteration advances every resident event by one stage of its own schedule; the
  * block kernels run only the tiles of resident requests. The worker enqueues the next
  * iteration before it waits for the current one to end, so the device does not idle while

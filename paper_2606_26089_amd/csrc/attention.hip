@@ -826,8 +826,8 @@ int64_t build_attention_work_kv(const int64_t* q_off, const int64_t* kv_start,
 
 int attention_query_tile(bool bf16, int dh, int64_t rows) {
   if (dh != kH32) return QT;
-  // FP32: 128 queries share each staged (and split) chunk; below about 64 row tiles per XCD the
-  // work is too thin for that and 64 spread it wider (632 rows: 11.7 us a launch with 64, 15.6
+  // FP32: 128 queries share each staged (and split) chunk; below 32 items of 64 queries an
+  // XCD and head the work is too thin for that and 64 spread it wider (632 rows: 11.7 us a launch with 64, 15.6
   // with 128; 14,276 rows: 30.2 and 30.5; 58,499 rows: 99 and 90; three tiles a wave spill)
   return bf16 || rows > 16384 ? 128 : 64;
 }

@@ -208,10 +208,6 @@ hipError_t launch_embed(hipStream_t st, const float* xs, int ldx, int f, int64_t
                         const int32_t* tok_event, const float* temb, StageCtl* ctl,
                         const float* W_xin, int d, float* H, int ldh, float2* stats);
 
-// v = (alpha + beta t) xs, then the same ODE update, with t, h, mode and the output write
-// taken from desc[ctl->first], which it advances.
-// Output head for d_model 256 and 9 features: ode-update(LN(H; stats, g, s) Wt^T + b) over
-// the ode.m_valid valid rows, Wt float [>= 9, 256] (row c: weights of output c).
 // One block's BF16 cross K/V rows [rows][2d] into the head-major cache planes (plane rows
 // each; this block's first plane at dst): rows land at [row0, row0 + rows).
 hipError_t launch_kv_headmajor(hipStream_t st, const void* src, int64_t rows, int d, int dh,
@@ -241,6 +237,8 @@ hipError_t launch_select_offsets(hipStream_t st, const int32_t* cnt, int64_t n_e
 hipError_t launch_select_write(hipStream_t st, const float* feat, int ldf, const int64_t* off,
                                const int64_t* off_out, int64_t n_events, const uint8_t* keep,
                                float* out);
+// Output head for d_model 256 and 9 features: ode-update(LN(H; stats, g, s) Wt^T + b) over
+// the ode.m_valid valid rows, Wt float [>= 9, 256] (row c: weights of output c).
 bool head256_supported(int d, int nf);
 // As launch_head256 for d a multiple of 64 up to 256, with the LayerNorm statistics formed in
 // the kernel.
@@ -249,6 +247,8 @@ hipError_t launch_head_rows(hipStream_t st, int d, const float* H, const float* 
 hipError_t launch_head256(hipStream_t st, const float* H, const float2* stats, const float* g,
                           const float* s, const float* Wt, const float* b, const OdeArgs& ode);
 
+// v = (alpha + beta t) xs, then the same ODE update, with t, h, mode and the output write
+// taken from desc[ctl->first], which it advances.
 hipError_t launch_linear_update(hipStream_t st, float alpha, float beta, const StageDesc* desc,
                                 StageCtl* ctl, int64_t T, int f, float* x, float* acc,
                                 float* xs, int ldx, int ldo);
