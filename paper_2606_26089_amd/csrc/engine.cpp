@@ -694,7 +694,9 @@ SplitArgs split_args(fmd_model* m, const Call& c, int cls, const DevBlock& B, co
 
 // Times the candidates of every site of the split products (see autotune). Launches of a few
 // microseconds are close together and timed no better than that, so each of them takes the best of
-// eight, and a later candidate has to be clearly faster; longer ones take the best of two.
+// eight, and a later candidate has to be clearly faster; longer ones take the best of three and a
+// margin as well (448,552 rows, 64 against 32 rows a workgroup of a projection: 395 and 412 us on
+// eight runs, 432.6 and 431.9 on two).
 int autotune_split(fmd_model* m, Call& c) {
   const int b = bucket_of(c.Tp);
   const DevBlock& B = m->blk[0];
@@ -712,19 +714,20 @@ int autotune_split(fmd_model* m, Call& c) {
     int best = -1, rows = 0, parts = 0;
     float best_us = 0.f;
     for (int k = 0; k < kSplitCands; ++k) {
-      // Columns spread over workgroups: while the 32-row tiles are fewer than two a CU. From there
-      // on it only reads the rows again (51,000 rows, d = 256: up 154 us with 64 rows, 175 with 32,
-      // 162 and 191 spread; 14,000 rows: 44, 48, 47 and 48; 4,100 rows: 39, 25, 18 and 18).
-      if (k >= 2 && c.Tp / 32 >= 2 * 256) continue;
+      // Columns spread over two workgroups: below sixteen 32-row tiles a CU; over all: below two. From
+      // there on they only read the rows again (d = 256, up, us with 64 rows, 32 rows, 32 spread over
+      // two and four: 7,100 rows 39, 26, 27, 28; 19,000 rows 72, 61, 54, 60; 76,000 rows 205, 230, 196,
+      // 235; 130,000 rows 313, 359, 403, 394; 448,000 rows 1024, 1199, 1352, 1693).
+      if (k >= 2 && c.Tp / 32 >= (k == 2 ? 16 : 2) * 256) continue;
       if (!split_tile(k, c.Tp, p.N, &rows, &parts)) continue;
       const float us = time_best_us(
-          c.st, e0, e1, [&] { return launch_split_gemm(c.st, cls[sl], c.Tp, p, k); }, 8, 2);
+          c.st, e0, e1, [&] { return launch_split_gemm(c.st, cls[sl], c.Tp, p, k); }, 8, 3);
       if (us < 0.f) {
         status = fail(FMD_E_DEVICE, "autotune launch failed");
         break;
       }
       m->tune_all[sl][b][k] = us;
-      if (best < 0 || us < best_us * (best_us < 20.f ? 0.95f : 1.f)) best = k, best_us = us;
+      if (best < 0 || us < best_us * (best_us < 20.f ? 0.95f : 0.98f)) best = k, best_us = us;
     }
     m->tune[sl][b] = (int8_t)best;
     m->tune_us[sl][b] = best_us;
