@@ -16,7 +16,6 @@
 //   BF16: v_mfma_f32_16x16x32_bf16 (8 consecutive k per lane group), or 16x16x16 for dh 16
 // Accumulator layout: lane l, register r holds row 4(l/16) + r, column l%16.
 #include <algorithm>
-#include <limits>
 #include <vector>
 
 #include "common.h"
@@ -744,11 +743,11 @@ namespace {
 // The builder over accessors: queries of event k at q_off[ids[k]], nq(k) rows; its keys at
 // k0(k), nk(k) rows.
 template <typename Nq, typename K0, typename Nk>
-int64_t build_work(const int64_t* q_off, const int64_t* ids, int64_t n, int qt, bool deal, Nq nq,
+int64_t build_work(const int64_t* q_off, const int64_t* ids, int64_t n, int qt, int deal, Nq nq,
                    K0 k0, Nk nk, AttnItem* items, AttnBins* bins) {
   // longest-processing-time assignment of whole events to bins; cost = query tiles x keys. With
-  // `deal`, the tiles of an event that holds more than a quarter of a bin's fair share go to the
-  // least loaded bin one by one.
+  // `deal` heads, the tiles of an event of more than two workgroups for each CU of an XCD that holds
+  // more than a quarter of a bin's fair share go to the least loaded bin one by one.
   std::vector<int64_t> order;
   order.reserve((size_t)n);
   for (int64_t k = 0; k < n; ++k) {
@@ -759,12 +758,12 @@ int64_t build_work(const int64_t* q_off, const int64_t* ids, int64_t n, int qt, 
   auto tiles = [&](int64_t k) { return (nq(k) + qt - 1) / qt; };
   auto cost = [&](int64_t k) { return tiles(k) * nk(k); };
   std::stable_sort(order.begin(), order.end(), [&](int64_t a, int64_t b) { return cost(a) > cost(b); });
-  int64_t whole = std::numeric_limits<int64_t>::max();   // largest cost of an event kept whole
-  if (deal) {
-    int64_t total = 0;
-    for (int64_t k : order) total += cost(k);
-    whole = total / (4 * kAttnBins);
-  }
+  constexpr int kXcdCus = 32;
+  int64_t total = 0;
+  for (int64_t k : order) total += cost(k);
+  auto dealt_out = [&](int64_t k) {
+    return tiles(k) * deal > 2 * kXcdCus && cost(k) > total / (4 * kAttnBins);
+  };
   std::vector<int8_t> bin_of, tile_bin;   // per event (-1: dealt); per tile of the dealt ones, in turn
   bin_of.reserve(order.size());
   int64_t load[kAttnBins] = {0};
@@ -778,7 +777,7 @@ int64_t build_work(const int64_t* q_off, const int64_t* ids, int64_t n, int qt, 
     return (int8_t)best;
   };
   for (int64_t k : order) {
-    if (cost(k) <= whole) {
+    if (!dealt_out(k)) {
       bin_of.push_back(assign(cost(k), tiles(k)));
       continue;
     }
@@ -808,7 +807,7 @@ int64_t build_work(const int64_t* q_off, const int64_t* ids, int64_t n, int qt, 
 }  // namespace
 
 int64_t build_attention_work(const int64_t* q_off, const int64_t* kv_off, const int64_t* ids,
-                             int64_t n, int qt, bool deal, AttnItem* items, AttnBins* bins) {
+                             int64_t n, int qt, int deal, AttnItem* items, AttnBins* bins) {
   return build_work(
       q_off, ids, n, qt, deal, [&](int64_t k) { return q_off[ids[k] + 1] - q_off[ids[k]]; },
       [&](int64_t k) { return kv_off[ids[k]]; },
@@ -817,7 +816,7 @@ int64_t build_attention_work(const int64_t* q_off, const int64_t* kv_off, const 
 
 int64_t build_attention_work_kv(const int64_t* q_off, const int64_t* kv_start,
                                 const int64_t* kv_len, const int64_t* ids, int64_t n, int qt,
-                                bool deal, AttnItem* items, AttnBins* bins) {
+                                int deal, AttnItem* items, AttnBins* bins) {
   return build_work(
       q_off, ids, n, qt, deal, [&](int64_t k) { return q_off[ids[k] + 1] - q_off[ids[k]]; },
       [&](int64_t k) { return kv_start[ids[k]]; }, [&](int64_t k) { return kv_len[ids[k]]; },
@@ -835,8 +834,10 @@ int attention_query_tile(bool bf16, int dh, int64_t rows) {
 // The FP32 kernel of heads of 32 takes several times as long as the BF16 one for the same keys, so
 // one event on one XCD (32 of the 256 CUs) is the launch's time where a few large events make up
 // a call. Their tiles go to all XCDs, which then read the keys from the last-level cache each (one
-// event of 4,000, 8 heads: 858 us a launch whole, 143 dealt; the general kernel before: 230).
-bool attention_deal(bool bf16, int dh) { return !bf16 && dh == kH32; }
+// event of 4,000, 8 heads: 858 us a launch whole, 143 dealt; the general kernel before: 230). Events
+// that do not fill an XCD stay whole and read their keys from one L2 (60 events of 20-200, 8 heads:
+// 19.5 us a launch whole, 20.2 with the larger ones dealt).
+int attention_deal(bool bf16, int dh, int n_heads) { return !bf16 && dh == kH32 ? n_heads : 0; }
 
 int attention_query_tiles(bool bf16, int dh, int* tiles) {
   if (bf16 && dh == kH32) {

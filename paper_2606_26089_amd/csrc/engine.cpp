@@ -291,7 +291,7 @@ void flush_timing(fmd_model* m) {
 int bucket_of(int64_t Tp);
 int attn_tiles(const fmd_model* m, int* tiles);
 int attn_tile_for(const fmd_model* m, int64_t Tp);
-bool attn_deal(const fmd_model* m);
+int attn_deal(const fmd_model* m);
 template <typename F>
 float time_best_us(hipStream_t st, hipEvent_t e0, hipEvent_t e1, F&& launch, int reps = 3,
                    int reps_long = 3);
@@ -311,7 +311,7 @@ int stage_events(fmd_model* m, const fmd_events_in* ev, Call& c, const int64_t* 
   // work items: (event, query tile), in bins of whole events balanced by attention work
   int tiles[4];
   const int n_tiles = attn_tiles(m, tiles);
-  const bool deal = attn_deal(m);
+  const int deal = attn_deal(m);
   std::vector<int64_t> ids((size_t)E);
   auto count_items = [&](int qt) {
     int64_t k = 0;
@@ -502,8 +502,9 @@ int attn_tiles(const fmd_model* m, int* tiles) {
   return attention_query_tiles(m->cfg.precision != FMD_FP32,
                                m->cfg.d_model / std::max(m->cfg.n_heads, 1), tiles);
 }
-bool attn_deal(const fmd_model* m) {
-  return attention_deal(m->cfg.precision != FMD_FP32, m->cfg.d_model / std::max(m->cfg.n_heads, 1));
+int attn_deal(const fmd_model* m) {
+  const int heads = std::max(m->cfg.n_heads, 1);
+  return attention_deal(m->cfg.precision != FMD_FP32, m->cfg.d_model / heads, heads);
 }
 int attn_tile_for(const fmd_model* m, int64_t Tp) {
   int tiles[4];
@@ -2092,7 +2093,7 @@ int fmd_debug_attention(int32_t precision, int64_t n_events, const int64_t* q_of
   std::vector<AttnItem> work((size_t)n_items);
   AttnBins bins{};
   if (build_attention_work(q_offsets, kv_offsets, ids.data(), n_events, qt,
-                           attention_deal(precision == FMD_BF16, dh), work.data(), &bins) != n_items)
+                           attention_deal(precision == FMD_BF16, dh, n_heads), work.data(), &bins) != n_items)
     return fail(FMD_E_INVALID, "rows beyond 2^31");
   const int64_t Tq = q_offsets[n_events], Tk = kv_offsets[n_events];
   if (work.empty()) return FMD_OK;

@@ -156,7 +156,7 @@ int output_head(fmd_model* m, Call& c, const OdeArgs& ode);
 // FP32 path: truth encoding and cross K/V rows of nT truth particles (features u) into kv.
 hipError_t split_truth_cache(fmd_model* m, hipStream_t st, const float* u, int64_t nT, float* kv);
 int attn_tile_for(const fmd_model* m, int64_t Tp);   // attention query tile for a padded size
-bool attn_deal(const fmd_model* m);   // whether its work lists deal large events over the bins
+int attn_deal(const fmd_model* m);   // `deal` of its attention work lists
 int enter_stream(fmd_model* m, hipStream_t caller, Call& c);
 int leave_stream(fmd_model* m, hipStream_t caller);
 template <typename T> int truth_cache(fmd_model* m, Call& c);

@@ -126,8 +126,9 @@ hipError_t launch_row_stats(hipStream_t st, const float* A, int ld, int K, int64
 // with the tile it is given.
 int attention_query_tile(bool bf16, int dh, int64_t rows);
 int attention_query_tiles(bool bf16, int dh, int* tiles);   // candidates; returns their count
-// Whether the work lists of a precision and head width deal large events over the bins.
-bool attention_deal(bool bf16, int dh);
+// The heads for which the work lists of a precision and head width deal large events over the
+// bins, 0 where they do not.
+int attention_deal(bool bf16, int dh, int n_heads);
 
 // Attention work list split into kAttnBins bins of whole events with about equal work, each
 // bin's items stored contiguously (bin i: items [start[i], start[i] + len[i])). Workgroup b
@@ -146,15 +147,15 @@ struct AttnItem {
 // Fills `items` (capacity >= sum over the events of ceil(n_q / qt)) for the events ids[0..n)
 // of the CSR offsets q_off / kv_off (host arrays): events with the most work first within
 // each bin, bins balanced by attention work (longest-processing-time assignment, with `deal`
-// events that are large against a bin tile by tile); events without queries get no item. Returns
+// heads, if not 0, events that are large against a bin and an XCD tile by tile); events without queries get no item. Returns
 // the item count, or -1 if a row index exceeds 2^31-1.
 int64_t build_attention_work(const int64_t* q_off, const int64_t* kv_off, const int64_t* ids,
-                             int64_t n, int qt, bool deal, AttnItem* items, AttnBins* bins);
+                             int64_t n, int qt, int deal, AttnItem* items, AttnBins* bins);
 // As build_attention_work, with the keys of event e at rows kv_start[e] .. + kv_len[e] (for
 // key sets that are not one CSR sequence, e.g. truth rows of pooled requests).
 int64_t build_attention_work_kv(const int64_t* q_off, const int64_t* kv_start,
                                 const int64_t* kv_len, const int64_t* ids, int64_t n, int qt,
-                                bool deal, AttnItem* items, AttnBins* bins);
+                                int deal, AttnItem* items, AttnBins* bins);
 
 // Weights that the kernels after an attention launch will stream, read into every XCD's L2 beside
 // it (BF16 with dh 32; bytes 0: none).

@@ -50,13 +50,14 @@ def test_dealt_events_keep_their_bits(d, heads):
     """Events whose tiles are dealt in a small call, and that stay whole behind enough others; reco
     counts on both sides of the truth counts; the oracle within the bar of the parity tests."""
     torch, fmd = torch_cuda(), fmd_lib()
-    cfg = configs.ModelCfg(d_model=d, n_blocks=1, n_heads=heads, n_max=1000)
+    cfg = configs.ModelCfg(d_model=d, n_blocks=1, n_heads=heads, n_max=2100)
     flat = params.draw(cfg, 3, perturbed=True)
     m = fmd.Model(cfg, flat)
-    sizes = [300, 1, 0, 64, 65, 257]
+    sizes = [600, 1, 0, 64, 65, 257] if d == 256 else [2100, 1, 0, 64, 65, 257]
     off, (feat, x, t) = _inputs(torch, sizes)
     alone = m.velocity(off, feat, x, t)
-    off2, (feat2, x2, t2) = _inputs(torch, sizes + [100] * 500, seed=1)
+    more = 1200 if d == 256 else 12000            # the large event then stays whole
+    off2, (feat2, x2, t2) = _inputs(torch, sizes + [100] * more, seed=1)
     n = int(off[-1])
     feat2[:n], x2[:n], t2[:len(sizes)] = feat, x, t
     assert torch.equal(m.velocity(off2, feat2, x2, t2)[:n], alone)
@@ -67,7 +68,7 @@ def test_dealt_events_keep_their_bits(d, heads):
     assert errors.normwise_rel_err(alone.cpu().numpy(), ref).max() < 1e-5
     # reco counts of their own: the cross-attention list is another one
     sched = configs.Schedule(configs.EULER, 3)
-    reco = np.array([100, 3, 0, 300, 1, 257] + [90] * 500)
+    reco = np.array([100, 3, 0, 600, 1, 257] + [90] * more)
     roff = np.r_[0, np.cumsum(reco)].astype(np.int64)
     small = m.simulate(off, feat, 5, sched, reco_offsets=roff[:len(sizes) + 1])
     big = m.simulate(off2, feat2, 5, sched, reco_offsets=roff)
