@@ -759,13 +759,14 @@ int64_t build_work(const int64_t* q_off, const int64_t* ids, int64_t n, int qt, 
   auto cost = [&](int64_t k) { return tiles(k) * nk(k); };
   std::stable_sort(order.begin(), order.end(), [&](int64_t a, int64_t b) { return cost(a) > cost(b); });
   constexpr int kXcdCus = 32;
-  int64_t total = 0;
-  for (int64_t k : order) total += cost(k);
-  auto dealt_out = [&](int64_t k) {
-    return tiles(k) * deal > 2 * kXcdCus && cost(k) > total / (4 * kAttnBins);
-  };
-  std::vector<int8_t> bin_of, tile_bin;   // per event (-1: dealt); per tile of the dealt ones, in turn
-  bin_of.reserve(order.size());
+  size_t large = 0;   // events of more than a quarter of a bin's share: the first 32 at most
+  if (deal) {
+    int64_t total = 0;
+    for (int64_t k : order) total += cost(k);
+    while (large < order.size() && cost(order[large]) > total / (4 * kAttnBins)) ++large;
+  }
+  std::vector<int> bin_of(order.size());   // -1: dealt
+  std::vector<int> tile_bin;               // bins of the dealt events' tiles
   int64_t load[kAttnBins] = {0};
   int64_t cnt[kAttnBins] = {0};
   auto assign = [&](int64_t c, int64_t t) {
@@ -774,32 +775,35 @@ int64_t build_work(const int64_t* q_off, const int64_t* ids, int64_t n, int qt, 
       if (load[b] < load[best]) best = b;
     load[best] += c;
     cnt[best] += t;
-    return (int8_t)best;
+    return best;
   };
-  for (int64_t k : order) {
-    if (!dealt_out(k)) {
-      bin_of.push_back(assign(cost(k), tiles(k)));
-      continue;
+  for (size_t i = 0; i < order.size(); ++i) {
+    const int64_t k = order[i];
+    if (i < large && tiles(k) * deal > 2 * kXcdCus) {
+      bin_of[i] = -1;
+      for (int64_t q = 0; q < tiles(k); ++q) tile_bin.push_back(assign(nk(k), 1));
+    } else {
+      bin_of[i] = assign(cost(k), tiles(k));
     }
-    bin_of.push_back(-1);
-    for (int64_t q = 0; q < tiles(k); ++q) tile_bin.push_back(assign(nk(k), 1));
   }
   int64_t pos = 0;
+  auto put = [&](int64_t k, int64_t q) {
+    items[pos++] = AttnItem{(int32_t)(q_off[ids[k]] + q * qt),
+                            (int32_t)std::min<int64_t>(qt, nq(k) - q * qt), (int32_t)k0(k),
+                            (int32_t)nk(k)};
+  };
   bins->max_len = 0;
   for (int b = 0; b < kAttnBins; ++b) {
     bins->start[b] = (int32_t)pos;
     bins->len[b] = (int32_t)cnt[b];
     bins->max_len = std::max<int32_t>(bins->max_len, (int32_t)cnt[b]);
     size_t dealt = 0;
+    for (size_t i = 0; i < large; ++i)
+      for (int64_t q = 0; bin_of[i] < 0 && q < tiles(order[i]); ++q)
+        if (tile_bin[dealt++] == b) put(order[i], q);
     for (size_t i = 0; i < order.size(); ++i) {
-      if (bin_of[i] >= 0 && bin_of[i] != b) continue;
-      const int64_t k = order[i], e = ids[k];
-      for (int64_t q = 0; q < tiles(k); ++q) {
-        if (bin_of[i] < 0 && tile_bin[dealt++] != b) continue;
-        items[pos++] = AttnItem{(int32_t)(q_off[e] + q * qt),
-                                (int32_t)std::min<int64_t>(qt, nq(k) - q * qt),
-                                (int32_t)k0(k), (int32_t)nk(k)};
-      }
+      if (bin_of[i] != b) continue;
+      for (int64_t q = 0; q < tiles(order[i]); ++q) put(order[i], q);
     }
   }
   return pos;
